@@ -153,32 +153,28 @@ typedef struct {
   int32_t n_templates;          /* template blocks appended to P, 0 .. 16 */
   const mm_template_t* templates;  /* host [n_templates], or NULL when n_templates = 0 */
   int32_t fft_shape;            /* workgroup shape of the overlap-save transform (n_f / 2 complex
-                                   points): 0 = library default (for 2^14 and 2^15 points shape
-                                   10 in float32, for 2^14 shape 3 in float64; else 1);
-                                   1 = 16 points per thread,
-                                   radix-16 passes (32 points per
-                                   thread for 2^15 points); 2 = radix-32 passes, 32 points per
-                                   thread (64 for 2^15); 3 = 512 threads x 32 points, radix-16
-                                   passes, conjugate pairs of the real-to-complex step in
-                                   registers; 4 = shape 3 with the LDS exchanges split into real
-                                   and imaginary halves so two workgroups share a CU; 5 = 256
-                                   threads x 64 points, radix-32, split exchanges, two
-                                   workgroups per CU; 6 = 1024 threads x 16 points, radix-8
-                                   passes, pairs in registers; 7 = shape 6 with split exchanges,
-                                   two workgroups per CU; 8 = 512 threads x 32 points, radix-8
-                                   passes, pairs in registers; 9 = shape 6 with each exchange
-                                   made in two halves of the index space through half the LDS,
-                                   two workgroups per CU; 10 = 1024 threads x 16 points, a
-                                   four-step transform (16 x 1024) whose 1024-point stages
-                                   stay inside one wavefront (exchanges without workgroup
-                                   barriers), float32 only; for 2^15 points 1024 threads x 32
-                                   points (32 x 1024, two 1024-point rows per wavefront,
-                                   workgroup exchanges in two halves).  For 2^15 points shape
-                                   3 is 1024 threads x 32 points, radix-8 passes, pairs in
-                                   registers.  Shape 2 exists for float32 transforms of
-                                   2^13 .. 2^15 points, shapes 3 and 10 for 2^14 and 2^15
-                                   points, shapes 4 .. 9 for 2^14 points (3, 6 and 8 also in
-                                   float64); elsewhere shape 1 is used.  Ignored with n_f = -1 (the autotuner tries every
+                                   points): 0 = library default (shape 10 for 2^14 and 2^15
+                                   points in float32, else 1).  1 = 16 points per thread: from
+                                   2^10 points on (float64 up to 2^14, float32 up to 2^13) a
+                                   four-step transform of rows of 1024 points whose stages stay
+                                   inside one wavefront, elsewhere radix-16 passes through LDS
+                                   (32 points per thread for 2^15 points); 2 = radix-32 passes,
+                                   32 points per thread (64 for 2^15); 3 = 512 threads x 32
+                                   points, radix-16 passes; 4 = shape 3 with the LDS exchanges
+                                   split into real and imaginary halves so two workgroups share
+                                   a CU; 5 = 256 threads x 64 points, radix-32, split exchanges,
+                                   two workgroups per CU; 6 = 1024 threads x 16 points, radix-8
+                                   passes; 7 = shape 6 with split exchanges, two workgroups per
+                                   CU; 8 = 512 threads x 32 points, radix-8 passes; 9 = shape 6
+                                   with each exchange made in two halves of the index space
+                                   through half the LDS, two workgroups per CU; 10 = the
+                                   four-step transform of shape 1 for 2^14 (16 rows) and 2^15
+                                   points (32 rows, two per wavefront), float32 only.  For 2^15
+                                   points shape 3 is 1024 threads x 32 points, radix-8 passes.
+                                   Shape 2 exists for float32 transforms of 2^13 .. 2^15 points,
+                                   shapes 3 and 10 for 2^14 and 2^15 points, shapes 4 .. 9 for
+                                   2^14 points (3, 6 and 8 also in float64); elsewhere shape 1
+                                   is used.  Ignored with n_f = -1 (the autotuner tries every
                                    shape). */
 } mm_desc_t;
 

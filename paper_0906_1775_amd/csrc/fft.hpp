@@ -18,20 +18,18 @@
 // Thread t owns butterflies b = t + i NT.  After the last pass the output of
 // (b, r) is point b + r N/R_last, i.e. the natural order, strided.
 //
-// Paired layout (PAIRED, for shapes with an even number NB of butterflies per
-// thread in the last forward pass): there thread t > 0 owns butterflies
-// t + i NT (i even) and (NB - i + 1) NT - t (i odd), and thread 0 owns i NT,
-// instead of t + i NT.  Butterflies b and N/R - b hold the points k and N - k,
-// so after the forward transform every thread has both members of its
-// conjugate pairs (Z_k, Z_{N-k}) in registers.  The first pass of the
-// radix-reversed sequence shares that layout.
+// Shifted transform: X[k] = sum_n z_n exp(-2 pi i n (k + 1/4) / N).  Decimation in time
+// keeps the shift at every level, so it only moves the twiddles of every pass (row j of
+// the tables below becomes exp(-2 pi i (j + 1/4) r / (Ns R)), the first pass's single row
+// included); the transform along the other index, sum_k v_k exp(-2 pi i n (k + 1/4) / N),
+// is the plain one times exp(-2 pi i n / (4N)).
 //
 // Twiddles come from per-pass tables built once in float64 and rounded to T:
 // pass p with radix R and span Ns owns Ns rows of R entries,
 // row j = exp(-2 pi i j r / (Ns R)), r < R, so a thread reads its R-1 factors
 // as one contiguous row.  The forward and the radix-reversed sequences have
-// their own tables (tw_offset).  A second table tw2[k] = exp(-2 pi i k/(2N)),
-// k < N, serves the real-to-complex packing of the overlap-save filter.
+// their own tables (tw_offset); the forward one is the shifted one where the
+// overlap-save filter uses it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -48,15 +46,6 @@ template <typename T>
 __device__ __forceinline__ cx<T> cadd(cx<T> a, cx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T>
 __device__ __forceinline__ cx<T> csub(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }
-// Pairs of TOD elements at any element boundary (windows of intervals that start at an
-// odd sample): 4- and 8-byte aligned, where float2 / double2 need 8 and 16 (the loads and
-// stores are still single 8- and 16-byte accesses)
-struct alignas(4) FloatPairU { float x, y; };
-struct alignas(8) DoublePairU { double x, y; };
-template <typename T> struct PairU;
-template <> struct PairU<float> { using type = FloatPairU; };
-template <> struct PairU<double> { using type = DoublePairU; };
-
 template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
@@ -134,15 +123,13 @@ __device__ __forceinline__ void dft_reg(cx<T>* v) {
 // per pass); with LOGR < LOGE each thread runs E / R butterflies per pass.
 // FORCE_SPLIT: exchange real and imaginary parts separately even when N complex
 // points fit in LDS (half the LDS, so two workgroups can share a CU).
-// PAIRED: the paired layout of the last forward pass (see above).
 // HALF: exchange through an LDS buffer of N/2 complex points, the lower half of the
 // index space first, then the upper half.  Which half a point is written to and read
 // from never depends on the thread (the top index bit comes from the butterfly block
 // or from r), so each half moves as many b64 accesses as the full exchange, at twice
 // the barriers and half the LDS: two workgroups share a CU, one's exchanges overlapping
 // the other's arithmetic.
-template <typename T, int LOGN, int NT_, int LOGE, int LOGR_ = LOGE, bool FORCE_SPLIT = false,
-          bool PAIRED_ = false, bool HALF_ = false>
+template <typename T, int LOGN, int NT_, int LOGE, int LOGR_ = LOGE, bool FORCE_SPLIT = false, bool HALF_ = false>
 struct BlockFFT {
   static constexpr int N = 1 << LOGN;
   static constexpr int NT = NT_;
@@ -166,52 +153,32 @@ struct BlockFFT {
   static constexpr bool HALF = HALF_;
   static constexpr int half_bytes = (N / 2 + ((N / 2) >> cx_pad_log)) * 2 * (int)sizeof(T);
   static constexpr bool SPLIT = !HALF && (FORCE_SPLIT || cx_bytes > kLdsLimit);
-  static constexpr bool PAIRED = PAIRED_;
-  static_assert(!PAIRED || (NP >= 2 && (E >> LOGR_) % 2 == 0), "paired layout needs an even butterfly count");
-  // is pass p of a sequence in the paired layout (last forward pass, first reversed pass)
-  static constexpr bool pass_paired(bool fwd, int p) { return PAIRED && (fwd ? p == NP - 1 : p == 0); }
   static constexpr int LDS_BYTES = HALF ? half_bytes : (SPLIT ? sc_bytes : cx_bytes);
   static_assert(!HALF || (NT * (1 << LOGR_) <= N / 2 && (1 << LOGR_) >= 2 && (LOGN % LOGR_ == 0 || (1 << (LOGN % LOGR_)) >= 2)),
                 "half exchanges need at least two butterflies per thread");
-  static_assert(!HALF || !PAIRED || (E >> LOGR_) == 2, "half exchanges with the paired layout need two butterflies");
   static_assert(LDS_BYTES <= kLdsLimit, "transform does not fit in LDS");
 
   __device__ static __forceinline__ int cpad(int i) { return i + (i >> cx_pad_log); }
   __device__ static __forceinline__ int spad(int i) { return i + (i >> sc_pad_log); }
 
-  // butterfly handled as the i-th of thread t in a pass (PAIR: paired layout)
-  template <bool PAIR>
-  __device__ static __forceinline__ int bfly(int t, int i) {
-    if constexpr (PAIR) {
-      constexpr int NB = E >> LOGR_;   // butterflies per thread in the paired passes
-      if (i % 2 == 0) return t + i * NT;
-      return t == 0 ? i * NT : (NB - i + 1) * NT - t;
-    } else {
-      return t + i * NT;
-    }
-  }
+  // butterfly handled as the i-th of thread t in a pass
+  __device__ static __forceinline__ int bfly(int t, int i) { return t + i * NT; }
   // output position of element (i, r) of thread t after a pass (LOGR, LOGNS)
-  template <int LOGR, int LOGNS, bool PAIR = false>
-  __device__ static __forceinline__ int out_index(int t, int i, int r) {
-    const int b = bfly<PAIR>(t, i);
-    return ((b >> LOGNS) << (LOGNS + LOGR)) + (b & ((1 << LOGNS) - 1)) + (r << LOGNS);
+  // is out_base(t, i) + (r << LOGNS)
+  template <int LOGR, int LOGNS>
+  __device__ static __forceinline__ int out_base(int t, int i) {
+    const int b = bfly(t, i);
+    return ((b >> LOGNS) << (LOGNS + LOGR)) + (b & ((1 << LOGNS) - 1));
   }
   // input position of element (i, r) of thread t for a pass of radix 2^LOGR
-  template <int LOGR, bool PAIR = false>
+  template <int LOGR>
   __device__ static __forceinline__ int in_index(int t, int i, int r) {
-    return bfly<PAIR>(t, i) + (r << (LOGN - LOGR));
-  }
-  // out_index(t, i, r) = out_base(t, i) + (r << LOGNS)
-  template <int LOGR, int LOGNS, bool PAIR>
-  __device__ static __forceinline__ int out_base(int t, int i) {
-    const int b = bfly<PAIR>(t, i);
-    return ((b >> LOGNS) << (LOGNS + LOGR)) + (b & ((1 << LOGNS) - 1));
+    return bfly(t, i) + (r << (LOGN - LOGR));
   }
   // Index half (0: below N/2) of the output slot of element (i, r) of a pass (LOGR, LOGNS),
   // and of the input slot of element (i, r) of a pass of radix 2^LOGR2, for every thread.
   // Output: below the last pass the top bit is the top bit of the butterfly b < N/R,
-  // i.e. of its block i NT (t < NT <= N/(2R)); the paired layout's odd i own block
-  // NB - i = i (NB = 2).  In the last pass (Ns R = N) it is the top bit of r.  Input:
+  // i.e. of its block i NT (t < NT <= N/(2R)).  In the last pass (Ns R = N) it is the top bit of r.  Input:
   // b < N/R2, so the top bit of b + r N/R2 is that of r.
   template <int LOGR, int LOGNS>
   static constexpr int out_half(int i, int r) {
@@ -243,8 +210,9 @@ struct BlockFFT {
     for (int q = 0; q < p; ++q) s += log_radix(fwd, q);
     return s;
   }
+  // (the forward sequence's first pass has one row, which only the shifted transform reads)
   static constexpr int tw_count(bool fwd, int p) {
-    return log_span(fwd, p) == 0 ? 0 : (1 << (log_span(fwd, p) + log_radix(fwd, p)));
+    return !fwd && log_span(fwd, p) == 0 ? 0 : (1 << (log_span(fwd, p) + log_radix(fwd, p)));
   }
   static constexpr int tw_total_seq(bool fwd) {
     int o = 0;
@@ -258,15 +226,16 @@ struct BlockFFT {
   }
   static constexpr int tw_total() { return tw_total_seq(true) + tw_total_seq(false); }
 
-  // butterflies of one pass, in registers; ptab = this pass's table (rows of R factors)
-  template <int LOGR, int LOGNS, bool PAIR>
+  // butterflies of one pass, in registers; ptab = this pass's table (rows of R factors),
+  // not read when TW is false
+  template <int LOGR, int LOGNS, bool TW>
   __device__ static __forceinline__ void butterflies(cx<T>* v, const cx<T>* __restrict__ ptab, int t) {
     constexpr int R = 1 << LOGR;
     constexpr int NB = E / R;
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      if (LOGNS > 0) {
-        const int j = bfly<PAIR>(t, i) & ((1 << LOGNS) - 1);
+      if (TW) {
+        const int j = bfly(t, i) & ((1 << LOGNS) - 1);
         const cx<T>* __restrict__ w = ptab + (j << LOGR);
 #pragma unroll
         for (int r = 1; r < R; ++r) v[i * R + r] = cmul(v[i * R + r], w[r]);
@@ -276,7 +245,7 @@ struct BlockFFT {
   }
 
   // redistribute: element (i, r) of a pass (LOGR, LOGNS) goes to the slot of the next pass (LOGR2)
-  template <int LOGR, int LOGNS, int LOGR2, bool PAIR_OUT, bool PAIR_IN>
+  template <int LOGR, int LOGNS, int LOGR2>
   __device__ static __forceinline__ void exchange(cx<T>* v, void* lds_raw, int t) {
     constexpr int R = 1 << LOGR, NB = E / R;
     constexpr int R2 = 1 << LOGR2, NB2 = E / R2;
@@ -291,7 +260,7 @@ struct BlockFFT {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-          const int vb = out_base<LOGR, LOGNS, PAIR_OUT>(t, i);
+          const int vb = out_base<LOGR, LOGNS>(t, i);
 #pragma unroll
           for (int r = 0; r < R; ++r)
             if (out_half<LOGR, LOGNS>(i, r) == h) lds[padded<cx_pad_log, LOGNS>(vb, r) - h * HP] = v[i * R + r];
@@ -299,7 +268,7 @@ struct BlockFFT {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < NB2; ++i) {
-          const int vb = bfly<PAIR_IN>(t, i);
+          const int vb = bfly(t, i);
 #pragma unroll
           for (int r = 0; r < R2; ++r)
             if (in_half<LOGR2>(r) == h) nv[i * R2 + r] = lds[padded<cx_pad_log, LOGN - LOGR2>(vb, r) - h * HP];
@@ -312,14 +281,14 @@ struct BlockFFT {
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
-        const int vb = out_base<LOGR, LOGNS, PAIR_OUT>(t, i);
+        const int vb = out_base<LOGR, LOGNS>(t, i);
 #pragma unroll
         for (int r = 0; r < R; ++r) lds[padded<cx_pad_log, LOGNS>(vb, r)] = v[i * R + r];
       }
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < NB2; ++i) {
-        const int vb = bfly<PAIR_IN>(t, i);
+        const int vb = bfly(t, i);
 #pragma unroll
         for (int r = 0; r < R2; ++r) v[i * R2 + r] = lds[padded<cx_pad_log, LOGN - LOGR2>(vb, r)];
       }
@@ -332,7 +301,7 @@ struct BlockFFT {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-          const int vb = out_base<LOGR, LOGNS, PAIR_OUT>(t, i);
+          const int vb = out_base<LOGR, LOGNS>(t, i);
 #pragma unroll
           for (int r = 0; r < R; ++r)
             lds[padded<sc_pad_log, LOGNS>(vb, r)] = part ? v[i * R + r].im : v[i * R + r].re;
@@ -340,7 +309,7 @@ struct BlockFFT {
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < NB2; ++i) {
-          const int vb = bfly<PAIR_IN>(t, i);
+          const int vb = bfly(t, i);
 #pragma unroll
           for (int r = 0; r < R2; ++r) {
             const T x = lds[padded<sc_pad_log, LOGN - LOGR2>(vb, r)];
@@ -351,38 +320,34 @@ struct BlockFFT {
     }
   }
 
-  // pass p of a sequence (FWD: forward order of radices, else inverse order)
-  template <bool FWD, int p, int LOGNS>
+  // pass p of a sequence (FWD: forward order of radices, else inverse order); SHIFT: the
+  // tables are those of the shifted transform (the first pass has twiddles too)
+  template <bool FWD, bool SHIFT, int p, int LOGNS>
   __device__ static __forceinline__ void run_from(cx<T>* v, void* lds, const cx<T>* __restrict__ ptw,
                                                   int t) {
     constexpr int LR = FWD ? flog(p) : ilog(p);
-    constexpr bool PO = pass_paired(FWD, p);
-    butterflies<LR, LOGNS, PO>(v, ptw + tw_offset(FWD, p), t);
+    butterflies<LR, LOGNS, SHIFT || (LOGNS > 0)>(v, ptw + tw_offset(FWD, p), t);
     if constexpr (p + 1 < NP) {
       constexpr int LR2 = FWD ? flog(p + 1) : ilog(p + 1);
-      exchange<LR, LOGNS, LR2, PO, pass_paired(FWD, p + 1)>(v, lds, t);
-      run_from<FWD, p + 1, LOGNS + LR>(v, lds, ptw, t);
+      exchange<LR, LOGNS, LR2>(v, lds, t);
+      run_from<FWD, SHIFT, p + 1, LOGNS + LR>(v, lds, ptw, t);
     }
   }
 
   // Input: point (i, r) of thread t holds x[in_index<first radix>(t, i, r)].
-  // Output: point (i, r) holds X[fwd_out_index(t, i, r)] (forward DFT, no scaling).
+  // Output: point (i, r) holds X[t + i NT + r N / R_last] (forward DFT, no scaling).
   // ptw: the per-pass twiddle tables of this shape (tw_total() entries).
+  template <bool SHIFT = false>
   __device__ static __forceinline__ void forward(cx<T>* v, void* lds, const cx<T>* __restrict__ ptw,
                                                  int t) {
-    run_from<true, 0, 0>(v, lds, ptw, t);
+    run_from<true, SHIFT, 0, 0>(v, lds, ptw, t);
   }
-  // Same transform with the radix order reversed (first pass = forward's last radix);
+  // The plain transform with the radix order reversed (first pass = forward's last radix);
   // its input layout is the forward output layout, its output point (i, r) holds
   // X[t + i NT + r N / R_last] with R_last its last radix.
   __device__ static __forceinline__ void forward_rev(cx<T>* v, void* lds, const cx<T>* __restrict__ ptw,
                                                      int t) {
-    run_from<false, 0, 0>(v, lds, ptw, t);
-  }
-
-  // position of point (i, r) of thread t after forward()
-  __device__ static __forceinline__ int fwd_out_index(int t, int i, int r) {
-    return bfly<PAIRED>(t, i) + (r << (LOGN - flog(NP - 1)));
+    run_from<false, false, 0, 0>(v, lds, ptw, t);
   }
 
   static constexpr int first_log_fwd() { return flog(0); }
@@ -390,5 +355,32 @@ struct BlockFFT {
   static constexpr int first_log_rev() { return ilog(0); }
   static constexpr int last_log_rev() { return ilog(NP - 1); }
 };
+
+// Buffer of `bytes` bytes at p (uniform): loads past its end return 0 and stores past it
+// are dropped by the hardware's range check, offsets below it included (they wrap to the top
+// of the 32-bit range).
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ __forceinline__ Rsrc buffer_of(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void buffer_get(Rsrc b, uint32_t off, float& x) {
+  x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0));
+}
+__device__ __forceinline__ void buffer_get(Rsrc b, uint32_t off, double& x) {
+  x = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, 0));
+}
+__device__ __forceinline__ void buffer_put(Rsrc b, uint32_t off, float x) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), b, (int)off, 0, 0);
+}
+typedef unsigned UInt2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void buffer_put(Rsrc b, uint32_t off, double x) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(UInt2, x), b, (int)off, 0, 0);
+}
+// off, opaque to the optimiser: a constant added to an offset that may have wrapped below 0
+// must not move into the instruction's own (unwrapped) offset field
+__device__ __forceinline__ uint32_t opaque(uint32_t off) {
+  asm volatile("" : "+v"(off));
+  return off;
+}
 
 }  // namespace mm

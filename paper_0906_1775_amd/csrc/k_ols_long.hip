@@ -2,26 +2,20 @@
 // (n_f = 2^17 and 2^18: the lengths of the paper's FFT-length rule for n_c = 8192,
 // Weighting section, eqs. FFTcomplexity and FFTcomplexityFunction).
 //
-// The n_f = 2N real window is packed as N = N1 x N2 complex points z_n (as in the
-// on-chip kernel) and transformed by the four-step decomposition, n = N2 n1 + n2,
-// k = k1 + N1 k2:
-//   X[k1 + N1 k2] = sum_n2 W_N2^(n2 k2) [ W_N^(n2 k1) sum_n1 z[N2 n1 + n2] W_N1^(n1 k1) ],
+// The n_f = 2N real window x is z_n = x_n - i x_(n+N) (negacyclic embedding, see
+// k_ols_wave.hip), N = N1 x N2, and its shifted transform runs by the four-step
+// decomposition, n = N2 n1 + n2, k = k1 + N1 k2:
+//   Z[k1 + N1 k2] = sum_n2 W_N2^(n2 k2) [ W_N^(n2 (k1 + 1/4)) sum_n1 z[N2 n1 + n2] W_N1^(n1 (k1 + 1/4)) ],
 // in three kernels over a batch of (chunk, RHS) jobs whose N-point intermediates
 // stay in device memory (sized so that a batch fits the last-level cache):
-//   columns  N1-point transforms of the N2 columns (16 per workgroup, staged through
+//   columns  shifted N1-point transforms of the N2 columns (16 per workgroup, staged through
 //            LDS so that every global access covers 16 consecutive points), times
-//            W_N^(n2 k1), stored as rows Y[k1][n2];
-//   rows     N2-point transforms of rows k1 and N1 - k1 (one wavefront each), the
-//            real-to-complex pairing of X_k with X_(N-k) (row k1 element k2 pairs
-//            with row N1 - k1 element N2 - 1 - k2; row 0 with itself, k2 with
-//            N2 - k2), the filter symbol and the folding back to the packed output
-//            spectrum (conjugated, as in the on-chip kernel), then the N2-point
-//            transforms of the inverse's first step, times W_N^(k1 n2), in place;
-//   output   N1-point transforms of the columns, and the valid outputs (the real and
-//            negated imaginary parts, i.e. the conjugate) written back.
-// The inverse transform is conj(FFT(conj Z')) with the same decomposition read the
-// other way (input index k = k1 + N1 k2, output index n = N2 n1 + n2), and the 1/N
-// of the inverse and the pairing's halvings are in the symbol table F/(4N).
+//            W_N^(n2 (k1 + 1/4)), stored as rows Y[k1][n2];
+//   rows     N2-point transform of row k1 (one wavefront), conj(F Z), then the N2-point
+//            transform of the inverse's first step, times W_N^((k1 + 1/4) n2), in place;
+//   output   N1-point transforms of the columns times W_N1^(n1 / 4), and the valid outputs
+//            (the real parts y_n and the imaginary parts y_(n+N)) written back.
+// The 1/N of the inverse is in the symbol table F / N.
 #include <algorithm>
 
 #include "fft.hpp"
@@ -40,31 +34,29 @@ template <> struct SubShape<9> { static constexpr int LOGE = 3; };
 template <typename T, int L>
 using SubFFT = BlockFFT<T, L, 64, SubShape<L>::LOGE, SubShape<L>::LOGE>;
 
-constexpr int kL1 = 8;     // columns are 2^8-point transforms
-constexpr int kCW = 16;    // columns per workgroup of the column kernels
+constexpr int kL1 = kLongRowLog;   // columns are 2^8-point transforms
+constexpr int kCW = 16;    // columns per workgroup of the column kernels (one per wavefront)
 
-template <typename V> struct Pair2;
-template <> struct Pair2<float> { using type = float2; };
-template <> struct Pair2<double> { using type = double2; };
-
-// Tables of the four-step transform (LongTables): lo[j] = W_N^j (j < N2), hi[j] = W_N^(N2 j)
-// (j < N1), so W_N^j = hi[j / N2] lo[j mod N2] for j < N; r2[k2] = exp(-2 pi i k2 / (2 N2))
-// (k2 < N2), so the pairing's exp(-2 pi i k / (2N)) at k = k1 + N1 k2 is tw2[k1] r2[k2].
+// Table of the four-step transform: W_N^(n2 (k1 + 1/4)) = exp(-2 pi i j / (4N)), j = n2 (4 k1 + 1)
+// < 4N, as hi[j / (4 N2)] lo[j mod (4 N2)]: lo[j] = exp(-2 pi i j / (4N)) (j < 4 N2),
+// hi[j] = exp(-2 pi i j / N1) (j < N1).
 template <typename T, int L1, int L2>
 struct LongTables {
   static constexpr int N1 = 1 << L1, N2 = 1 << L2;
-  static constexpr int LO = 0, HI = N2, R2 = N2 + N1, TOTAL = 2 * N2 + N1;
+  static constexpr int LO = 0, HI = 4 * N2, TOTAL = 4 * N2 + N1;
 };
 
+// W_N^(n2 (k1 + 1/4))
 template <typename T, int L1, int L2>
-__device__ __forceinline__ cx<T> w_n(const cx<T>* __restrict__ tab, int j) {
+__device__ __forceinline__ cx<T> w_n(const cx<T>* __restrict__ tab, int n2, int k1) {
   using LT = LongTables<T, L1, L2>;
-  return cmul(tab[LT::HI + (j >> L2)], tab[LT::LO + (j & (LT::N2 - 1))]);
+  const int j = n2 * (4 * k1 + 1);
+  return cmul(tab[LT::HI + (j >> (L2 + 2))], tab[LT::LO + (j & (4 * LT::N2 - 1))]);
 }
 
 template <typename T, int L1, int L2>
 constexpr int col_lds_bytes() {
-  constexpr int a = 16 * SubFFT<T, L1>::LDS_BYTES;
+  constexpr int a = kCW * SubFFT<T, L1>::LDS_BYTES;
   constexpr int b = kCW * ((1 << L1) + 1) * (int)sizeof(cx<T>);
   constexpr int c = (1 << L1) * (kCW + 1) * (int)sizeof(cx<T>);
   return a > b ? (a > c ? a : c) : (b > c ? b : c);
@@ -72,7 +64,14 @@ constexpr int col_lds_bytes() {
 
 }  // namespace
 
-// columns of the forward transform: work[j][k1][n2] = W_N^(n2 k1) sum_n1 z[N2 n1 + n2] W_N1^(n1 k1)
+// Block of the column kernels: the hardware deals blocks to the 8 XCDs in turn, so XCD x takes
+// a contiguous run of column groups (their count is a multiple of 16), and neighbouring
+// groups, whose 64-byte runs of float32 samples share cache lines, meet in one L2.
+__device__ __forceinline__ uint32_t xcd_block() {
+  return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+}
+
+// columns of the forward transform: work[j][k1][n2] = W_N^(n2 (k1 + 1/4)) sum_n1 z[N2 n1 + n2] W_N1^(n1 (k1 + 1/4))
 template <typename T, typename Tin, int L1, int L2>
 __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ yin, cx<T>* __restrict__ work,
                                                        const OlsChunk* __restrict__ chunks, int64_t job0,
@@ -84,8 +83,9 @@ __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ y
   constexpr int N1 = 1 << L1, N2 = 1 << L2, NG = N2 / kCW, TS = N1 + 1, OS = kCW + 1;
   constexpr int64_t N = (int64_t)N1 * N2;
   __shared__ __align__(16) char lds[col_lds_bytes<T, L1, L2>()];
-  const int64_t jl = blockIdx.x / NG;
-  const int cg = blockIdx.x % NG;
+  const uint32_t wg = xcd_block();
+  const int64_t jl = wg / NG;
+  const int cg = wg % NG;
   const int64_t job = job0 + jl;
   const int rhs = (int)(job / n_chunks);
   if (st && !st[rhs].active) return;   // this RHS has stopped iterating
@@ -94,15 +94,15 @@ __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ y
   const int64_t s0 = ch.out_start - n_c, lo = ch.iv_lo, hi = ch.iv_hi;
   cx<T>* tile = reinterpret_cast<cx<T>*>(lds);
   const int tid = threadIdx.x;
-  // the workgroup's 16 columns, row by row: 16 consecutive points = 32 consecutive samples
+  // the workgroup's 16 columns, row by row: 16 consecutive points = two runs of 16 samples
 #pragma unroll
   for (int q = 0; q < N1 * kCW / 1024; ++q) {
     const int e = tid + 1024 * q;
     const int c = e % kCW, n1 = e / kCW;
-    const int64_t j = s0 + 2 * ((int64_t)N2 * n1 + cg * kCW + c);
+    const int64_t j = s0 + (int64_t)N2 * n1 + cg * kCW + c;
     const T a = (j >= lo && j < hi) ? (T)src[j] : (T)0;
-    const T b = (j + 1 >= lo && j + 1 < hi) ? (T)src[j + 1] : (T)0;
-    tile[c * TS + n1] = {a, b};
+    const T b = (j + N >= lo && j + N < hi) ? (T)src[j + N] : (T)0;
+    tile[c * TS + n1] = {a, -b};
   }
   __syncthreads();
   const int w = tid >> 6, t = tid & 63;   // wavefront w transforms column cg * 16 + w
@@ -111,10 +111,10 @@ __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ y
   for (int r = 0; r < F1::E; ++r) v[r] = tile[w * TS + t + 64 * r];
   // (the transform's first exchange begins with a barrier: every column is in registers
   // before any wavefront reuses the tile's LDS)
-  F1::forward(v, lds + w * F1::LDS_BYTES, ptw1, t);
+  F1::template forward<true>(v, lds + w * F1::LDS_BYTES, ptw1, t);
   const int n2 = cg * kCW + w;
 #pragma unroll
-  for (int r = 0; r < F1::E; ++r) v[r] = cmul(v[r], w_n<T, L1, L2>(ltab, n2 * (t + 64 * r)));   // n2 k1 < N
+  for (int r = 0; r < F1::E; ++r) v[r] = cmul(v[r], w_n<T, L1, L2>(ltab, n2, t + 64 * r));
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < F1::E; ++r) tile[(t + 64 * r) * OS + w] = v[r];
@@ -128,85 +128,59 @@ __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ y
   }
 }
 
-// rows k1 = g and N1 - g: forward N2-point transforms, pairing and symbol, then the
-// first step of the inverse (N2-point transforms, times W_N^(k1 n2)), in place
+// row k1: N2-point transform, symbol, then the first step of the inverse (N2-point
+// transform, times W_N^((k1 + 1/4) n2)), in place; one row per wavefront
+constexpr int kRowWaves = 1;
 template <typename T, int L1, int L2>
-__global__ __launch_bounds__(128) void k_long_rows(cx<T>* __restrict__ work, const OlsChunk* __restrict__ chunks,
-                                                   int64_t job0, int n_chunks, const CgState* __restrict__ st,
-                                                   const T* __restrict__ spec_rows, const cx<T>* __restrict__ ptw2,
-                                                   const cx<T>* __restrict__ tw2, const cx<T>* __restrict__ ltab) {
+__global__ __launch_bounds__(64 * kRowWaves) void k_long_rows(cx<T>* __restrict__ work,
+                                                              const OlsChunk* __restrict__ chunks, int64_t job0,
+                                                              int n_chunks, const CgState* __restrict__ st,
+                                                              const T* __restrict__ spec_rows,
+                                                              const cx<T>* __restrict__ ptw2,
+                                                              const cx<T>* __restrict__ ltab) {
   using F2 = SubFFT<T, L2>;
-  constexpr int N1 = 1 << L1, N2 = 1 << L2, NP = N1 / 2 + 1;
+  constexpr int N1 = 1 << L1, N2 = 1 << L2, WG = N1 / kRowWaves;
   constexpr int64_t N = (int64_t)N1 * N2;
-  __shared__ __align__(16) char lds[2 * F2::LDS_BYTES];
-  __shared__ cx<T> spx[2][N2];
-  const int64_t jl = blockIdx.x / NP;
-  const int g = blockIdx.x % NP;
+  __shared__ __align__(16) char lds[kRowWaves * F2::LDS_BYTES];
+  const int64_t jl = blockIdx.x / WG;
   const int64_t job = job0 + jl;
   const int rhs = (int)(job / n_chunks);
   if (st && !st[rhs].active) return;   // this RHS has stopped iterating
   const OlsChunk ch = chunks[job - (int64_t)rhs * n_chunks];
   const int w = threadIdx.x >> 6, t = threadIdx.x & 63;
-  const int a = g, b = (N1 - g) & (N1 - 1);   // a = b for rows 0 and N1/2 (both wavefronts hold it)
-  const int row = w == 0 ? a : b;
-  cx<T>* __restrict__ base = work + jl * N;
+  const int row = (int)(blockIdx.x % WG) * kRowWaves + w;
+  cx<T>* __restrict__ base = work + jl * N + (int64_t)row * N2;
   cx<T> v[F2::E];
 #pragma unroll
-  for (int r = 0; r < F2::E; ++r) v[r] = base[(int64_t)row * N2 + t + 64 * r];
-  F2::forward(v, lds + w * F2::LDS_BYTES, ptw2, t);
-  // v[r] = X[row + N1 k2], k2 = t + 64 r
-#pragma unroll
-  for (int r = 0; r < F2::E; ++r) spx[w][t + 64 * r] = v[r];
-  __syncthreads();
-  // For the pair (k, N-k): A = X_k, B = conj X_(N-k), E = A + B, O = -i (A - B),
-  // Y = (E + W O) F_k, Y' = (E - W O) F_(N-k), W = e^(-2 pi i k/(2N)); the transform of
-  // the inverse's input at k is conj(s + i W^-1 d), s = Y + Y', d = Y - Y'.
-  // the symbol in row order: SR[k1 N2 + k2] = F_(k1 + N1 k2) / (4N), SR[N] = F_N / (4N)
-  const T* __restrict__ SR = spec_rows + (int64_t)ch.filter * (N + 1);
-  using LT = LongTables<T, L1, L2>;
-  const cx<T> wrow = tw2[row];
+  for (int r = 0; r < F2::E; ++r) v[r] = base[t + 64 * r];
+  F2::forward_rev(v, lds + w * F2::LDS_BYTES, ptw2, t);
+  // v[r] = Z[row + N1 k2], k2 = t + 64 r; the symbol in row order
+  const T* __restrict__ SR = spec_rows + (int64_t)ch.filter * N + (int64_t)row * N2;
 #pragma unroll
   for (int r = 0; r < F2::E; ++r) {
-    const int k2 = t + 64 * r;
-    const cx<T> partner = row == 0 ? spx[w][(N2 - k2) & (N2 - 1)] : spx[1 - w][N2 - 1 - k2];
-    const cx<T> A = v[r];
-    const cx<T> B = cconj(partner);
-    const cx<T> Ev = cadd(A, B);
-    const cx<T> D = csub(A, B);
-    const cx<T> O = {D.im, -D.re};
-    const cx<T> W = cmul(wrow, ltab[LT::R2 + k2]);   // exp(-2 pi i k / (2N)), k = row + N1 k2
-    const cx<T> WO = cmul(W, O);
-    // F_(N-k): row N1 - row, element N2 - 1 - k2 (row 0: element N2 - k2, and F_N for k2 = 0)
-    const T sa = SR[(int64_t)row * N2 + k2];
-    const T sb = row != 0 ? SR[(int64_t)(N1 - row) * N2 + (N2 - 1 - k2)] : (k2 == 0 ? SR[N] : SR[N2 - k2]);
-    const cx<T> Y = cscale(cadd(Ev, WO), sa);
-    const cx<T> Yp = cscale(csub(Ev, WO), sb);
-    const cx<T> sum = cadd(Y, Yp);
-    const cx<T> Wd = cmul(cconj(W), csub(Y, Yp));
-    v[r] = {sum.re - Wd.im, -(sum.im + Wd.re)};
+    const T f = SR[t + 64 * r];
+    v[r] = {v[r].re * f, -(v[r].im * f)};
   }
-  F2::forward(v, lds + w * F2::LDS_BYTES, ptw2, t);
-  if (a == b && w == 1) return;   // the second copy of a row paired with itself
+  F2::forward_rev(v, lds + w * F2::LDS_BYTES, ptw2, t);
 #pragma unroll
-  for (int r = 0; r < F2::E; ++r) {
-    const int n2 = t + 64 * r;
-    base[(int64_t)row * N2 + n2] = cmul(v[r], w_n<T, L1, L2>(ltab, row * n2));   // row n2 < N
-  }
+  for (int r = 0; r < F2::E; ++r) base[t + 64 * r] = cmul(v[r], w_n<T, L1, L2>(ltab, t + 64 * r, row));
 }
 
-// columns of the inverse: N1-point transforms over k1, conjugated, and the valid outputs
+// columns of the inverse: N1-point transforms over k1, times W_N1^(n1 / 4), and the valid outputs
 template <typename T, int L1, int L2>
 __global__ __launch_bounds__(1024) void k_long_output(const cx<T>* __restrict__ work, T* __restrict__ yout,
                                                       const OlsChunk* __restrict__ chunks, int64_t job0,
                                                       int n_chunks, int64_t n_t, int n_c, int m,
                                                       const CgState* __restrict__ st,
-                                                      const cx<T>* __restrict__ ptw1) {
+                                                      const cx<T>* __restrict__ ptw1,
+                                                      const cx<T>* __restrict__ qtw) {
   using F1 = SubFFT<T, L1>;
   constexpr int N1 = 1 << L1, N2 = 1 << L2, NG = N2 / kCW, TS = N1 + 1, OS = kCW + 1;
   constexpr int64_t N = (int64_t)N1 * N2;
   __shared__ __align__(16) char lds[col_lds_bytes<T, L1, L2>()];
-  const int64_t jl = blockIdx.x / NG;
-  const int cg = blockIdx.x % NG;
+  const uint32_t wg = xcd_block();
+  const int64_t jl = wg / NG;
+  const int cg = wg % NG;
   const int64_t job = job0 + jl;
   const int rhs = (int)(job / n_chunks);
   if (st && !st[rhs].active) return;   // this RHS has stopped iterating
@@ -226,7 +200,9 @@ __global__ __launch_bounds__(1024) void k_long_output(const cx<T>* __restrict__ 
   cx<T> v[F1::E];
 #pragma unroll
   for (int r = 0; r < F1::E; ++r) v[r] = tile[w * TS + t + 64 * r];
-  F1::forward(v, lds + w * F1::LDS_BYTES, ptw1, t);
+  F1::forward_rev(v, lds + w * F1::LDS_BYTES, ptw1, t);
+#pragma unroll
+  for (int r = 0; r < F1::E; ++r) v[r] = cmul(v[r], qtw[t + 64 * r]);
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < F1::E; ++r) tile[(t + 64 * r) * OS + w] = v[r];   // output n1 = t + 64 r
@@ -236,10 +212,10 @@ __global__ __launch_bounds__(1024) void k_long_output(const cx<T>* __restrict__ 
   for (int q = 0; q < N1 * kCW / 1024; ++q) {
     const int e = tid + 1024 * q;
     const int c = e % kCW, n1 = e / kCW;
-    const int64_t pos = 2 * ((int64_t)N2 * n1 + cg * kCW + c);
+    const int64_t pos = (int64_t)N2 * n1 + cg * kCW + c;
     const cx<T> z = tile[n1 * OS + c];
     if (pos >= n_c && pos < n_c + m && s0 + pos < hi) dst[s0 + pos] = z.re;
-    if (pos + 1 >= n_c && pos + 1 < n_c + m && s0 + pos + 1 < hi) dst[s0 + pos + 1] = -z.im;
+    if (pos + N >= n_c && pos + N < n_c + m && s0 + pos + N < hi) dst[s0 + pos + N] = z.im;
   }
 }
 
@@ -250,27 +226,14 @@ __global__ void k_long_tables(cx<T>* __restrict__ tab) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= LT::TOTAL) return;
   double frac;   // angle / (-2 pi)
-  if (e < LT::HI) frac = (double)e / (double)(LT::N1 * LT::N2);
-  else if (e < LT::R2) frac = (double)(e - LT::HI) / (double)LT::N1;
-  else frac = (double)(e - LT::R2) / (double)(2 * LT::N2);
+  if (e < LT::HI) frac = (double)e / (4.0 * LT::N1 * LT::N2);
+  else frac = (double)(e - LT::HI) / (double)LT::N1;
   double sn, cs;
   sincospi(2.0 * frac, &sn, &cs);
   tab[e] = {(T)cs, (T)(-sn)};
 }
 
-// spec_rows[f][k1 N2 + k2] = spec[f][k1 + N1 k2], spec_rows[f][N] = spec[f][N]
-template <typename T, int L1, int L2>
-__global__ void k_long_symbol_rows(const T* __restrict__ spec, T* __restrict__ rows) {
-  constexpr int N1 = 1 << L1, N2 = 1 << L2;
-  constexpr int64_t N = (int64_t)N1 * N2;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e > N) return;
-  const T* __restrict__ src = spec + (int64_t)blockIdx.y * (N + 1);
-  T* __restrict__ dst = rows + (int64_t)blockIdx.y * (N + 1);
-  dst[e] = e == N ? src[N] : src[(e & (N2 - 1)) * N1 + (e >> L2)];
-}
-
-int ols_long_table_count(int logn) { return 2 * (1 << (logn - kL1)) + (1 << kL1); }
+int ols_long_table_count(int logn) { return 4 * (1 << (logn - kL1)) + (1 << kL1); }
 
 template <typename T, int L2>
 static hipError_t long_tables_launch(void* tab, hipStream_t s) {
@@ -279,28 +242,9 @@ static hipError_t long_tables_launch(void* tab, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int L2>
-static hipError_t symbol_rows_launch(const void* spec, void* rows, int n_filters, hipStream_t s) {
-  if (n_filters <= 0) return hipSuccess;
-  const int64_t n = (int64_t(1) << (kL1 + L2)) + 1;
-  hipLaunchKernelGGL((k_long_symbol_rows<T, kL1, L2>), dim3((unsigned)((n + 255) / 256), (unsigned)n_filters),
-                     dim3(256), 0, s, (const T*)spec, (T*)rows);
-  return hipGetLastError();
-}
-
 hipError_t launch_long_tables(int logn, bool fp64, void* tab, hipStream_t s) {
   if (logn == kL1 + 8) return fp64 ? long_tables_launch<double, 8>(tab, s) : long_tables_launch<float, 8>(tab, s);
   if (logn == kL1 + 9) return fp64 ? long_tables_launch<double, 9>(tab, s) : long_tables_launch<float, 9>(tab, s);
-  return hipErrorInvalidValue;
-}
-
-hipError_t launch_long_symbol_rows(int logn, bool fp64, const void* spec, void* rows, int n_filters, hipStream_t s) {
-  if (logn == kL1 + 8)
-    return fp64 ? symbol_rows_launch<double, 8>(spec, rows, n_filters, s)
-                : symbol_rows_launch<float, 8>(spec, rows, n_filters, s);
-  if (logn == kL1 + 9)
-    return fp64 ? symbol_rows_launch<double, 9>(spec, rows, n_filters, s)
-                : symbol_rows_launch<float, 9>(spec, rows, n_filters, s);
   return hipErrorInvalidValue;
 }
 
@@ -313,21 +257,21 @@ int64_t ols_long_batch(int logn, bool fp64) {
 
 template <typename T, typename Tin, int L2>
 static hipError_t long_launch(const void* y_in, void* y_out, const OlsChunk* chunks, int n_chunks, const void* spec,
-                              const void* ptw1, const void* ptw2, const void* tw2, const void* ltab, void* work,
+                              const void* ptw1, const void* ptw2, const void* qtw, const void* ltab, void* work,
                               int64_t batch, int64_t n_t, int n_c, int m, int n_rhs, hipStream_t s,
                               const CgState* st) {
-  constexpr int NG = (1 << L2) / kCW, NP = (1 << kL1) / 2 + 1;
+  constexpr int NG = (1 << L2) / kCW, NP = (1 << kL1) / kRowWaves;
   const int64_t n_jobs = (int64_t)n_chunks * n_rhs;
   for (int64_t j0 = 0; j0 < n_jobs; j0 += batch) {
     const int64_t nb = std::min(batch, n_jobs - j0);
     hipLaunchKernelGGL((k_long_columns<T, Tin, kL1, L2>), dim3((unsigned)(nb * NG)), dim3(1024), 0, s,
                        (const Tin*)y_in, (cx<T>*)work, chunks, j0, n_chunks, n_t, n_c, st, (const cx<T>*)ptw1,
                        (const cx<T>*)ltab);
-    hipLaunchKernelGGL((k_long_rows<T, kL1, L2>), dim3((unsigned)(nb * NP)), dim3(128), 0, s, (cx<T>*)work, chunks,
-                       j0, n_chunks, st, (const T*)spec, (const cx<T>*)ptw2, (const cx<T>*)tw2,
-                       (const cx<T>*)ltab);
+    hipLaunchKernelGGL((k_long_rows<T, kL1, L2>), dim3((unsigned)(nb * NP)), dim3(64 * kRowWaves), 0, s, (cx<T>*)work,
+                       chunks, j0, n_chunks, st, (const T*)spec, (const cx<T>*)ptw2, (const cx<T>*)ltab);
     hipLaunchKernelGGL((k_long_output<T, kL1, L2>), dim3((unsigned)(nb * NG)), dim3(1024), 0, s,
-                       (const cx<T>*)work, (T*)y_out, chunks, j0, n_chunks, n_t, n_c, m, st, (const cx<T>*)ptw1);
+                       (const cx<T>*)work, (T*)y_out, chunks, j0, n_chunks, n_t, n_c, m, st, (const cx<T>*)ptw1,
+                       (const cx<T>*)qtw);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -336,32 +280,32 @@ static hipError_t long_launch(const void* y_in, void* y_out, const OlsChunk* chu
 
 template <typename T, typename Tin>
 static hipError_t long_dispatch(int logn, const void* y_in, void* y_out, const OlsChunk* chunks, int n_chunks,
-                                const void* spec, const void* ptw1, const void* ptw2, const void* tw2,
+                                const void* spec, const void* ptw1, const void* ptw2, const void* qtw,
                                 const void* ltab, void* work, int64_t batch, int64_t n_t, int n_c, int m, int n_rhs,
                                 hipStream_t s, const CgState* st) {
   if (logn == kL1 + 8)
-    return long_launch<T, Tin, 8>(y_in, y_out, chunks, n_chunks, spec, ptw1, ptw2, tw2, ltab, work, batch, n_t, n_c,
+    return long_launch<T, Tin, 8>(y_in, y_out, chunks, n_chunks, spec, ptw1, ptw2, qtw, ltab, work, batch, n_t, n_c,
                                   m, n_rhs, s, st);
   if (logn == kL1 + 9)
-    return long_launch<T, Tin, 9>(y_in, y_out, chunks, n_chunks, spec, ptw1, ptw2, tw2, ltab, work, batch, n_t, n_c,
+    return long_launch<T, Tin, 9>(y_in, y_out, chunks, n_chunks, spec, ptw1, ptw2, qtw, ltab, work, batch, n_t, n_c,
                                   m, n_rhs, s, st);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_ols_long(bool fp64, bool in_f64, int logn, const void* y_in, void* y_out, const OlsChunk* chunks,
-                           int n_chunks, const void* spec_rows, const void* ptw1, const void* ptw2, const void* tw2,
+                           int n_chunks, const void* spec_rows, const void* ptw1, const void* ptw2, const void* qtw,
                            const void* ltab, void* work, int64_t batch, int64_t n_t, int n_c, int m, int n_rhs,
                            hipStream_t s, const CgState* st) {
   if (n_chunks == 0 || n_rhs == 0) return hipSuccess;
   if (batch < 1) return hipErrorInvalidValue;
   if (fp64)
-    return in_f64 ? long_dispatch<double, double>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, tw2,
+    return in_f64 ? long_dispatch<double, double>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, qtw,
                                                   ltab, work, batch, n_t, n_c, m, n_rhs, s, st)
-                  : long_dispatch<double, float>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, tw2,
+                  : long_dispatch<double, float>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, qtw,
                                                  ltab, work, batch, n_t, n_c, m, n_rhs, s, st);
-  return in_f64 ? long_dispatch<float, double>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, tw2, ltab,
+  return in_f64 ? long_dispatch<float, double>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, qtw, ltab,
                                                work, batch, n_t, n_c, m, n_rhs, s, st)
-                : long_dispatch<float, float>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, tw2, ltab,
+                : long_dispatch<float, float>(logn, y_in, y_out, chunks, n_chunks, spec_rows, ptw1, ptw2, qtw, ltab,
                                               work, batch, n_t, n_c, m, n_rhs, s, st);
 }
 

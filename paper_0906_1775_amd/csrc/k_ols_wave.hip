@@ -1,30 +1,42 @@
-// Overlap-save N^-1 with four-step transforms of 2^14 and 2^15 points whose inner
-// stages stay inside one wavefront (float32, n_f = 2^15 and 2^16; the paper's transform
-// is the chunked circulant embedding of its Weighting section).
+// Overlap-save N^-1 with transforms of N = 1024 NO complex points whose inner stages stay
+// inside one wavefront (NO = 1 .. 32; the paper's transform is the chunked circulant
+// embedding of its Weighting section).
 //
-// The N = 1024 NO packed complex points z_n (n = g + 1024 n_o, thread g of 1024 holds
-// n_o = 0..NO-1; NO = 16 or 32) are transformed as
-//   Z[k_o + NO k_in] = sum_g W_1024^(g k_in) [ W_N^(g k_o) sum_n_o z[g + 1024 n_o] W_NO^(n_o k_o) ]:
-// NO-point DFTs in registers, a workgroup exchange that gives wavefront w the row k_o = w
-// (and, for NO = 32, the row w + 16: the exchange then runs in two halves), then a
-// 1024-point DFT of each row inside the wavefront (lane l and register j hold index
-// l + 64 j): 16-point DFTs over j, a twiddle, an exchange through the wavefront's own LDS
-// row, 4-point DFTs across lane groups, a twiddle, a second private exchange and 16-point
-// DFTs.  Its output sits at lane mu, register c2 for index mu + 64 c2, which is the input
-// layout of the same stage, so the inverse (a forward transform of the conjugate, read
-// with the decomposition the other way round: 1024-point stage first, twiddle
-// W_N^(n_a k_o), workgroup exchange, NO-point DFTs) reuses it.  Only the outer exchanges
-// of each transform and the real-to-complex pairing span the workgroup; the private ones
-// need no barrier, so the wavefronts of a SIMD drift apart and one's exchanges overlap
-// another's arithmetic.
+// Embedding.  A band of half-width n_c is applied exactly, away from the window's ends, by
+// any cyclic extension of the window: also by the negacyclic one (t^(2N) = -1 instead of
+// 1).  A real window x of 2N samples modulo t^(2N) + 1 is the N complex points
+//   z_n = x_n - i x_(n + N)   (t^N = -i),
+// so one shifted transform
+//   Z_k = sum_n z_n exp(-2 pi i n (k + 1/4) / N)
+// holds its whole spectrum, a symmetric band multiplies it by the real symbol
+//   F_k = f(0) + 2 sum_tau f(tau) cos(2 pi (k + 1/4) tau / N),
+// and no real-to-complex pairing of Z_k with Z_(N-k) is needed between the forward and the
+// inverse transform: every point meets only its own symbol value, in the register it is in.
+// (The pairing it replaces cost a workgroup exchange, two barriers, 14 operations per point
+// and the packing twiddles.)  The inverse is y_n + i y_(n + N) =
+// sum_k conj(F_k Z_k) exp(-2 pi i n (k + 1/4) / N) (the table holds F_k / N).
 //
-// Pairing: Z_k (row k_o, k_in) meets Z_(N-k) at row NO - k_o, 1023 - k_in (row 0: row 0,
-// (1024 - k_in) mod 1024) through the LDS rows.  For NO = 16 the side with k_in < 512
-// forms both new points and writes its partner's back; for NO = 32 wavefront w >= 1 forms
-// every pair of its row w with row 32 - w (wavefront 16 - w's second row, which waits in
-// LDS), and wavefront 0 pairs rows 0 and 16 within themselves.  The symbol and the packing
-// twiddle are read in the same row order (tables built by launch_wave_tables /
-// launch_wave_symbols).
+// Transform.  n = g + 1024 n_o (g = l + 64 j, l = m + 16 h) and k = k_o + NO (k1 + 16 c1 +
+// 64 c2).  The inner stages run by decimation in time with the twiddles inside the
+// butterflies (a + w b, a - w b), so that no separate twiddle multiplications remain there.
+// A shift of the frequency passes down every level of a decimation in time unchanged, so
+// the 1/4 costs nothing in the forward direction, and each stage's leftover twiddle is a
+// shift of the next:
+//   forward   outer  NO points over n_o           (shift 1/4, constants)        -> k_o
+//             workgroup exchange: wavefront w takes row k_o = w (NO = 32: and w + 16)
+//             16 points over j, shift s1 = (k_o + 1/4) / NO                     -> k1
+//             private exchange, 4 points over h, shift s2 = (k1 + s1) / 16      -> c1
+//             private exchange, 16 points over m, shift s3 = (c1 + s2) / 4      -> c2
+//   symbol    lane mu = k1 + 16 c1, register c2
+//   inverse   16 points over c2 (no shift)                                      -> m
+//             private exchange, 4 points over c1, shift m / 16                  -> h
+//             private exchange, 16 points over k1, shift l / 64                 -> j
+//             twiddle exp(-2 pi i g (k_o + 1/4) / N), workgroup exchange, NO points over
+//             k_o (the transpose of the first stage), stores.
+// Private exchanges go through the wavefront's own LDS row and need no barrier, so the
+// wavefronts of a workgroup drift apart and one's exchanges overlap another's arithmetic.
+// In float64 every exchange moves the real parts, then the imaginary parts, through the
+// same LDS space.
 #include <algorithm>
 #include <type_traits>
 
@@ -35,25 +47,41 @@ namespace mm {
 
 namespace {
 
-constexpr int kWN = 1 << 14;      // complex points of the 16 x 1024 transform
-constexpr int kWN32 = 1 << 15;    // complex points of the 32 x 1024 transform
-constexpr int kWRow = 1088;       // LDS row stride (1024 + 64 padding for the second private exchange)
-// table offsets (complex entries): twB[k * 64 + l] = W_1024^(l k), twC[c * 16 + m] = W_64^(m c),
-// twA[k * 1024 + g] = W_N^(g k) (k < NO; the forward's outer twiddle and the inverse's),
-// tw2[r * 1024 + k_in] = W_2N^(r + NO k_in) (r < NO)
-constexpr int kTB = 0, kTC = 1024, kTA = 1088;
-constexpr int wave_t2(int logn) { return kTA + (1 << logn); }
-constexpr int wave_table_total(int logn) { return kTA + 2 * (1 << logn); }
-constexpr int kT2 = wave_t2(14);
+constexpr int kWRow = 1088;   // LDS row stride in 8-byte slots (1024 + 64 padding for the second private exchange)
 
-// l, opaque to the optimiser: table reads indexed by the result cannot be hoisted to the
-// kernel's start (where they would stay live across the whole transform and spill)
-// (the result is masked back to a lane index so that the compiler still knows its range
-// and forms 32-bit offsets from the uniform table bases)
-__device__ __forceinline__ int opaque(int l) {
-  asm volatile("" : "+v"(l));
-  return l & 63;
-}
+// NO rows of 1024 points; a thread holds C columns of NO points in the outer stages, RPW
+// rows of 16 points in the inner ones.
+template <int NO, int RPW_>
+struct WaveShape {
+  static constexpr int N = 1024 * NO;
+  static constexpr int RPW = RPW_;               // rows per wavefront
+  static constexpr int NW = NO / RPW;            // wavefronts
+  static constexpr int NT = 64 * NW;
+  static constexpr int E = 16 * RPW;
+  static constexpr int C = E / NO;
+  static constexpr int LDS_SLOTS = NW * kWRow;
+  static constexpr int LOGNO = NO == 1 ? 0 : NO == 2 ? 1 : NO == 4 ? 2 : NO == 8 ? 3 : NO == 16 ? 4 : 5;
+  static_assert(NO == 1 << LOGNO && NW * RPW == NO && NW <= 16 && C * NO == E, "shape");
+};
+
+// Twiddle tables (complex entries).  A decimation-in-time stage of 2^s points with shift
+// sigma needs exp(-2 pi i (j + sigma) / len) for len = 2, 4, .., 2^s, j < max(1, len / 4) (the
+// other quarter is -i times these).  The tables hold j = 0, the s values
+// exp(-2 pi i sigma / len); the others follow by constants, one operation per point and one
+// rounding more, because table loads (from L2, a few dozen per thread) cost more than
+// arithmetic here: with all eight values of a 16-point stage in the tables 2^26 samples at
+// n_c = 8192 take 299 us instead of 227 (float32, NO = 32) and 571 instead of 528 (float64,
+// NO = 16).
+template <int NO>
+struct WaveTables {
+  static constexpr int F1 = 0;                      // [NO][8]: sigma = s1, j < max(1, len / 4)
+  static constexpr int F2 = F1 + NO * 8;            // [NO][16 k1][2]: sigma = s2
+  static constexpr int F3 = F2 + NO * 32;           // [NO][64 mu][4]: sigma = s3
+  static constexpr int I2 = F3 + NO * 256;          // [16 m][2]: sigma = m / 16
+  static constexpr int I3 = I2 + 32;                // [64 l][4]: sigma = l / 64
+  static constexpr int I4 = I3 + 256;               // [NO k_o][1024 g]: exp(-2 pi i g (k_o + 1/4) / N)
+  static constexpr int TOTAL = I4 + NO * 1024;
+};
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -61,10 +89,170 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 16-point DFT in registers, natural order in and out, as 4 x 4:
+// cos(2 pi k / 128), k in [0, 32] (correctly rounded decimal expansions)
+__host__ __device__ constexpr double cos128_quarter(int k) {
+  constexpr double c[33] = {
+      1.0, 0.99879545620517239271477160, 0.99518472667219688624483695, 0.98917650996478097345167373,
+      0.98078528040323044912618223, 0.97003125319454399260398420, 0.95694033573220886493579788,
+      0.94154406518302077841250940, 0.92387953251128675612818318, 0.90398929312344333158620029,
+      0.88192126434835502971275686, 0.85772861000027206990226998, 0.83146961230254523707878837,
+      0.80320753148064490980667651, 0.77301045336273696081090660, 0.74095112535495909117561689,
+      0.70710678118654752440084436, 0.67155895484701840062537685, 0.63439328416364549821517161,
+      0.59569930449243334346703652, 0.55557023301960222474283081, 0.51410274419322172659369383,
+      0.47139673682599764855638762, 0.42755509343028209432096685, 0.38268343236508977172845998,
+      0.33688985339222005068925321, 0.29028467725446236763619237, 0.24298017990326388994827416,
+      0.19509032201612826784828486, 0.14673047445536175165885012, 0.09801714032956060199419556,
+      0.04906767432741801425495497, 0.0};
+  return c[k];
+}
+
+// exp(-2 pi i k / 128), a compile-time constant after unrolling
+template <typename T>
+__device__ __forceinline__ constexpr cx<T> unit128(int k) {
+  const int q = (k >> 5) & 3, f = k & 31;   // quarter turns, rest
+  const T c = (T)cos128_quarter(f), s = (T)cos128_quarter(32 - f);
+  return q == 0 ? cx<T>{c, -s} : q == 1 ? cx<T>{-s, -c} : q == 2 ? cx<T>{-c, s} : cx<T>{s, c};
+}
+
+// a + w b and a - w b by fused multiply-adds
+template <typename T>
+__device__ __forceinline__ cx<T> madd(cx<T> a, cx<T> w, cx<T> b) {
+  return {fma(w.re, b.re, fma(-w.im, b.im, a.re)), fma(w.re, b.im, fma(w.im, b.re, a.im))};
+}
+template <typename T>
+__device__ __forceinline__ cx<T> msub(cx<T> a, cx<T> w, cx<T> b) {
+  return {fma(-w.re, b.re, fma(w.im, b.im, a.re)), fma(-w.re, b.im, fma(-w.im, b.re, a.im))};
+}
+
+// 4-point DFT of (a, w1 b, w2 c, w3 d), natural order out
+template <typename T>
+__device__ __forceinline__ void bfly4(cx<T>& a, cx<T>& b, cx<T>& c, cx<T>& d, cx<T> w1, cx<T> w2, cx<T> w3) {
+  const cx<T> t0 = madd(a, w2, c), t1 = msub(a, w2, c);
+  const cx<T> u = cmul(b, w1);
+  const cx<T> t2 = madd(u, w3, d), t3 = msub(u, w3, d);
+  a = cadd(t0, t2);
+  c = csub(t0, t2);
+  b = {t1.re + t3.im, t1.im - t3.re};   // t1 - i t3
+  d = {t1.re - t3.im, t1.im + t3.re};
+}
+
+// Decimation-in-time transform of R = 2^LOGR <= 16 points in registers, natural order in and
+// out: X[k] = sum_n v[n] exp(-2 pi i n (k + sigma) / R), by radix-2 butterflies
+// (a + w b, a - w b); tw(len, j) = exp(-2 pi i (j + sigma) / len), j < max(1, len / 4).
+// SUM6: six operations per butterfly, the difference as 2 a - (a + w b), which carries the
+// sum's rounding along; else eight.
+template <typename T, int LOGR, bool SUM6, typename Tw>
+__device__ __forceinline__ void dit(cx<T>* v, Tw tw) {
+  constexpr int R = 1 << LOGR;
+  cx<T> x[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) x[k] = v[bitrev(k, LOGR)];
+#pragma unroll
+  for (int s = 1; s <= LOGR; ++s) {
+    const int len = 1 << s, half = len >> 1, q = len >> 2;
+#pragma unroll
+    for (int j = 0; j < (s == 1 ? 1 : q); ++j) {
+      const cx<T> u = tw(len, j);
+#pragma unroll
+      for (int h = 0; h < (s == 1 ? 1 : 2); ++h) {   // j, and a quarter of len further: -i times the twiddle
+        const cx<T> wj = h ? cx<T>{u.im, -u.re} : u;
+#pragma unroll
+        for (int k = j + h * q; k < R; k += len) {
+          const cx<T> sum = madd(x[k], wj, x[k + half]);
+          x[k + half] = SUM6 ? cx<T>{fma((T)2, x[k].re, -sum.re), fma((T)2, x[k].im, -sum.im)}
+                             : msub(x[k], wj, x[k + half]);
+          x[k] = sum;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) v[k] = x[k];
+}
+
+// the twiddle (len, j) from the len = 2, 4, 8, 16 ones of j = 0
+template <typename T>
+__device__ __forceinline__ cx<T> derived(const cx<T>* w, int len, int j) {
+  const cx<T> u = w[len == 2 ? 0 : len == 4 ? 1 : len == 8 ? 2 : 3];
+  return j == 0 ? u : cmul(u, unit128<T>(j * (128 / len)));
+}
+
+// The same for R <= 32, sigma = 1/4 and compile-time twiddles, in radix-4 levels after a
+// radix-2 one when LOGR is odd (28 operations per radix-4 butterfly, fewer roundings)
+template <typename T, int LOGR>
+__device__ __forceinline__ void dit_quarter(cx<T>* v) {
+  constexpr int R = 1 << LOGR, FIRST = LOGR % 2 ? 8 : 4;
+  cx<T> x[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) x[k] = v[bitrev(k, LOGR)];
+  if constexpr (LOGR % 2) {
+#pragma unroll
+    for (int k = 0; k < R; k += 2) {
+      const cx<T> a = x[k], b = x[k + 1];
+      x[k] = madd(a, unit128<T>(16), b);
+      x[k + 1] = msub(a, unit128<T>(16), b);
+    }
+  }
+#pragma unroll
+  for (int len = FIRST; len <= R; len *= 4) {
+    const int q = len / 4;
+#pragma unroll
+    for (int j = 0; j < q; ++j) {
+      const int h = (4 * j + 1) * (32 / len);
+#pragma unroll
+      for (int k = j; k < R; k += len) {   // residues 0, 2, 1, 3 mod 4 of the sub-transforms, bit-reversed
+        cx<T> a = x[k], c = x[k + q], b = x[k + 2 * q], d = x[k + 3 * q];
+        bfly4(a, b, c, d, unit128<T>(h), unit128<T>(2 * h), unit128<T>(3 * h));
+        x[k] = a;
+        x[k + q] = b;
+        x[k + 2 * q] = c;
+        x[k + 3 * q] = d;
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) v[k] = x[k];
+}
+
+// Its transpose, X[n] = sum_k v[k] exp(-2 pi i n (k + 1/4) / R): the same levels in reverse
+// order, a 4-point DFT followed by the twiddles
+template <typename T, int LOGR>
+__device__ __forceinline__ void dif_quarter(cx<T>* v) {
+  constexpr int R = 1 << LOGR, FIRST = LOGR % 2 ? 8 : 4;
+#pragma unroll
+  for (int len = R; len >= FIRST; len /= 4) {
+    const int q = len / 4;
+#pragma unroll
+    for (int j = 0; j < q; ++j) {
+#pragma unroll
+      for (int k = j; k < R; k += len) {
+        const cx<T> a = v[k], b = v[k + q], c = v[k + 2 * q], d = v[k + 3 * q];
+        const cx<T> t0 = cadd(a, c), t1 = csub(a, c), t2 = cadd(b, d), t3 = csub(b, d);
+        const int h = (4 * j + 1) * (32 / len);
+        v[k] = cadd(t0, t2);
+        v[k + q] = cmul(csub(t0, t2), unit128<T>(2 * h));   // residue 2, in bit-reversed place
+        v[k + 2 * q] = cmul(cx<T>{t1.re + t3.im, t1.im - t3.re}, unit128<T>(h));
+        v[k + 3 * q] = cmul(cx<T>{t1.re - t3.im, t1.im + t3.re}, unit128<T>(3 * h));
+      }
+    }
+  }
+  if constexpr (LOGR % 2) {
+#pragma unroll
+    for (int k = 0; k < R; k += 2) {
+      const cx<T> a = v[k], b = v[k + 1];
+      v[k] = cadd(a, b);
+      v[k + 1] = cmul(csub(a, b), unit128<T>(16));
+    }
+  }
+  cx<T> x[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) x[k] = v[bitrev(k, LOGR)];
+#pragma unroll
+  for (int k = 0; k < R; ++k) v[k] = x[k];
+}
+
+// Plain 16-point DFT in registers, natural order in and out, as 4 x 4:
 // X[k1 + 4 k2] = sum_n2 W_4^(n2 k2) [ W_16^(n2 k1) sum_n1 x[n2 + 4 n1] W_4^(n1 k1) ]
-// (8 4-point DFTs and 9 twiddles, one of them -i: 160 VALU operations against 168 for
-// four radix-2 stages)
 template <typename T>
 __device__ __forceinline__ void dft4(cx<T>& a0, cx<T>& a1, cx<T>& a2, cx<T>& a3) {
   const cx<T> t0 = cadd(a0, a2), t1 = csub(a0, a2), t2 = cadd(a1, a3), t3 = csub(a1, a3);
@@ -97,562 +285,332 @@ __device__ __forceinline__ void dft16(cx<T>* v) {
   for (int k = 0; k < 16; ++k) v[k] = y[k];
 }
 
-// 32-point DFT in registers, natural order in and out: radix-2 butterflies of n and
-// n + 16 with W_32^n on the differences, then two 16-point DFTs:
-// X[2 k + b] = sum_n W_16^(n k) [ W_32^(n b) (x[n] + (-1)^b x[n + 16]) ]
-template <typename T>
-__device__ __forceinline__ void dft32(cx<T>* v) {
-  cx<T> e[16], o[16];
-#pragma unroll
-  for (int n = 0; n < 16; ++n) {
-    e[n] = cadd(v[n], v[n + 16]);
-    o[n] = twiddle_const(csub(v[n], v[n + 16]), n, 32);
-  }
-  dft16<T>(e);
-  dft16<T>(o);
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    v[2 * k] = e[k];
-    v[2 * k + 1] = o[k];
-  }
-}
+// 8-byte LDS slots: a float32 point, or one part of a float64 point
+template <typename T> struct Slot;
+template <> struct Slot<float> { using type = cx<float>; };
+template <> struct Slot<double> { using type = double; };
 
-// dft32's factorization transposed (the same DFT): 16-point DFTs of the even and odd
-// inputs, W_32^n on the odd ones, radix-2 butterflies X[n], X[n + 16]
-template <typename T>
-__device__ __forceinline__ void dft32_t(cx<T>* v) {
-  cx<T> e[16], o[16];
+// v[i] <- the value that wrote slot rd(i), where this lane's v[i] goes to slot wr(i); the
+// slots belong to this wavefront
+template <typename T, typename Wr, typename Rd>
+__device__ __forceinline__ void exchange_private(cx<T>* v, typename Slot<T>::type* row, Wr wr, Rd rd) {
+  if constexpr (sizeof(T) == 4) {
+    wave_sync();
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    e[k] = v[2 * k];
-    o[k] = v[2 * k + 1];
-  }
-  dft16<T>(e);
-  dft16<T>(o);
+    for (int i = 0; i < 16; ++i) row[wr(i)] = v[i];
+    wave_sync();
 #pragma unroll
-  for (int n = 0; n < 16; ++n) {
-    const cx<T> t = twiddle_const(o[n], n, 32);
-    v[n] = cadd(e[n], t);
-    v[n + 16] = csub(e[n], t);
-  }
-}
-
-// 1024-point DFT of a wavefront's row: lane l, register j hold a[l + 64 j] on entry;
-// lane mu, register c2 hold A[mu + 64 c2] on exit.  row: this wavefront's LDS row.
-template <typename T>
-__device__ __forceinline__ void inner_dft(cx<T>* v, cx<T>* row, const cx<T>* __restrict__ tab, int l) {
-  // a[l + 64 j]: 16-point DFTs over j (output k1), twiddle W_1024^(l k1)
-  l = opaque(l);
-  dft16<T>(v);
-#pragma unroll
-  for (int k = 1; k < 16; ++k) v[k] = cmul(v[k], tab[(uint32_t)(kTB + k * 64 + l)]);
-  // private exchange: value (k1, l) to k1 * 64 + l; lane (m, h) = (l & 15, l >> 4) takes
-  // k1 = 4h + e and l' = m + 16 lh
-  wave_sync();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) row[k * 64 + l] = v[k];
-  wave_sync();
-  const int m = l & 15, h = l >> 4;
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int lh = 0; lh < 4; ++lh) v[e * 4 + lh] = row[(4 * h + e) * 64 + m + 16 * lh];
-  // 4-point DFTs over lh (output c1), twiddle W_64^(m c1)
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    dft4(v[e * 4], v[e * 4 + 1], v[e * 4 + 2], v[e * 4 + 3]);
-#pragma unroll
-    for (int c = 1; c < 4; ++c) v[e * 4 + c] = cmul(v[e * 4 + c], tab[(uint32_t)(kTC + c * 16 + m)]);
-  }
-  // private exchange: value (k1, c1, m) to (c1 * 16 + k1) * 17 + m; lane mu = c1 * 16 + k1 takes m = 0..15
-  wave_sync();
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) row[(c * 16 + 4 * h + e) * 17 + m] = v[e * 4 + c];
-  wave_sync();
-#pragma unroll
-  for (int q = 0; q < 16; ++q) v[q] = row[l * 17 + q];
-  // 16-point DFTs over m (output c2): index k1 + 16 (c1 + 4 c2) = mu + 64 c2
-  dft16<T>(v);
-}
-
-// The transpose of inner_dft's factorization, stage by stage in reverse order: lane mu =
-// k1 + 16 c1, register c2 hold a[mu + 64 c2] on entry (inner_dft's output layout); lane l,
-// register j hold A[l + 64 j] on exit.  The inverse transform runs this form, so that in
-// floating point it is the transpose of the forward one and the float32 operator stays as
-// symmetric as the exact one (the same DFT, with the rounding of the forward mirrored).
-template <typename T>
-__device__ __forceinline__ void inner_dft_t(cx<T>* v, cx<T>* row, const cx<T>* __restrict__ tab, int l) {
-  l = opaque(l);
-  // 16-point DFTs over c2 (output m), twiddle W_64^(m c1), c1 = mu >> 4
-  dft16<T>(v);
-  const int c1 = l >> 4;
-#pragma unroll
-  for (int q = 1; q < 16; ++q) v[q] = cmul(v[q], tab[(uint32_t)(kTC + c1 * 16 + q)]);
-  // private exchange: value (k1, c1, m) at (c1 * 16 + k1) * 17 + m; lane (m, h) takes k1 = 4h + e, c1 = 0..3
-  wave_sync();
-#pragma unroll
-  for (int q = 0; q < 16; ++q) row[l * 17 + q] = v[q];
-  wave_sync();
-  const int m = l & 15, h = l >> 4;
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) v[e * 4 + c] = row[(c * 16 + 4 * h + e) * 17 + m];
-  // 4-point DFTs over c1 (output lh), twiddle W_1024^(l' k1), l' = m + 16 lh, k1 = 4h + e
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    dft4(v[e * 4], v[e * 4 + 1], v[e * 4 + 2], v[e * 4 + 3]);
-#pragma unroll
-    for (int lh = 0; lh < 4; ++lh)   // (k1 = 0 or l' = 0: the table holds exactly 1)
-      v[e * 4 + lh] = cmul(v[e * 4 + lh], tab[(uint32_t)(kTB + (4 * h + e) * 64 + m + 16 * lh)]);
-  }
-  // private exchange: value (k1, l') at k1 * 64 + l'; lane l takes k1 = 0..15
-  wave_sync();
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int lh = 0; lh < 4; ++lh) row[(4 * h + e) * 64 + m + 16 * lh] = v[e * 4 + lh];
-  wave_sync();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[k] = row[k * 64 + l];
-  // 16-point DFTs over k1 (output j)
-  dft16<T>(v);
-}
-
-
-// The packed window of one (chunk, RHS) job: thread g gets z[g + 1024 n_o] = u[2n] + i u[2n + 1],
-// n_o < NO, u[i] = TOD sample s0 + i inside the chunk's interval, else 0 (s0 = out_start - n_c).
-// Offsets inside the window are 32-bit from its first sample.
-template <typename Tin, int NO>
-__device__ __forceinline__ void wave_load(cx<float>* v, const Tin* __restrict__ yin, const OlsChunk& ch, int rhs,
-                                          int64_t n_t, int n_c, int g) {
-  using T = float;
-  using PU = typename PairU<Tin>::type;
-  constexpr int W = 2048 * NO;   // window samples
-  const Tin* __restrict__ src = yin + (int64_t)rhs * n_t;
-  const int64_t s0 = ch.out_start - n_c;
-  const int64_t lo = ch.iv_lo, hi = ch.iv_hi;
-  if (s0 >= lo && s0 + W <= hi) {   // the whole window inside the interval
-    const PU* __restrict__ b2 = reinterpret_cast<const PU*>(src + s0);
-#pragma unroll
-    for (int no = 0; no < NO; ++no) {
-      const PU x = b2[(uint32_t)(g + 1024 * no)];
-      v[no] = {(T)x.x, (T)x.y};
-    }
-  } else if (s0 >= 0) {   // a window cut by an end of the interval: samples [a, b) of it are data
-    const Tin* __restrict__ base = src + s0;
-    const int a = (int)(lo > s0 ? lo - s0 : 0);
-    const int b = (int)(hi - s0 < W ? hi - s0 : W);
-#pragma unroll
-    for (int no = 0; no < NO; ++no) {
-      const int i = 2 * (g + 1024 * no);
-      const T x = (i >= a && i < b) ? (T)base[(uint32_t)i] : (T)0;
-      const T y = (i + 1 >= a && i + 1 < b) ? (T)base[(uint32_t)(i + 1)] : (T)0;
-      v[no] = {x, y};
-    }
-  } else {   // the window starts before the TOD row (the first interval's first chunk)
-#pragma unroll
-    for (int no = 0; no < NO; ++no) {
-      const int64_t j = s0 + 2 * (int64_t)(g + 1024 * no);
-      const T a = (j >= lo && j < hi) ? (T)src[j] : (T)0;
-      const T b = (j + 1 >= lo && j + 1 < hi) ? (T)src[j + 1] : (T)0;
-      v[no] = {a, b};
-    }
-  }
-}
-
-// Outputs 2n, 2n + 1 of n = g + 1024 n_b (n_b < NO) of one job: the conjugate (re, -im) of
-// v[n_b]; window positions [n_c, n_c + m) are the chunk's outputs, out_start onwards, cut at
-// the interval's end.  Offsets are 32-bit from out_start.
-template <int NO>
-__device__ __forceinline__ void wave_store(const cx<float>* v, float* __restrict__ yout, const OlsChunk& ch,
-                                           int rhs, int64_t n_t, int n_c, int m, int g) {
-  float* __restrict__ base = yout + (int64_t)rhs * n_t + ch.out_start;
-  const int len = (int)(ch.iv_hi - ch.out_start < m ? ch.iv_hi - ch.out_start : m);   // outputs of this chunk
-  if ((n_c & 1) == 0 && len == m) {   // whole pairs, all inside
-    FloatPairU* __restrict__ b2 = reinterpret_cast<FloatPairU*>(base);
-#pragma unroll
-    for (int nb = 0; nb < NO; ++nb) {
-      const int j = 2 * (g + 1024 * nb) - n_c;
-      if (j >= 0 && j < m) b2[(uint32_t)(j >> 1)] = FloatPairU{v[nb].re, -v[nb].im};
-    }
+    for (int i = 0; i < 16; ++i) v[i] = row[rd(i)];
   } else {
+    wave_sync();
 #pragma unroll
-    for (int nb = 0; nb < NO; ++nb) {
-      const int j = 2 * (g + 1024 * nb) - n_c;
-      if (j >= 0 && j < len) base[(uint32_t)j] = v[nb].re;
-      if (j + 1 >= 0 && j + 1 < len) base[(uint32_t)(j + 1)] = -v[nb].im;
-    }
+    for (int i = 0; i < 16; ++i) row[wr(i)] = v[i].re;
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i].re = row[rd(i)];
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) row[wr(i)] = v[i].im;
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i].im = row[rd(i)];
   }
 }
 
-// One conjugate pair of the real-to-complex step with the filter symbol (as k_ols):
-// A = Z_k, B = conj Z_(N-k), E = A + B, O = -i (A - B), Y = (E + W O) F_k,
-// Y' = (E - W O) F_(N-k), s = Y + Y', d = W^-1 (Y - Y'); the new Z_k is conj(s + i d),
-// the new Z_(N-k) is s - i d.  W = W_2N^k, sa = F_k / (4N), sb = F_(N-k) / (4N).
-// (Y and Y' are formed with each symbol value on its own: combining sa +- sb first
-// would round a small F_k, where the 1/f filter suppresses, against a large F_(N-k).)
-__device__ __forceinline__ void wave_pair(cx<float> A, cx<float> Bp, cx<float> W, float sa, float sb,
-                                          cx<float>& zk, cx<float>& znk) {
-  using T = float;
-  const cx<T> B = cconj(Bp);
-  const cx<T> Ev = cadd(A, B);
-  const cx<T> D = csub(A, B);
-  const cx<T> O = {D.im, -D.re};
-  const cx<T> WO = cmul(W, O);
-  const cx<T> Y = cscale(cadd(Ev, WO), sa);
-  const cx<T> Yp = cscale(csub(Ev, WO), sb);
-  const cx<T> sm = cadd(Y, Yp);
-  const cx<T> Wd = cmul(cconj(W), csub(Y, Yp));
-  zk = {sm.re - Wd.im, -(sm.im + Wd.re)};
-  znk = {sm.re + Wd.im, sm.im - Wd.re};
-}
-
-// N^-1 of one job whose window is in v (wave_load); writes the job's valid outputs.
-__device__ __forceinline__ void wave_filter(cx<float>* v, cx<float>* lds, const OlsChunk ch, int rhs,
-                                            float* __restrict__ yout, const float* __restrict__ spec_w,
-                                            const cx<float>* __restrict__ tab, int64_t n_t, int n_c, int m,
-                                            int g_in) {
-  using T = float;
-  constexpr int N = kWN;
-  const int g = g_in, l = g_in & 63;
-  const int w = __builtin_amdgcn_readfirstlane(g_in >> 6);   // wavefront index, uniform
-  cx<T>* row = lds + w * kWRow;
-  // forward, outer stage: 16-point DFTs over n_o (output k_o), twiddle W_N^(g k_o)
-  dft16<T>(v);
-#pragma unroll
-  for (int k = 1; k < 16; ++k) v[k] = cmul(v[k], tab[(uint32_t)(kTA + k * 1024 + g)]);
-  // workgroup exchange: wavefront w takes row k_o = w, lane l the g = l + 64 j
-#pragma unroll
-  for (int k = 0; k < 16; ++k) lds[k * kWRow + g] = v[k];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 16; ++j) v[j] = row[l + 64 * j];
-  // forward, inner stage: lane mu, register c2 hold Z[w + 16 (mu + 64 c2)]
-  inner_dft<T>(v, row, tab, l);
-
-  // pairing with Z_(N-k) and the filter symbol (wave_pair).
-  // Each wavefront forms both members of the pairs whose k_in < 512 (registers 0..7)
-  // and writes the partner's member into the partner's row; it then reads its own
-  // members with k_in >= 512 from its row.
-  wave_sync();
-#pragma unroll
-  for (int c = 0; c < 16; ++c) row[l + 64 * c] = v[c];
-  __syncthreads();
-  const int wp = (16 - w) & 15;                 // partner wavefront
-  cx<T>* prow = lds + wp * kWRow;
-  const float* __restrict__ S = spec_w + (int64_t)ch.filter * (N + 1);
-  const int lp = opaque(l);
-  auto pair = [&](int kin, int kp, cx<T> A, cx<T> Bp, T sb, cx<T>& zk, cx<T>& znk) {
-    wave_pair(A, Bp, tab[(uint32_t)(kT2 + w * 1024 + kin)], S[(uint32_t)(w * 1024 + kin)], sb, zk, znk);
-  };
-  cx<T> other[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    // (four pairs at a time: the scheduler would otherwise hoist every table and
-    // partner load and spill)
-    if (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-    const int kin = lp + 64 * c;
-    const int kp = w == 0 ? ((1024 - kin) & 1023) : 1023 - kin;   // partner's k_in
-    const T sb = (w == 0 && kin == 0) ? S[N] : S[(uint32_t)(wp * 1024 + kp)];   // F_(N-k); k = 0 pairs with F_N
-    pair(kin, kp, v[c], prow[kp], sb, v[c], other[c]);
-  }
-  // k = N/2 (wavefront 0, k_in = 512) is its own partner: lane 0 of wavefront 0
-  cx<T> mid = v[8];
-  if (w == 0 && lp == 0) {
-    cx<T> unused;
-    pair(512, 512, v[8], v[8], S[512], mid, unused);
-  }
-  wave_sync();   // this wavefront's partner-row reads precede its writes there
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const int kin = lp + 64 * c;
-    const int kp = w == 0 ? ((1024 - kin) & 1023) : 1023 - kin;
-    if (!(w == 0 && kin == 0)) prow[kp] = other[c];   // k = 0 is its own partner
-  }
-  if (w == 0 && lp == 0) row[512] = mid;
-  __syncthreads();
-#pragma unroll
-  for (int c = 8; c < 16; ++c) v[c] = row[l + 64 * c];
-
-  // inverse: forward transform of the conjugated spectrum, the transpose of the forward
-  // one: inner stage first (input index k_in = mu + 64 c2, output n_a = l + 64 j), then
-  // twiddle W_N^(n_a k_o) with k_o = w
-  inner_dft_t<T>(v, row, tab, l);
-  const int ld = opaque(l);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    if (c % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    v[c] = cmul(v[c], tab[(uint32_t)(kTA + w * 1024 + ld + 64 * c)]);
-  }
-  wave_sync();
-#pragma unroll
-  for (int c = 0; c < 16; ++c) row[l + 64 * c] = v[c];
-  __syncthreads();
-  // thread g = n_a takes k_o = 0..15; 16-point DFTs over k_o give X[g + 1024 n_b]
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[k] = lds[k * kWRow + g];
-  dft16<T>(v);
-
-  wave_store<16>(v, yout, ch, rhs, n_t, n_c, m, g);
-}
-
-
-// N^-1 of one job of the 32 x 1024 transform whose window is in v[32] (wave_load); writes
-// the job's valid outputs.  Wavefront w holds rows w (va) and w + 16 (vb) between the outer
-// stages; lds has 17 rows (the 17th takes row 0 during the pairing).
-__device__ __forceinline__ void wave_filter32(cx<float>* v, cx<float>* lds, const OlsChunk ch, int rhs,
-                                              float* __restrict__ yout, const float* __restrict__ spec_w,
-                                              const cx<float>* __restrict__ tab, int64_t n_t, int n_c, int m,
-                                              int g_in) {
-  using T = float;
-  constexpr int N = kWN32;
-  constexpr int T2 = wave_t2(15);
-  const int g = g_in, l = g_in & 63;
-  const int w = __builtin_amdgcn_readfirstlane(g_in >> 6);   // wavefront index, uniform
-  cx<T>* row = lds + w * kWRow;
-  // forward, outer stage: 32-point DFTs over n_o (output k_o), twiddle W_N^(g k_o)
-  dft32<T>(v);
-#pragma unroll
-  for (int k = 1; k < 32; ++k) {
-    if (k % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    v[k] = cmul(v[k], tab[(uint32_t)(kTA + k * 1024 + g)]);
-  }
-  // workgroup exchange in two halves: wavefront w takes row k_o = w, then k_o = w + 16
-  cx<T> va[16], vb[16];
-#pragma unroll
-  for (int k = 0; k < 16; ++k) lds[k * kWRow + g] = v[k];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 16; ++j) va[j] = row[l + 64 * j];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) lds[k * kWRow + g] = v[16 + k];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 16; ++j) vb[j] = row[l + 64 * j];
-  // forward, inner stages: lane mu, register c2 hold Z[r + 32 (mu + 64 c2)], r = w, w + 16
-  inner_dft<T>(va, row, tab, l);
-  inner_dft<T>(vb, row, tab, l);
-
-  // pairing with Z_(N-k) and the filter symbol (wave_pair).  The second rows wait in the
-  // LDS rows (wavefront 0 also puts its row 0 in the 17th); wavefront w >= 1 forms every pair
-  // of its row w (k_in) with row 32 - w (k_in' = 1023 - k_in, in wavefront 16 - w's LDS row),
-  // keeps its own members and writes the partner's back; wavefront 0 pairs row 16 (k_in <
-  // 512 with 1023 - k_in) and row 0 (k_in <= 512 with (1024 - k_in) mod 1024) in place.
-  // Every LDS entry of the phase is read and written by one lane only.
-  const float* __restrict__ S = spec_w + (int64_t)ch.filter * (N + 1);
-  cx<T>* row0 = lds + 16 * kWRow;
-  wave_sync();
-#pragma unroll
-  for (int c = 0; c < 16; ++c) row[l + 64 * c] = vb[c];
-  if (w == 0) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) row0[l + 64 * c] = va[c];
-  }
-  __syncthreads();
-  const int lp = opaque(l);
-  if (w != 0) {
-    const int r = w, rp = 32 - w;
-    cx<T>* prow = lds + (16 - w) * kWRow;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      // (four pairs at a time: the scheduler would otherwise hoist every table and
-      // partner load and spill)
-      if (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-      const int kin = lp + 64 * c, kp = 1023 - kin;
-      cx<T> znk;
-      wave_pair(va[c], prow[kp], tab[(uint32_t)(T2 + r * 1024 + kin)], S[(uint32_t)(r * 1024 + kin)],
-                S[(uint32_t)(rp * 1024 + kp)], va[c], znk);
-      prow[kp] = znk;
-    }
+// Workgroup exchange from columns to rows (TO_ROWS; v[c NO + k] of column g = t + NT c ->
+// v[16 i + j] of row w + 16 i at l + 64 j) or back, in RPW halves of 16 rows.  Entered and
+// left with the LDS rows free of readers other than their own wavefront.
+template <typename T, int NO, int RPW, bool TO_ROWS>
+__device__ __forceinline__ void exchange_rows(cx<T>* v, typename Slot<T>::type* lds, int t) {
+  using S = WaveShape<NO, RPW>;
+  if constexpr (S::NW == 1 && NO == 1) {
+    return;   // a wavefront's columns l + 64 c are its row
   } else {
+    constexpr int PARTS = sizeof(T) == 4 ? 1 : 2, H = S::NW;   // H rows in LDS at a time
+    const int l = t & 63, w = t >> 6;
+    cx<T> out[S::E];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {   // row 16 with itself (in this wavefront's LDS row)
-      if (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-      const int kin = lp + 64 * c, kp = 1023 - kin;
-      cx<T> zk, znk;
-      wave_pair(row[kin], row[kp], tab[(uint32_t)(T2 + 16 * 1024 + kin)], S[(uint32_t)(16 * 1024 + kin)],
-                S[(uint32_t)(16 * 1024 + kp)], zk, znk);
-      row[kin] = zk;
-      row[kp] = znk;
-    }
+    for (int i = 0; i < S::RPW; ++i)
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {   // row 0 with itself; k = 0 pairs with F_N
-      if (c % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-      const int kin = lp + 64 * c, kp = (1024 - kin) & 1023;
-      cx<T> zk, znk;
-      wave_pair(row0[kin], row0[kp], tab[(uint32_t)(T2 + kin)], S[(uint32_t)kin],
-                kin == 0 ? S[N] : S[(uint32_t)kp], zk, znk);
-      row0[kin] = zk;
-      if (kin != 0) row0[kp] = znk;
-    }
-    if (lp == 0) {   // k = N/2 (row 0, k_in = 512) is its own partner
-      const cx<T> a = row0[512];
-      cx<T> zk, unused;
-      wave_pair(a, a, tab[(uint32_t)(T2 + 512)], S[512], S[512], zk, unused);
-      row0[512] = zk;
-    }
+      for (int part = 0; part < PARTS; ++part) {
+        auto put = [&](int slot, cx<T> z) {
+          if constexpr (sizeof(T) == 4) lds[slot] = z;
+          else lds[slot] = part ? z.im : z.re;
+        };
+        auto get = [&](int slot, cx<T>& z) {
+          if constexpr (sizeof(T) == 4) {
+            z = lds[slot];
+          } else {
+            const T x = lds[slot];
+            if (part) z.im = x; else z.re = x;
+          }
+        };
+        if (i + part > 0) __syncthreads();   // the previous part's readers are done
+        if constexpr (TO_ROWS) {
+#pragma unroll
+          for (int c = 0; c < S::C; ++c)
+#pragma unroll
+            for (int k = 0; k < H; ++k) put(k * kWRow + t + S::NT * c, v[c * NO + H * i + k]);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) put(w * kWRow + l + 64 * j, v[16 * i + j]);
+        }
+        __syncthreads();
+        if constexpr (TO_ROWS) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) get(w * kWRow + l + 64 * j, out[16 * i + j]);
+        } else {
+#pragma unroll
+          for (int c = 0; c < S::C; ++c)
+#pragma unroll
+            for (int k = 0; k < H; ++k) get(k * kWRow + t + S::NT * c, out[c * NO + H * i + k]);
+        }
+      }
+#pragma unroll
+    for (int e = 0; e < S::E; ++e) v[e] = out[e];
   }
-  __syncthreads();
-  if (w == 0) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) va[c] = row0[l + 64 * c];
-  }
-#pragma unroll
-  for (int c = 0; c < 16; ++c) vb[c] = row[l + 64 * c];
-
-  // inverse: forward transform of the conjugated spectrum, the transpose of the forward
-  // one: inner stages first (input index k_in = mu + 64 c2, output n_a = l + 64 j), twiddle
-  // W_N^(n_a k_o) with k_o = w, w + 16
-  const int ld = opaque(l);
-  inner_dft_t<T>(va, row, tab, l);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    if (c % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    va[c] = cmul(va[c], tab[(uint32_t)(kTA + w * 1024 + ld + 64 * c)]);
-  }
-  inner_dft_t<T>(vb, row, tab, l);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    if (c % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-    vb[c] = cmul(vb[c], tab[(uint32_t)(kTA + (w + 16) * 1024 + ld + 64 * c)]);
-  }
-  // workgroup exchange in two halves: thread g = n_a takes k_o = 0..15, then 16..31
-  wave_sync();
-#pragma unroll
-  for (int c = 0; c < 16; ++c) row[l + 64 * c] = va[c];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[k] = lds[k * kWRow + g];
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < 16; ++c) row[l + 64 * c] = vb[c];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 16; ++k) v[16 + k] = lds[k * kWRow + g];
-  // 32-point DFTs over k_o (the forward's outer factorization transposed) give X[g + 1024 n_b]
-  dft32_t<T>(v);
-  wave_store<32>(v, yout, ch, rhs, n_t, n_c, m, g);
 }
 
-// One workgroup per (chunk, RHS), as k_ols (same XCD-aware order, same outputs).
-template <typename Tin>
-__global__ __launch_bounds__(1024) void k_ols_wave(const Tin* __restrict__ yin, float* __restrict__ yout,
-                                                   const OlsChunk* __restrict__ chunks,
-                                                   const float* __restrict__ spec_w,
-                                                   const cx<float>* __restrict__ tab, int64_t n_t, int n_c, int m,
-                                                   const CgState* __restrict__ st) {
+// Keeps the scheduler from hoisting later table loads over this point, where they would
+// not fit in registers beside the transform and spill
+__device__ __forceinline__ void sched_stop() { __builtin_amdgcn_sched_barrier(0); }
+
+template <int n, typename T>
+__device__ __forceinline__ void load_twiddles(cx<T>* w, const cx<T>* __restrict__ p) {
+#pragma unroll
+  for (int i = 0; i < n; ++i) w[i] = p[i];
+}
+
+// One row: 1024-point forward stage, symbol, 1024-point inverse stage and the twiddle
+// before the inverse's outer stage.  v[j] = column l + 64 j of row k_o on entry and exit.
+// EARLY: table loads go out a stage ahead, behind the exchange before it, and the symbol's
+// before the stage that needs it; else (float64, or two rows in registers, TWO) behind the
+// exchange only.
+template <typename T, int NO, bool EARLY, bool TWO>
+__device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row, const cx<T>* __restrict__ tab,
+                                           const T* __restrict__ sym, int k_o, int l) {
+  using W = WaveTables<NO>;
+  constexpr bool SUM6 = sizeof(T) == 8;
+  const int m = l & 15, hq = l >> 4;
+  const cx<T>* __restrict__ t2 = tab + W::F2 + (uint32_t)((k_o * 16 + 4 * hq) * 2);
+  const cx<T>* __restrict__ t3 = tab + W::F3 + (uint32_t)((k_o * 64 + l) * 4);
+  const T* __restrict__ fs = sym + (uint32_t)(k_o * 1024 + l);
+  cx<T> w2[8], w3[4];
+  T f[16];
+  if (EARLY) load_twiddles<8>(w2, t2);
+  {   // forward: 16 points over j; the row's twiddles are uniform (scalar loads, all of them)
+    const cx<T>* __restrict__ w1 = tab + W::F1 + k_o * 8;
+    dit<T, 4, SUM6>(v, [&](int len, int j) { return w1[len == 2 ? 0 : len / 4 + j]; });
+  }
+  if (TWO) sched_stop();
+  if (!EARLY) load_twiddles<8>(w2, t2);
+  // (k1, l) -> lane (m, hq): k1 = 4 hq + e, h = 0 .. 3
+  exchange_private<T>(v, row, [&](int i) { return i * 64 + l; },
+                      [&](int i) { return (4 * hq + (i >> 2)) * 64 + m + 16 * (i & 3); });
+  if (EARLY) load_twiddles<4>(w3, t3);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) dit<T, 2, SUM6>(v + 4 * e, [&](int len, int) { return w2[2 * e + len / 4]; });   // 4 points over h
+  if (!EARLY) load_twiddles<4>(w3, t3);
+  // (k1, c1, m) -> lane mu = k1 + 16 c1, register m
+  exchange_private<T>(v, row, [&](int i) { return ((i & 3) * 16 + 4 * hq + (i >> 2)) * 17 + m; },
+                      [&](int i) { return l * 17 + i; });
+  if (EARLY) {
+#pragma unroll
+    for (int c = 0; c < 16; ++c) f[c] = fs[64 * c];
+  }
+  dit<T, 4, !EARLY>(v, [&](int len, int j) { return derived(w3, len, j); });   // 16 points over m
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {   // conj(F Z)
+    if (!EARLY) f[c] = fs[64 * c];
+    v[c] = {v[c].re * f[c], -(v[c].im * f[c])};
+  }
+  dft16<T>(v);   // inverse: 16 points over c2
+  load_twiddles<2>(w2, tab + W::I2 + (uint32_t)(m * 2));
+  // (c1, k1, m) -> lane (m, hq): k1 = 4 hq + e, c1 = 0 .. 3
+  exchange_private<T>(v, row, [&](int i) { return l * 17 + i; },
+                      [&](int i) { return ((i & 3) * 16 + 4 * hq + (i >> 2)) * 17 + m; });
+  load_twiddles<4>(w3, tab + W::I3 + (uint32_t)(l * 4));
+#pragma unroll
+  for (int e = 0; e < 4; ++e) dit<T, 2, true>(v + 4 * e, [&](int len, int) { return w2[len / 4]; });   // 4 points over c1
+  // (k1, l) -> lane l, register k1
+  exchange_private<T>(v, row, [&](int i) { return (4 * hq + (i >> 2)) * 64 + m + 16 * (i & 3); },
+                      [&](int i) { return i * 64 + l; });
+  dit<T, 4, true>(v, [&](int len, int j) { return derived(w3, len, j); });   // 16 points over k1
+  const cx<T>* __restrict__ w4 = tab + W::I4 + (uint32_t)(k_o * 1024 + l);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = cmul(v[j], w4[64 * j]);
+}
+
+// One workgroup per (chunk, RHS).  Workgroups are dealt to the 8 XCDs round-robin in linear
+// (x-fastest) order, so XCD x takes workgroups x, x + 8, ...; it gets a contiguous run of
+// (RHS, chunk) pairs instead, so that neighbouring chunks, whose windows overlap by 2 n_c
+// samples, read the shared samples through the same L2.  16 wavefronts per CU (4 per SIMD)
+// whatever NO: LDS holds 16 rows.
+template <typename T, typename Tin, int NO, int RPW>
+__global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, WaveShape<NO, RPW>::NT),
+                          amdgpu_waves_per_eu(4))) void k_ols_wave(
+    const Tin* __restrict__ yin, T* __restrict__ yout, const OlsChunk* __restrict__ chunks,
+    const T* __restrict__ spec, const cx<T>* __restrict__ tab, int64_t n_t, int n_c, int m,
+    const CgState* __restrict__ st) {
+  using S = WaveShape<NO, RPW>;
+  constexpr int N = S::N, NT = S::NT;
+  constexpr int LOGNO = S::LOGNO;
   const int64_t n_wg = (int64_t)gridDim.x * gridDim.y;
   const int64_t wl = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
   const int64_t xq = n_wg >> 3, xr = n_wg & 7, xw = wl & 7;
   const int64_t job = xw * xq + (xw < xr ? xw : xr) + (wl >> 3);
   const int rhs = __builtin_amdgcn_readfirstlane((int)(job / gridDim.x));   // uniform: scalar row offsets
   if (st && !st[rhs].active) return;   // this RHS has stopped iterating
-  __shared__ __align__(16) cx<float> lds[16 * kWRow];
+  __shared__ __align__(16) typename Slot<T>::type lds[S::LDS_SLOTS];
   const OlsChunk ch = chunks[job - (int64_t)rhs * gridDim.x];
-  cx<float> v[16];
-  wave_load<Tin, 16>(v, yin, ch, rhs, n_t, n_c, threadIdx.x);
-  wave_filter(v, lds, ch, rhs, yout, spec_w, tab, n_t, n_c, m, threadIdx.x);
+  const int t = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+
+  // the window: v[c NO + n_o] = x[n] - i x[n + N], n = t + NT c + 1024 n_o, x[i] = TOD sample
+  // s0 + i inside the interval, else 0: window samples [a, b) are data, and a buffer over
+  // them gives the zeros (every constant beside a column's offset is a multiple of 4096
+  // bytes, which the instruction's offset field cannot hold)
+  cx<T> v[S::E];
+  {
+    const int64_t s0 = ch.out_start - n_c;
+    const int64_t lo = ch.iv_lo, hi = ch.iv_hi;
+    const int a = (int)(lo > s0 ? lo - s0 : 0);   // (lo <= out_start: a <= n_c)
+    const int b = (int)(hi - s0 < 2 * N ? hi - s0 : 2 * N);
+    const Rsrc src = buffer_of(yin + (int64_t)rhs * n_t + s0 + a, (b - a) * (int)sizeof(Tin));
+#pragma unroll
+    for (int c = 0; c < S::C; ++c) {
+      const uint32_t off = opaque((uint32_t)(t + NT * c - a) * (uint32_t)sizeof(Tin));
+#pragma unroll
+      for (int n_o = 0; n_o < NO; ++n_o) {
+        Tin x, y;
+        buffer_get(src, off + 1024 * n_o * (uint32_t)sizeof(Tin), x);
+        buffer_get(src, off + (1024 * n_o + N) * (uint32_t)sizeof(Tin), y);
+        v[c * NO + n_o] = {(T)x, -(T)y};
+      }
+    }
+  }
+  // forward, outer stage over n_o
+  if constexpr (NO > 1) {
+#pragma unroll
+    for (int c = 0; c < S::C; ++c) dit_quarter<T, LOGNO>(v + c * NO);
+  }
+  exchange_rows<T, NO, RPW, true>(v, lds, t);
+  // the rows of this wavefront
+#pragma unroll
+  for (int i = 0; i < S::RPW; ++i)
+    filter_row<T, NO, sizeof(T) == 4 && RPW == 1, RPW == 2>(v + 16 * i, lds + w * kWRow, tab, spec + (int64_t)ch.filter * N, w + S::NW * i, t & 63);
+  exchange_rows<T, NO, RPW, false>(v, lds, t);
+  // inverse, outer stage over k_o; the outputs n and n + N of the window, positions
+  // [n_c, n_c + m) of it from out_start on, cut at the interval's end
+  const int len = (int)(ch.iv_hi - ch.out_start < m ? ch.iv_hi - ch.out_start : m);
+  const Rsrc dst = buffer_of(yout + (int64_t)rhs * n_t + ch.out_start, len * (int)sizeof(T));
+#pragma unroll
+  for (int c = 0; c < S::C; ++c) {
+    if constexpr (NO > 1) dif_quarter<T, LOGNO>(v + c * NO);
+    const uint32_t off = opaque((uint32_t)(t + NT * c - n_c) * (uint32_t)sizeof(T));
+#pragma unroll
+    for (int n_b = 0; n_b < NO; ++n_b) {
+      const cx<T> z = v[c * NO + n_b];
+      buffer_put(dst, off + 1024 * n_b * (uint32_t)sizeof(T), z.re);
+      buffer_put(dst, off + (1024 * n_b + N) * (uint32_t)sizeof(T), z.im);
+    }
+  }
 }
 
-// One workgroup per (chunk, RHS) of the 32 x 1024 transform, as k_ols_wave
-template <typename Tin>
-__global__ __launch_bounds__(1024) void k_ols_wave32(const Tin* __restrict__ yin, float* __restrict__ yout,
-                                                     const OlsChunk* __restrict__ chunks,
-                                                     const float* __restrict__ spec_w,
-                                                     const cx<float>* __restrict__ tab, int64_t n_t, int n_c,
-                                                     int m, const CgState* __restrict__ st) {
-  const int64_t n_wg = (int64_t)gridDim.x * gridDim.y;
-  const int64_t wl = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  const int64_t xq = n_wg >> 3, xr = n_wg & 7, xw = wl & 7;
-  const int64_t job = xw * xq + (xw < xr ? xw : xr) + (wl >> 3);
-  const int rhs = __builtin_amdgcn_readfirstlane((int)(job / gridDim.x));   // uniform: scalar row offsets
-  if (st && !st[rhs].active) return;   // this RHS has stopped iterating
-  __shared__ __align__(16) cx<float> lds[17 * kWRow];
-  const OlsChunk ch = chunks[job - (int64_t)rhs * gridDim.x];
-  cx<float> v[32];
-  wave_load<Tin, 32>(v, yin, ch, rhs, n_t, n_c, threadIdx.x);
-  wave_filter32(v, lds, ch, rhs, yout, spec_w, tab, n_t, n_c, m, threadIdx.x);
-}
-
-// Twiddle tables of the 2^LOGN-point transform, float32 from float64 angles
-template <int LOGN>
-__global__ void k_wave_tables(cx<float>* __restrict__ tab) {
-  constexpr int N = 1 << LOGN, NO = N / 1024, T2 = wave_t2(LOGN);
+// Twiddle tables from float64 angles
+template <typename T, int NO>
+__global__ void k_wave_tables(cx<T>* __restrict__ tab) {
+  using W = WaveTables<NO>;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= wave_table_total(LOGN)) return;
-  double num, den;   // angle = -2 pi num / den
-  if (e < kTC) { const int k = e / 64, l = e % 64; num = (double)l * k; den = 1024; }
-  else if (e < kTA) { const int c = (e - kTC) / 16, m = (e - kTC) % 16; num = (double)m * c; den = 64; }
-  else if (e < T2) { const int k = (e - kTA) / 1024, g = (e - kTA) % 1024; num = (double)g * k; den = N; }
-  else { const int r = (e - T2) / 1024, kin = (e - T2) % 1024; num = (double)(r + NO * kin); den = 2.0 * N; }
-  const double frac = num / den;
+  if (e >= W::TOTAL) return;
+  // entry i of a stage with shift num / den, as a fraction of a turn: num / (den 2^(i + 1))
+  auto stage = [](int i, double num, double den) -> double { return num / (den * (double)(2 << i)); };
+  double frac;
+  if (e < W::F2) {
+    const int i = e % 8, len = i == 0 ? 2 : i == 1 ? 4 : i < 4 ? 8 : 16, j = i == 0 ? 0 : i - len / 4;
+    frac = (j * (double)NO + e / 8 + 0.25) / ((double)len * NO);
+  } else if (e < W::F3) {
+    const int i = e - W::F2, k_o = i / 32, k1 = (i / 2) % 16;
+    frac = stage(i % 2, k_o + 0.25 + (double)NO * k1, 16.0 * NO);
+  } else if (e < W::I2) {
+    const int i = e - W::F3, k_o = i / 256, mu = (i / 4) % 64;
+    frac = stage(i % 4, k_o + 0.25 + (double)NO * mu, 64.0 * NO);
+  } else if (e < W::I3) {
+    const int i = e - W::I2;
+    frac = stage(i % 2, i / 2, 16.0);
+  } else if (e < W::I4) {
+    const int i = e - W::I3;
+    frac = stage(i % 4, i / 4, 64.0);
+  } else {
+    const int i = e - W::I4, k_o = i / 1024, g = i % 1024;
+    frac = (double)(g * (4 * k_o + 1)) / (4096.0 * NO);
+  }
   double sn, cs;
-  sincospi(2.0 * (frac - floor(frac)), &sn, &cs);
-  tab[e] = {(float)cs, (float)(-sn)};
+  sincospi(2.0 * frac, &sn, &cs);
+  tab[e] = {(T)cs, (T)(-sn)};
 }
 
-// spec_w[f][r * 1024 + k_in] = spec[f][r + NO k_in], spec_w[f][N] = spec[f][N]
-template <int LOGN>
-__global__ void k_wave_symbols(const float* __restrict__ spec, float* __restrict__ spec_w) {
-  constexpr int N = 1 << LOGN, NO = N / 1024;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e > N) return;
-  const float* __restrict__ src = spec + (int64_t)blockIdx.y * (N + 1);
-  float* __restrict__ dst = spec_w + (int64_t)blockIdx.y * (N + 1);
-  dst[e] = e == N ? src[N] : src[(e >> 10) + NO * (e & 1023)];
+template <typename T, int NO>
+hipError_t tables_launch(void* tab, hipStream_t s) {
+  constexpr int n = WaveTables<NO>::TOTAL;
+  hipLaunchKernelGGL((k_wave_tables<T, NO>), dim3((n + 255) / 256), dim3(256), 0, s, (cx<T>*)tab);
+  return hipGetLastError();
+}
+
+template <typename T, typename Tin, int NO>
+hipError_t wave_launch(const void* y_in, void* y_out, const OlsChunk* chunks, int n_chunks, const void* spec,
+                       const void* tab, int64_t n_t, int n_c, int m, int n_rhs, hipStream_t s, const CgState* st) {
+  constexpr int RPW = NO == 32 ? 2 : 1;   // (16 wavefronts at most)
+  hipLaunchKernelGGL((k_ols_wave<T, Tin, NO, RPW>), dim3((unsigned)n_chunks, (unsigned)n_rhs),
+                     dim3(WaveShape<NO, RPW>::NT), 0, s, (const Tin*)y_in, (T*)y_out, chunks, (const T*)spec, (const cx<T>*)tab, n_t, n_c, m, st);
+  return hipGetLastError();
+}
+
+// NO = 2^(logn - 10) of the lengths that exist: 2^10 .. 2^15 points in float32, .. 2^14 in float64
+template <typename T, typename F>
+auto wave_dispatch(int logn, F&& f) {
+  switch (logn) {
+    case 10: return f(std::integral_constant<int, 1>{});
+    case 11: return f(std::integral_constant<int, 2>{});
+    case 12: return f(std::integral_constant<int, 4>{});
+    case 13: return f(std::integral_constant<int, 8>{});
+    case 14: return f(std::integral_constant<int, 16>{});
+    default:
+      if constexpr (sizeof(T) == 4) return f(std::integral_constant<int, 32>{});
+      else return f(std::integral_constant<int, 16>{});
+  }
 }
 
 }  // namespace
 
-bool ols_wave_exists(int logn, bool fp64) { return (logn == 14 || logn == 15) && !fp64; }
-int ols_wave_table_count(int logn) { return wave_table_total(logn); }
+bool ols_wave_exists(int logn, bool fp64) { return logn >= 10 && logn <= (fp64 ? 14 : 15); }
 
-hipError_t launch_wave_tables(int logn, void* tab, hipStream_t s) {
-  if (!ols_wave_exists(logn, false)) return hipErrorInvalidValue;
-  const int n = wave_table_total(logn);
-  if (logn == 14)
-    hipLaunchKernelGGL(k_wave_tables<14>, dim3((n + 255) / 256), dim3(256), 0, s, (cx<float>*)tab);
-  else
-    hipLaunchKernelGGL(k_wave_tables<15>, dim3((n + 255) / 256), dim3(256), 0, s, (cx<float>*)tab);
-  return hipGetLastError();
+int ols_wave_table_count(int logn) {
+  return wave_dispatch<float>(logn, [](auto no) -> int { return WaveTables<decltype(no)::value>::TOTAL; });
 }
 
-hipError_t launch_wave_symbols(int logn, const void* spec, void* spec_w, int n_filters, hipStream_t s) {
-  if (!ols_wave_exists(logn, false)) return hipErrorInvalidValue;
-  if (n_filters <= 0) return hipSuccess;
-  const dim3 grid(((1 << logn) + 1 + 255) / 256, (unsigned)n_filters);
-  if (logn == 14)
-    hipLaunchKernelGGL(k_wave_symbols<14>, grid, dim3(256), 0, s, (const float*)spec, (float*)spec_w);
-  else
-    hipLaunchKernelGGL(k_wave_symbols<15>, grid, dim3(256), 0, s, (const float*)spec, (float*)spec_w);
-  return hipGetLastError();
+hipError_t launch_wave_tables(int logn, bool fp64, void* tab, hipStream_t s) {
+  if (!ols_wave_exists(logn, fp64)) return hipErrorInvalidValue;
+  if (fp64)
+    return wave_dispatch<double>(logn, [&](auto no) -> hipError_t { return tables_launch<double, decltype(no)::value>(tab, s); });
+  return wave_dispatch<float>(logn, [&](auto no) -> hipError_t { return tables_launch<float, decltype(no)::value>(tab, s); });
 }
 
-hipError_t launch_ols_wave(int logn, bool in_f64, const void* y_in, void* y_out, const OlsChunk* chunks,
-                           int n_chunks, const void* spec_w, const void* tab, int64_t n_t, int n_c, int m,
-                           int n_rhs, hipStream_t s, const CgState* st) {
-  if (!ols_wave_exists(logn, false)) return hipErrorInvalidValue;
+hipError_t launch_ols_wave(int logn, bool fp64, bool in_f64, const void* y_in, void* y_out, const OlsChunk* chunks,
+                           int n_chunks, const void* spec, const void* tab, int64_t n_t, int n_c, int m, int n_rhs,
+                           hipStream_t s, const CgState* st) {
+  if (!ols_wave_exists(logn, fp64)) return hipErrorInvalidValue;
   if (n_chunks == 0 || n_rhs == 0) return hipSuccess;
-  const dim3 grid((unsigned)n_chunks, (unsigned)n_rhs);
-  const float* sw = (const float*)spec_w;
-  const cx<float>* tw = (const cx<float>*)tab;
-  if (logn == 14 && in_f64)
-    hipLaunchKernelGGL(k_ols_wave<double>, grid, dim3(1024), 0, s, (const double*)y_in, (float*)y_out, chunks, sw,
-                       tw, n_t, n_c, m, st);
-  else if (logn == 14)
-    hipLaunchKernelGGL(k_ols_wave<float>, grid, dim3(1024), 0, s, (const float*)y_in, (float*)y_out, chunks, sw,
-                       tw, n_t, n_c, m, st);
-  else if (in_f64)
-    hipLaunchKernelGGL(k_ols_wave32<double>, grid, dim3(1024), 0, s, (const double*)y_in, (float*)y_out, chunks,
-                       sw, tw, n_t, n_c, m, st);
-  else
-    hipLaunchKernelGGL(k_ols_wave32<float>, grid, dim3(1024), 0, s, (const float*)y_in, (float*)y_out, chunks,
-                       sw, tw, n_t, n_c, m, st);
-  return hipGetLastError();
+  auto go = [&](auto tc, auto tin) -> hipError_t {
+    using T = decltype(tc);
+    using Tin = decltype(tin);
+    return wave_dispatch<T>(logn, [&](auto no) -> hipError_t {
+      return wave_launch<T, Tin, decltype(no)::value>(y_in, y_out, chunks, n_chunks, spec, tab, n_t, n_c, m, n_rhs, s,
+                                                      st);
+    });
+  };
+  if (fp64) return in_f64 ? go(double{}, double{}) : go(double{}, float{});
+  return in_f64 ? go(float{}, double{}) : go(float{}, float{});
 }
 
 }  // namespace mm

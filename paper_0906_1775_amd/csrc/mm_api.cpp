@@ -108,12 +108,12 @@ struct FilterSetup {
   int logn = 0;
   int variant = 0;         // workgroup shape of the transform (ols_variant_exists)
   int N = 0, nf = 0, m = 0;
-  void* tw2 = nullptr;     // exp(-2 pi i k / n_f), k < N (real-to-complex packing)
-  void* ptw = nullptr;     // per-pass twiddle tables of the transform (long: of its 2^8-point columns)
+  void* qtw = nullptr;     // workgroup and long transforms: the inverse's last twiddle (launch_quarter_table)
+  void* ptw = nullptr;     // twiddle tables of the transform (long: of its 2^8-point columns)
   void* spec = nullptr;
   bool long_path = false;  // n_f beyond one workgroup: the batched four-step transform (launch_ols_long)
   void* ptw_b = nullptr;   // long: per-pass twiddle tables of its rows
-  void* ltab = nullptr;    // long: W_N and pairing twiddle tables (launch_long_tables)
+  void* ltab = nullptr;    // long: its W_N table (launch_long_tables)
   void* work = nullptr;    // long: intermediates of `batch` jobs
   int64_t batch = 0;
   OlsChunk* chunks = nullptr;
@@ -398,13 +398,12 @@ void wait_ready(mm_plan_s* P, hipStream_t stream) {
 void build_filter_nf(mm_plan_s* P, FilterSetup& fs, bool fp64, int64_t nf, hipStream_t s, int variant, bool tmp);
 void build_symbols(const FilterSetup& fs, const double* lags, int n_filt, int n_c, void* out, char* scr,
                    hipStream_t s);
-size_t symbol_scratch_bytes(int logn, bool fp64, int n_filt, int variant = 0);
 void apply_ols(mm_plan_s* P, const FilterSetup& fs, bool in_f64, const void* y_in, void* y_out, const void* spec,
                int R, hipStream_t s, const CgState* st = nullptr);
 
 void release_filter(mm_plan_s* P, FilterSetup& fs) {
   P->release(fs.chunks);
-  P->release(fs.tw2);
+  P->release(fs.qtw);
   P->release(fs.ptw);
   P->release(fs.spec);
   P->release(fs.ptw_b);
@@ -485,13 +484,11 @@ void autotune_filter(mm_plan_s* P, FilterSetup& fs, bool fp64, hipStream_t s) {
   build_filter_nf(P, fs, fp64, best_nf, s, best_v, false);
 }
 
-// transform shape used when the descriptor leaves it open: the fastest measured
-// for each length (2^14 and 2^15 points in float32: the four-step transforms with
-// wavefront-private inner stages; 2^14 in float64: 512 threads x 32 points, radix-16
-// passes, pairs in registers)
+// transform shape used when the descriptor leaves it open: the fastest measured for each
+// length, which from 2^10 points on is the one with wavefront-private inner stages
+// (variant 9 for 2^14 and 2^15 points in float32, else variant 0)
 int default_ols_variant(int logn, bool fp64) {
-  if (!fp64 && ols_wave_exists(logn, fp64)) return 9;
-  return logn == 14 && fp64 ? 2 : 0;
+  return ols_variant_exists(logn, fp64, 9) ? 9 : 0;
 }
 
 int64_t count_chunks(const std::vector<int64_t>& iv_start, int64_t m);
@@ -511,8 +508,8 @@ int compute_units() {
 }
 
 // Workgroup time of one 2^15-point wavefront-private transform over one 2^14-point one
-// (the float32 filter pass of 2^30 samples x 8 RHS at n_c = 8192: 32.6 ms for 179,088
-// jobs at n_f = 2^16 against 42.7 ms for 529,632 at 2^15)
+// (2^28 float32 samples at n_c = 8192: 834 us for 5,632 jobs at n_f = 2^16 against 1,064 us
+// for 16,384 at 2^15)
 constexpr double kWave15Cost = 2.25;
 
 // n_f of a filter set-up that is not autotuned (secondary: the float64 filter of a
@@ -573,6 +570,13 @@ void check_transform_length(int64_t nf, bool fp64) {
   if (logn < kMinLogN) fail(MM_EUNSUPPORTED, "FFT length below 128");
 }
 
+// Entries of the inverse's last twiddle table: the long transform's columns, or the
+// points of a workgroup transform (the wavefront-private ones have it in their own tables)
+int quarter_count(int logn, bool fp64, int variant) {
+  if (transform_long(logn, fp64)) return 1 << kLongRowLog;
+  return ols_variant_wave(logn, fp64, variant) ? 0 : 1 << logn;
+}
+
 void build_filter_nf(mm_plan_s* P, FilterSetup& fs, bool fp64, int64_t nf, hipStream_t s, int variant, bool tmp) {
   check_transform_length(nf, fp64);
   const int logn = ilog2(nf) - 1;
@@ -599,9 +603,11 @@ void build_filter_nf(mm_plan_s* P, FilterSetup& fs, bool fp64, int64_t nf, hipSt
     hipchk(hipMemcpyAsync(fs.chunks, ch.data(), ch.size() * sizeof(OlsChunk), hipMemcpyHostToDevice, s),
            "chunk table upload");
   const int esz = fp64 ? 8 : 4;
-  fs.tw2 = get((int64_t)fs.N * 2 * esz);
-  hipchk(launch_tw2_table(fs.tw2, logn, fp64, s), "twiddle table");
   fs.long_path = transform_long(logn, fp64);
+  if (const int nq = quarter_count(logn, fp64, variant)) {
+    fs.qtw = get((int64_t)nq * 2 * esz);
+    hipchk(launch_quarter_table(fs.qtw, nq, fp64, s), "twiddle table");
+  }
   if (fs.long_path) {   // four-step: twiddles of its 2^8-point columns and 2^(logn - 8)-point rows
     fs.ptw = get((int64_t)std::max(pass_twiddle_count(8, fp64, 0), 1) * 2 * esz);
     hipchk(launch_pass_twiddles(fs.ptw, 8, fp64, s, 0), "pass twiddle tables");
@@ -617,30 +623,19 @@ void build_filter_nf(mm_plan_s* P, FilterSetup& fs, bool fp64, int64_t nf, hipSt
     fs.ptw = get((int64_t)std::max(ntw, 1) * 2 * esz);
     hipchk(launch_pass_twiddles(fs.ptw, logn, fp64, s, variant), "pass twiddle tables");
   }
-  fs.spec = get((int64_t)P->n_filt * (fs.N + 1) * esz);
-  char* sscr = P->temp<char>((int64_t)symbol_scratch_bytes(logn, fp64, P->n_filt, fs.variant));
+  fs.spec = get((int64_t)P->n_filt * fs.N * esz);
+  char* sscr = P->temp<char>((int64_t)spectra_scratch_bytes(logn));
   build_symbols(fs, P->lags, P->n_filt, P->n_c, fs.spec, sscr, s);
   P->release(sscr);   // later work on this stream may reuse it
   fs.ready = true;
 }
 
-// Symbol tables F_b / (4N) of n_filt filters from their lags (launch_spectra), in the
-// order the transform of fs reads them: natural, or row order for the batched four-step
-// transform (launch_long_symbol_rows) and for the wavefront-private one (variant 9,
-// launch_wave_symbols); scr: symbol_scratch_bytes
+// Symbol tables F_b / N of n_filt filters from their lags (launch_spectra), in the order
+// the transform of fs reads them; scr: spectra_scratch_bytes
 void build_symbols(const FilterSetup& fs, const double* lags, int n_filt, int n_c, void* out, char* scr,
                    hipStream_t s) {
-  const bool wave = !fs.long_path && fs.variant == 9;
-  if (!fs.long_path && !wave) {
-    hipchk(launch_spectra(lags, n_filt, n_c, fs.logn, fs.fp64, out, scr, s), "filter spectra");
-    return;
-  }
-  char* nat = scr + block_bytes((int64_t)spectra_scratch_bytes(fs.logn), 1);
-  hipchk(launch_spectra(lags, n_filt, n_c, fs.logn, fs.fp64, nat, scr, s), "filter spectra");
-  if (wave)
-    hipchk(launch_wave_symbols(fs.logn, nat, out, n_filt, s), "filter spectra in row order");
-  else
-    hipchk(launch_long_symbol_rows(fs.logn, fs.fp64, nat, out, n_filt, s), "filter spectra in row order");
+  const int rowlog = fs.long_path ? kLongRowLog : ols_variant_wave(fs.logn, fs.fp64, fs.variant) ? fs.logn - 10 : 0;
+  hipchk(launch_spectra(lags, n_filt, n_c, fs.logn, rowlog, fs.fp64, out, scr, s), "filter spectra");
 }
 
 // y_out = N^-1 y_in by the overlap-save transforms of fs with the symbol table spec
@@ -650,10 +645,10 @@ void apply_ols(mm_plan_s* P, const FilterSetup& fs, bool in_f64, const void* y_i
                int R, hipStream_t s, const CgState* st) {
   if (fs.long_path)
     hipchk(launch_ols_long(fs.fp64, in_f64, fs.logn, y_in, y_out, fs.chunks, fs.n_chunks, spec, fs.ptw, fs.ptw_b,
-                           fs.tw2, fs.ltab, fs.work, fs.batch, P->n_t, P->n_c, fs.m, R, s, st),
+                           fs.qtw, fs.ltab, fs.work, fs.batch, P->n_t, P->n_c, fs.m, R, s, st),
            "overlap-save filter (four-step)");
   else
-    hipchk(launch_ols(fs.fp64, in_f64, fs.logn, y_in, y_out, fs.chunks, fs.n_chunks, spec, fs.ptw, fs.tw2, P->n_t,
+    hipchk(launch_ols(fs.fp64, in_f64, fs.logn, y_in, y_out, fs.chunks, fs.n_chunks, spec, fs.ptw, fs.qtw, P->n_t,
                       P->n_c, fs.m, R, s, fs.variant, st),
            "overlap-save filter");
 }
@@ -1124,14 +1119,6 @@ void validate_desc(const mm_desc_t* d) {
 
 int64_t y_bytes(bool fp64, int R, int64_t n) { return fp64 ? (int64_t)R * n * 8 : std::max<int64_t>((int64_t)R * 4, 8) * n; }
 
-// Scratch of build_symbols: the spectra's own, then (four-step transform) the tables in
-// natural order before they are put in row order
-size_t symbol_scratch_bytes(int logn, bool fp64, int n_filt, int variant) {
-  const size_t b = spectra_scratch_bytes(logn);
-  if (!transform_long(logn, fp64) && !(variant == 9 && ols_wave_exists(logn, fp64))) return b;
-  return block_bytes((int64_t)b, 1) + (size_t)n_filt * ((size_t(1) << logn) + 1) * (fp64 ? 8 : 4);
-}
-
 // Device bytes of a filter set-up (chunk table, twiddles, spectra) and of the
 // spectra build's scratch
 size_t filter_bytes(const std::vector<int64_t>& iv_start, int n_filt, int n_c, int64_t nf, int variant, bool fp64,
@@ -1149,8 +1136,9 @@ size_t filter_bytes(const std::vector<int64_t>& iv_start, int n_filt, int n_c, i
   } else {
     tw = block_bytes((int64_t)std::max(pass_twiddle_count(logn, fp64, variant), 1) * 2 * esz, 1);
   }
-  return block_bytes(n_chunks * (int64_t)sizeof(OlsChunk), 1) + block_bytes(N * 2 * esz, 1) + tw +
-         block_bytes((int64_t)n_filt * (N + 1) * esz, 1);
+  const int nq = quarter_count(logn, fp64, variant);
+  return block_bytes(n_chunks * (int64_t)sizeof(OlsChunk), 1) + (nq ? block_bytes((int64_t)nq * 2 * esz, 1) : 0) + tw +
+         block_bytes((int64_t)n_filt * N * esz, 1);
 }
 
 // Upper bounds of a plan's device memory from its descriptor alone: persistent data,
@@ -1235,7 +1223,7 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
         const size_t fb = filter_bytes(iv, nf_filt, n_c, nf, v, fp64, R);
         most = std::max(most, fb);
         most_tmp =
-            std::max(most_tmp, fb + block_bytes((int64_t)symbol_scratch_bytes(ilog2(nf) - 1, fp64, nf_filt, v), 1));
+            std::max(most_tmp, fb + block_bytes((int64_t)spectra_scratch_bytes(ilog2(nf) - 1), 1));
         if (fp64) logn64 = std::max(logn64, ilog2(nf) - 1);
       }
     B.pers += most;
@@ -1246,7 +1234,7 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
     check_transform_length(nf, fp64);
     const int v = choose_variant(d->fft_shape, nf, fp64);
     B.pers += filter_bytes(iv, nf_filt, n_c, nf, v, fp64, R);
-    B.temps += block_bytes((int64_t)symbol_scratch_bytes(logn, fp64, nf_filt, v), 1);
+    B.temps += block_bytes((int64_t)spectra_scratch_bytes(logn), 1);
     if (fp64) logn64 = logn;
   }
   if (!fp64) {
@@ -1254,7 +1242,7 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
     logn64 = ilog2(nf) - 1;
     check_transform_length(nf, true);
     B.pers += filter_bytes(iv, nf_filt, n_c, nf, choose_variant(d->fft_shape, nf, true), true, R);
-    B.temps += block_bytes((int64_t)symbol_scratch_bytes(logn64, true, nf_filt), 1);
+    B.temps += block_bytes((int64_t)spectra_scratch_bytes(logn64), 1);
   }
   // interval tables and their coarse index
   const int sh = interval_hint_shift(iv, n);
@@ -1280,9 +1268,9 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
   if (d->filter_params) {
     const int64_t N64 = int64_t(1) << logn64;
     B.call_temps = block_bytes(std::max<int64_t>(n, 1), 8) + block_bytes((int64_t)nf_filt * n_c, 8) +
-                   block_bytes(3 * (int64_t)nf_filt * (N64 + 1), 8) + block_bytes(3 * (int64_t)std::max(d->n_intervals, 1), 8) +
+                   block_bytes(3 * (int64_t)nf_filt * N64, 8) + block_bytes(3 * (int64_t)std::max(d->n_intervals, 1), 8) +
                    block_bytes((int64_t)std::max(lags_scratch_bytes(n_c, lag_len, batch),
-                                                 symbol_scratch_bytes(logn64, true, nf_filt)), 1);
+                                                 spectra_scratch_bytes(logn64)), 1);
   }
   return B;
 }
@@ -2317,7 +2305,7 @@ mm_status_t mm_noise_gradient(mm_plan_t P, const void* d_tod, int32_t tod_dtype,
     const bool in64 = tod_dtype == MM_F64;
     const int esz = in64 ? 8 : 4;
     const int nfl = P->n_filt, n_iv = std::max(P->n_iv, 1);
-    const int64_t spec_n = (int64_t)nfl * (f64.N + 1);
+    const int64_t spec_n = (int64_t)nfl * f64.N;
     const int batch = std::max(1, std::min(nfl, 16));
     const size_t lsb = lags_scratch_bytes(P->n_c, P->lag_len, batch);
     // temporaries above the work vectors, released in reverse order on every exit
@@ -2325,7 +2313,7 @@ mm_status_t mm_noise_gradient(mm_plan_t P, const void* d_tod, int32_t tod_dtype,
     double* dlags = P->temp<double>((int64_t)nfl * P->n_c);
     double* dspec = P->temp<double>(3 * spec_n);                                   // one symbol per theta
     double* ivd = P->temp<double>(3 * (int64_t)n_iv);
-    char* lscr = P->temp<char>((int64_t)std::max(lsb, symbol_scratch_bytes(f64.logn, true, nfl)));
+    char* lscr = P->temp<char>((int64_t)std::max(lsb, spectra_scratch_bytes(f64.logn)));
     auto release_all = [&]() {
       P->release(lscr);
       P->release(ivd);

@@ -63,59 +63,58 @@ __device__ __forceinline__ double group_sum(double v) {
 
 // ---------------------------------------------------------------- filter (k_filter.hip)
 int ols_max_logn(bool fp64);
-hipError_t launch_tw2_table(void* tw2, int logn, bool fp64, hipStream_t s);
-// per-pass twiddle tables of the workgroup transform of 2^logn points
-// (variant: workgroup shape of the overlap-save transform; 0 for every other use)
+// tab[n] = exp(-2 pi i n / (4N)), n < N (workgroup and long transforms)
+hipError_t launch_quarter_table(void* tab, int N, bool fp64, hipStream_t s);
+// twiddle tables of the overlap-save transform of 2^logn points in workgroup shape `variant`
+// (complex entries; the shifted forward transform's and the plain inverse's)
 int pass_twiddle_count(int logn, bool fp64, int variant = 0);
 hipError_t launch_pass_twiddles(void* tab, int logn, bool fp64, hipStream_t s, int variant = 0);
 // whether the overlap-save transform of 2^logn points has workgroup shape `variant`
 constexpr int kOlsVariants = 10;
 bool ols_variant_exists(int logn, bool fp64, int variant);
+// whether that shape is the transform with wavefront-private inner stages (k_ols_wave.hip)
+bool ols_variant_wave(int logn, bool fp64, int variant);
 // lags (mode 0) or their derivative with respect to sigma (1), f_knee (2), alpha (3)
 hipError_t launch_lags(const double* params /*dev [nf][3]*/, int n_filters, double f_samp, int n_c,
                        int64_t lag_len, double* lags /*dev [nf][n_c]*/, void* scratch,
                        size_t scratch_bytes, hipStream_t s, int mode = 0);
 size_t lags_scratch_bytes(int n_c, int64_t lag_len, int filters_per_batch);
-// spec[f][k] = F_k / (4N), k = 0..N, the symbol of filter f's circulant of n_f = 2N points
+// the symbol of filter f at the shifted frequencies k + 1/4 of N = 2^logn points, times 1/N:
+// F_k at spec[f][(k mod 2^rowlog) 2^(logn - rowlog) + (k >> rowlog)]
 size_t spectra_scratch_bytes(int logn);
-hipError_t launch_spectra(const double* lags, int n_filters, int n_c, int logn, bool fp64,
-                          void* spec /*[nf][N+1]*/, void* scratch, hipStream_t s);
+hipError_t launch_spectra(const double* lags, int n_filters, int n_c, int logn, int rowlog, bool fp64,
+                          void* spec /*[nf][N]*/, void* scratch, hipStream_t s);
 // y_out[r][t] = (N^-1 y_in)[r][t]; compute type T (fp64 flag); input type in_f64; output type T
 // st (optional): per-RHS CG states; rows of RHS no longer active are skipped
 hipError_t launch_ols(bool fp64, bool in_f64, int logn, const void* y_in, void* y_out,
                       const OlsChunk* chunks, int n_chunks, const void* spec, const void* ptw,
-                      const void* tw2, int64_t n_t, int n_c, int m, int n_rhs, hipStream_t s,
+                      const void* qtw, int64_t n_t, int n_c, int m, int n_rhs, hipStream_t s,
                       int variant = 0, const CgState* st = nullptr);
 
 // ---------------------------------------------------------------- long filter (k_ols_long.hip)
 // The overlap-save N^-1 with transforms of 2^logn complex points beyond one workgroup
 // (logn 16 and 17, n_f = 2^17 and 2^18), as a batched four-step transform: ptw1 / ptw2 =
-// launch_pass_twiddles tables of lengths 2^8 and 2^(logn - 8), tw2 as for launch_ols,
-// work = device buffer of batch jobs x 2^logn complex points of the compute type.
-// spec_rows: the symbol table in row order (launch_long_tables), ltab: its twiddle tables
-// four-step transforms of 2^14 and 2^15 points (NO x 1024, NO = 16, 32) with wavefront-private
-// inner stages (variant 9, float32): tab = its twiddle tables (ols_wave_table_count complex
-// entries, launch_wave_tables); spec_w[f] = launch_spectra's table in row order (entry
-// r * 1024 + k_in holds k = r + NO k_in, entry N holds k = N)
-bool ols_wave_exists(int logn, bool fp64);
-int ols_wave_table_count(int logn);
-hipError_t launch_wave_tables(int logn, void* tab, hipStream_t s);
-hipError_t launch_wave_symbols(int logn, const void* spec, void* spec_w, int n_filters, hipStream_t s);
-hipError_t launch_ols_wave(int logn, bool in_f64, const void* y_in, void* y_out, const OlsChunk* chunks,
-                           int n_chunks, const void* spec_w, const void* tab, int64_t n_t, int n_c, int m,
-                           int n_rhs, hipStream_t s, const CgState* st);
+// launch_pass_twiddles tables of lengths 2^8 and 2^(logn - 8), qtw = launch_quarter_table of
+// 2^8, work = device buffer of batch jobs x 2^logn complex points of the compute type.
+// spec_rows: the symbol in row order (rowlog = kLongRowLog), ltab: its twiddle table
+constexpr int kLongRowLog = 8;
 bool ols_long_exists(int logn);
 int64_t ols_long_batch(int logn, bool fp64);   // jobs per batch (intermediates of ~64 MiB)
 int ols_long_table_count(int logn);            // complex entries of ltab
 hipError_t launch_long_tables(int logn, bool fp64, void* ltab, hipStream_t s);
-// spec_rows[f] = spec[f] (launch_spectra's tables) in row order: entry k1 N2 + k2 holds
-// k = k1 + N1 k2 (N1 = 2^8, N2 = 2^(logn - 8)), entry N holds k = N; n_filters tables
-hipError_t launch_long_symbol_rows(int logn, bool fp64, const void* spec, void* spec_rows, int n_filters,
-                                   hipStream_t s);
 hipError_t launch_ols_long(bool fp64, bool in_f64, int logn, const void* y_in, void* y_out, const OlsChunk* chunks,
-                           int n_chunks, const void* spec_rows, const void* ptw1, const void* ptw2, const void* tw2,
+                           int n_chunks, const void* spec_rows, const void* ptw1, const void* ptw2, const void* qtw,
                            const void* ltab, void* work, int64_t batch, int64_t n_t, int n_c, int m, int n_rhs,
                            hipStream_t s, const CgState* st = nullptr);
+// transforms of 2^10 .. 2^15 points (NO x 1024; float64 up to 2^14) with wavefront-private
+// inner stages: tab = its twiddle tables (ols_wave_table_count complex entries), spec in row
+// order (rowlog = logn - 10)
+bool ols_wave_exists(int logn, bool fp64);
+int ols_wave_table_count(int logn);
+hipError_t launch_wave_tables(int logn, bool fp64, void* tab, hipStream_t s);
+hipError_t launch_ols_wave(int logn, bool fp64, bool in_f64, const void* y_in, void* y_out, const OlsChunk* chunks,
+                           int n_chunks, const void* spec, const void* tab, int64_t n_t, int n_c, int m, int n_rhs,
+                           hipStream_t s, const CgState* st);
 
 // ---------------------------------------------------------------- pointing (k_pointing.hip)
 // y[r][t] = (P p_r)_t; p rows of stride vs (map values first, observed layout)
