@@ -12,9 +12,10 @@
 // inverse DFT over L_K frequencies nu_j = j f_samp / L_K of 1/p(nu_j),
 // p = sigma^2 (1 + (f_knee/nu)^alpha) (Algorithm section), 1/p(0) taken as its
 // limit, times the Bartlett taper (1 - tau/n_c).  Only tau < n_c is needed, so
-// the L_K-point inverse DFT is split as j = r + R q (R = L_K / n_c'):
-//   G_r(tau) = sum_q s_{r + R q} e^{+2 pi i q tau / n_c'}   (R transforms of n_c' points)
-//   f~(tau)  = (1/L_K) Re sum_r e^{+2 pi i r tau / L_K} G_r(tau).
+// the L_K-point inverse DFT is split as j = r + R q (R = L_K / M):
+//   F_r(tau) = sum_q s_{r + R q} e^{-2 pi i q tau / M}   (R transforms of M points, period M in tau)
+//   f~(tau)  = (1/L_K) sum_r Re [ e^{-2 pi i r tau / L_K} F_r(tau) ],
+// and since s_j = s_{L_K - j} the terms of r and R - r are equal: r = 0 .. R/2 suffice.
 #include <type_traits>
 
 #include "fft.hpp"
@@ -225,79 +226,135 @@ static hipError_t launch_plain_twiddles(void* tab, int logn, hipStream_t s) {
   return with_plain(logn, [&](auto L) -> hipError_t { return pass_tw_launch<double, decltype(L)::value>(tab, 0.0, s); });
 }
 
+// log2 of the fraction of j: tab[j] = log2(j / 2^e), 2^e <= j < 2^(e + 1), j = 1 .. n - 1
+__device__ __forceinline__ double log2_fraction(uint32_t j, int e) {
+  return log2((double)j * __builtin_bit_cast(double, (uint64_t)(1023 - e) << 52));
+}
+__global__ void k_log2_table(double* __restrict__ tab, int64_t n) {
+  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j == 0 || j >= n) return;
+  tab[j] = log2_fraction((uint32_t)j, 31 - __clz((uint32_t)j));
+}
+
+// Noise parameters of one filter, with q = f_knee L / f_samp split as 2^e2 times a fraction
+struct PsdParams {
+  double sigma, fknee, alpha, frac2;
+  int e2;
+};
+__device__ __forceinline__ PsdParams psd_params(const double* __restrict__ p, double f_samp, int64_t L) {
+  PsdParams P{p[0], p[1], p[2], 0.0, 0};
+  if (P.fknee != 0.0) P.frac2 = log2(frexp(P.fknee * ((double)L / f_samp), &P.e2));
+  return P;
+}
+
 // 1/p(nu_j) on the L-point grid, Hermitian-extended: s_j = s_{L-j}; mode 1-3
 // give its derivative with respect to sigma, f_knee, alpha.  With
 // x = (f_knee/nu)^alpha:  ds/dsigma = -2 s/sigma,  ds/df_knee = -s^2 sigma^2 alpha x/f_knee,
 // ds/dalpha = -s^2 sigma^2 x ln(f_knee/nu); the nu = 0 value (0 or 1/sigma^2)
 // does not depend on f_knee or alpha.
-__device__ __forceinline__ double inv_psd(int64_t j, int64_t L, double f_samp, double sigma,
-                                          double fknee, double alpha, int mode) {
+// x = 2^(alpha log2(f_knee / nu_j)) with log2(f_knee L / f_samp) - log2(j) held as an integer
+// and a fraction, and the product's rounding carried to first order, so that x is as
+// accurate as pow(f_knee / nu, alpha) (whose argument is rounded, an error times alpha) at
+// a fifth of its operations.
+__device__ __forceinline__ double inv_psd(uint32_t j, uint32_t L, const PsdParams& P, const double* __restrict__ tab,
+                                          int mode) {
+  const double sigma = P.sigma, fknee = P.fknee, alpha = P.alpha;
   if (j > L / 2) j = L - j;
   if (j == 0) {
     const double s0 = fknee > 0.0 ? 0.0 : 1.0 / (sigma * sigma);
     return mode == 0 ? s0 : (mode == 1 ? -2.0 * s0 / sigma : 0.0);
   }
-  const double nu = (double)j * (f_samp / (double)L);
-  const double x = pow(fknee / nu, alpha);
+  double x = 0.0, ln = 0.0;
+  if (fknee != 0.0) {
+    const int e = 31 - __clz(j);
+    const double di = (double)(P.e2 - e), df = P.frac2 - (tab ? tab[j] : log2_fraction(j, e));
+    const double hi = alpha * di, v = fma(alpha, df, fma(alpha, di, -hi));
+    const double w = hi + v, rest = v - (w - hi);
+    x = exp2(w);
+    if (isfinite(x)) x = fma(x * 0.69314718055994530942, rest, x);
+    ln = (di + df) * 0.69314718055994530942;
+  }
   const double s = 1.0 / (sigma * sigma * (1.0 + x));
   switch (mode) {
     case 0: return s;
     case 1: return -2.0 * s / sigma;
     case 2: return fknee > 0.0 ? -s * s * sigma * sigma * alpha * x / fknee : 0.0;
-    default: return fknee > 0.0 ? -s * s * sigma * sigma * x * log(fknee / nu) : 0.0;
+    default: return fknee > 0.0 ? -s * s * sigma * sigma * x * ln : 0.0;
   }
 }
 
-// step 1: grid (R, filters in batch); one n_c'-point transform per (r, filter)
-template <int LOGN>
-__global__ __launch_bounds__(Shape<LOGN>::NT) void k_lag_step1(
-    const double* __restrict__ params, int f0, double f_samp, int64_t L, int n_c,
-    const cx<double>* __restrict__ ptw, cx<double>* __restrict__ G, int mode) {
-  using F = ShapeFFT<double, LOGN>;
+// Partial sums over r of the lags: grid (G groups, filters in batch); group g takes
+// r = g, g + G, .. <= R/2, keeps its sums over tau < NB M in registers and writes them to
+// part[filter][g][tau].  Every F_r stays on chip (written out and read back they were 16 bytes
+// per frequency and filter, and the sum over r ran serially in n_c threads).
+template <int LOGM, int NB>
+__global__ __launch_bounds__(Shape<LOGM>::NT) void k_lag_sums(const double* __restrict__ params, int f0, double f_samp,
+                                                              int64_t L, int n_c, const cx<double>* __restrict__ ptw,
+                                                              const double* __restrict__ tab,
+                                                              double* __restrict__ part, int mode) {
+  using F = ShapeFFT<double, LOGM>;
   __shared__ __align__(16) char lds[F::LDS_BYTES];
-  constexpr int N = F::N, E = F::E;
+  constexpr int M = F::N, E = F::E;
   const int t = threadIdx.x;
-  const int64_t R = L >> LOGN;
-  const int64_t r = blockIdx.x;
-  const int fl = f0 + blockIdx.y;
-  const double sg = params[3 * fl], fk = params[3 * fl + 1], al = params[3 * fl + 2];
-  cx<double> v[E];
+  const uint32_t R = (uint32_t)(L >> LOGM), mask = (uint32_t)L - 1;   // (L <= 2^30)
+  const double unit = 2.0 / (double)L;   // exact: L is a power of two
+  const PsdParams P = psd_params(params + 3 * (int64_t)(f0 + blockIdx.y), f_samp, L);
   constexpr int L0 = F::first_log_fwd(), R0 = 1 << L0;
-#pragma unroll
-  for (int i = 0; i < E / R0; ++i)
-#pragma unroll
-    for (int rr = 0; rr < R0; ++rr) {
-      const int q = F::template in_index<L0>(t, i, rr);
-      v[i * R0 + rr] = {inv_psd(r + R * (int64_t)q, L, f_samp, sg, fk, al, mode), 0.0};
-    }
-  F::forward(v, lds, ptw, t);
   constexpr int LL = F::last_log_fwd(), RL = 1 << LL;
-  cx<double>* out = G + ((int64_t)blockIdx.y * R + r) * n_c;
+  double acc[NB][E];
 #pragma unroll
-  for (int i = 0; i < E / RL; ++i)
+  for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int rr = 0; rr < RL; ++rr) {
-      const int tau = t + i * F::NT + rr * (N >> LL);
-      if (tau < n_c) out[tau] = cconj(v[i * RL + rr]);
-    }
+    for (int i = 0; i < E; ++i) acc[b][i] = 0.0;
+  for (uint32_t r = blockIdx.x; r <= R / 2; r += gridDim.x) {
+    cx<double> v[E];
+#pragma unroll
+    for (int i = 0; i < E / R0; ++i)
+#pragma unroll
+      for (int rr = 0; rr < R0; ++rr)
+        v[i * R0 + rr] = {inv_psd(r + R * (uint32_t)F::template in_index<L0>(t, i, rr), (uint32_t)L, P, tab, mode), 0.0};
+    F::forward(v, lds, ptw, t);
+    const double twice = r == 0 || 2 * r == R ? 1.0 : 2.0;
+    // e^{-2 pi i r tau / L} F_r(tau): exact at tau < M, then by e^{-2 pi i r / R} per block of M
+    cx<double> wr = {1.0, 0.0};
+    if (NB > 1) sincospi(unit * (double)(r << LOGM), &wr.im, &wr.re), wr.im = -wr.im;
+#pragma unroll
+    for (int i = 0; i < E / RL; ++i)
+#pragma unroll
+      for (int rr = 0; rr < RL; ++rr) {
+        const int e = i * RL + rr, tau = t + i * F::NT + rr * (M >> LL);
+        double sn, cs;
+        sincospi(unit * (double)((r * (uint32_t)tau) & mask), &sn, &cs);
+        cx<double> z = cmul(v[e], cx<double>{twice * cs, -twice * sn});
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          acc[b][e] += z.re;
+          if (b + 1 < NB) z = cmul(z, wr);
+        }
+      }
+  }
+  double* __restrict__ out = part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * n_c;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < E / RL; ++i)
+#pragma unroll
+      for (int rr = 0; rr < RL; ++rr) {
+        const int tau = b * M + t + i * F::NT + rr * (M >> LL);
+        if (tau < n_c) out[tau] = acc[b][i * RL + rr];
+      }
 }
 
-// step 2: lags[f][tau] = taper * (1/L) Re sum_r e^{2 pi i r tau / L} G_r(tau)
-__global__ void k_lag_step2(const cx<double>* __restrict__ G, int f0, int64_t L, int64_t R,
-                            int n_c, double* __restrict__ lags) {
+// lags[f][tau] = taper * (1/L) sum_g part[f][g][tau]
+__global__ void k_lag_reduce(const double* __restrict__ part, int f0, int64_t L, int groups, int n_c,
+                             double* __restrict__ lags) {
   const int tau = blockIdx.x * blockDim.x + threadIdx.x;
   if (tau >= n_c) return;
-  const cx<double>* g = G + (int64_t)blockIdx.y * R * n_c + tau;
+  const double* __restrict__ p = part + (int64_t)blockIdx.y * groups * n_c + tau;
   double acc = 0.0;
-  for (int64_t r = 0; r < R; ++r) {
-    const int64_t k = (r * (int64_t)tau) & (L - 1);
-    double sn, cs;
-    sincospi(2.0 * (double)k / (double)L, &sn, &cs);
-    const cx<double> z = g[r * n_c];
-    acc += cs * z.re - sn * z.im;
-  }
-  lags[(int64_t)(f0 + blockIdx.y) * n_c + tau] =
-      acc / (double)L * (1.0 - (double)tau / (double)n_c);
+#pragma unroll 8
+  for (int g = 0; g < groups; ++g) acc += p[(int64_t)g * n_c];
+  lags[(int64_t)(f0 + blockIdx.y) * n_c + tau] = acc / (double)L * (1.0 - (double)tau / (double)n_c);
 }
 
 static int ceil_log2(int64_t x) {
@@ -309,58 +366,84 @@ static int ceil_log2(int64_t x) {
 static size_t lag_tw_bytes(int logn) {
   return ((size_t)plain_twiddle_count(logn) * sizeof(cx<double>) + 255) & ~(size_t)255;
 }
+static int lag_min_logm(int n_c) { return ceil_log2(n_c) < kMinLogN ? kMinLogN : ceil_log2(n_c); }
 
 size_t lags_scratch_bytes(int n_c, int64_t lag_len, int filters_per_batch) {
-  const int logn = ceil_log2(n_c) < kMinLogN ? kMinLogN : ceil_log2(n_c);
+  const int logn = lag_min_logm(n_c);
   const int64_t R = lag_len >> logn;
   return lag_tw_bytes(logn) + (size_t)filters_per_batch * R * n_c * sizeof(cx<double>);
 }
 
-template <int LOGN>
-static hipError_t lag_step1(dim3 g, hipStream_t s, const double* params, int f0, double fs,
-                            int64_t L, int n_c, const cx<double>* ptw, cx<double>* G, int mode) {
-  hipLaunchKernelGGL(k_lag_step1<LOGN>, g, dim3(Shape<LOGN>::NT), 0, s, params, f0, fs, L, n_c,
-                     ptw, G, mode);
-  return hipGetLastError();
+// Split of the lag construction, a function of n_c and L alone (the lags then do not depend on
+// the scratch a caller gives): M = 2^11 points (four 37 KB workgroups per CU, and at most
+// eight blocks of M lags) where L allows, and up to kLagGroups groups of r, so that one
+// filter already occupies many CUs, within the scratch of one filter.  L = 2^20, one filter:
+// 74 -> 49 us at n_c = 8192, 3,910 -> 46 us at 64 (M was the power of two above n_c, the sum
+// over r a serial loop); 64 filters at 8192: 4,690 -> 670 us.  M = 2^13 at n_c = 8192 (one
+// workgroup per CU): 126 and 1,139 us.
+constexpr int kLagLogM = 11, kLagGroups = 65;
+struct LagSplit {
+  int logm, groups;
+};
+static LagSplit lag_split(int n_c, int64_t lag_len) {
+  const size_t have = lags_scratch_bytes(n_c, lag_len, 1);
+  for (int logm = kLagLogM; logm >= kMinLogN; --logm) {
+    const int64_t R = lag_len >> logm;
+    if (R < 2 || lag_tw_bytes(logm) >= have) continue;
+    const int64_t fit = (int64_t)((have - lag_tw_bytes(logm)) / ((size_t)n_c * sizeof(double)));
+    const int64_t want = R / 2 + 1 < kLagGroups ? R / 2 + 1 : kLagGroups;
+    // (shorter transforms only where the longer one's tables crowd out its groups)
+    if (fit >= want || (fit >= 1 && logm <= lag_min_logm(n_c))) return {logm, (int)(fit < want ? fit : want)};
+  }
+  return {0, 0};
 }
 
 hipError_t launch_lags(const double* params, int n_filters, double f_samp, int n_c,
                        int64_t lag_len, double* lags, void* scratch, size_t scratch_bytes,
                        hipStream_t s, int mode) {
-  int logn = ceil_log2(n_c);
-  if (logn < kMinLogN) logn = kMinLogN;
-  if (logn > kMaxLogNF64) return hipErrorInvalidValue;
-  const int64_t R = lag_len >> logn;
-  if (R < 2 || (R << logn) != lag_len) return hipErrorInvalidValue;
-  cx<double>* ptw = (cx<double>*)scratch;   // per-pass twiddle tables of the transform
-  cx<double>* G = (cx<double>*)((char*)scratch + lag_tw_bytes(logn));
-  const size_t per_filter = (size_t)R * n_c * sizeof(cx<double>);
-  if (scratch_bytes < lag_tw_bytes(logn) + per_filter) return hipErrorInvalidValue;
-  const size_t avail = scratch_bytes - lag_tw_bytes(logn);
-  const size_t fit = avail / per_filter;
-  const int batch = (int)(fit < 65535 ? fit : 65535);   // filters per launch (grid y)
-  hipError_t e = launch_plain_twiddles(ptw, logn, s);
+  if (lag_min_logm(n_c) > kMaxLogNF64) return hipErrorInvalidValue;
+  const int64_t R0 = lag_len >> lag_min_logm(n_c);
+  if (R0 < 2 || (R0 << lag_min_logm(n_c)) != lag_len) return hipErrorInvalidValue;
+  if (scratch_bytes < lags_scratch_bytes(n_c, lag_len, 1)) return hipErrorInvalidValue;
+  const LagSplit sp = lag_split(n_c, lag_len);
+  if (sp.groups < 1 || n_c > (8 << sp.logm)) return hipErrorInvalidValue;
+  // scratch: twiddles, the log2 table (where it leaves room for the partial sums of eight
+  // filters, or of all; else the kernel evaluates the same logarithms), partial sums
+  cx<double>* ptw = (cx<double>*)scratch;
+  size_t off = lag_tw_bytes(sp.logm);
+  const size_t per_filter = (size_t)sp.groups * n_c * sizeof(double);
+  const size_t tab_bytes = ((size_t)(lag_len / 2 + 1) * sizeof(double) + 255) & ~(size_t)255;
+  double* tab = nullptr;
+  hipError_t e = launch_plain_twiddles(ptw, sp.logm, s);
   if (e != hipSuccess) return e;
+  if (off + tab_bytes + (size_t)(n_filters < 8 ? n_filters : 8) * per_filter <= scratch_bytes) {
+    tab = (double*)((char*)scratch + off);
+    off += tab_bytes;
+    const int64_t n = lag_len / 2 + 1;
+    hipLaunchKernelGGL(k_log2_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tab, n);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  double* part = (double*)((char*)scratch + off);
+  const size_t fit = (scratch_bytes - off) / per_filter;
+  const int batch = (int)(fit < 65535 ? fit : 65535);   // filters per launch (grid y)
   for (int f0 = 0; f0 < n_filters; f0 += batch) {
     const int nb = (n_filters - f0) < batch ? (n_filters - f0) : batch;
-    const dim3 g1((unsigned)R, (unsigned)nb);
-    switch (logn) {
-      case 6: e = lag_step1<6>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 7: e = lag_step1<7>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 8: e = lag_step1<8>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 9: e = lag_step1<9>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 10: e = lag_step1<10>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 11: e = lag_step1<11>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 12: e = lag_step1<12>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 13: e = lag_step1<13>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      case 14: e = lag_step1<14>(g1, s, params, f0, f_samp, lag_len, n_c, ptw, G, mode); break;
-      default: return hipErrorInvalidValue;
-    }
+    e = with_plain(sp.logm, [&](auto LC) -> hipError_t {
+      constexpr int LOGM = decltype(LC)::value < kLagLogM ? decltype(LC)::value : kLagLogM;
+      const dim3 g((unsigned)sp.groups, (unsigned)nb), b(Shape<LOGM>::NT);
+#define MM_LAGS(NB) \
+  hipLaunchKernelGGL((k_lag_sums<LOGM, NB>), g, b, 0, s, params, f0, f_samp, lag_len, n_c, ptw, tab, part, mode)
+      if (n_c <= (1 << LOGM)) MM_LAGS(1);
+      else if (n_c <= (2 << LOGM)) MM_LAGS(2);
+      else if (n_c <= (4 << LOGM)) MM_LAGS(4);
+      else MM_LAGS(8);
+#undef MM_LAGS
+      return hipGetLastError();
+    });
     if (e != hipSuccess) return e;
-    const dim3 g2((unsigned)((n_c + 255) / 256), (unsigned)nb);
-    hipLaunchKernelGGL(k_lag_step2, g2, dim3(256), 0, s, G, f0, lag_len, R, n_c, lags);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lag_reduce, dim3((unsigned)((n_c + 255) / 256), (unsigned)nb), dim3(256), 0, s, part, f0,
+                       lag_len, sp.groups, n_c, lags);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -386,7 +469,8 @@ __global__ __launch_bounds__(Shape<LOGM>::NT) void k_symbol(
   constexpr int M = F::N, E = F::E;
   const int t = threadIdx.x;
   const int b = blockIdx.x, B = gridDim.x;
-  const int64_t N = int64_t(1) << logn, mask = 4 * N - 1;
+  const uint32_t N = 1u << logn, mask = 4 * N - 1;
+  const double unit = 0.5 / (double)N;   // exact: N is a power of two
   const double* __restrict__ f = lags + (int64_t)blockIdx.y * n_c;
   cx<double> v[E];
   constexpr int L0 = F::first_log_fwd(), R0 = 1 << L0;
@@ -400,7 +484,7 @@ __global__ __launch_bounds__(Shape<LOGM>::NT) void k_symbol(
       for (int q = n < n_c ? -((n_c - 1 - n) / M) : (n - n_c) / M + 1; n - M * q > -n_c; ++q) {
         const int tau = n - M * q;
         double sn, cs;
-        sincospi((double)(((int64_t)tau * (4 * b + 1)) & mask) / (double)(2 * N), &sn, &cs);
+        sincospi(unit * (double)(((uint32_t)tau * (uint32_t)(4 * b + 1)) & mask), &sn, &cs);
         const double x = f[tau < 0 ? -tau : tau];
         u.re += x * cs;
         u.im -= x * sn;
@@ -409,13 +493,13 @@ __global__ __launch_bounds__(Shape<LOGM>::NT) void k_symbol(
     }
   F::forward(v, lds, ptw, t);
   const double scale = 1.0 / (double)N;
-  T* __restrict__ out = spec + (int64_t)blockIdx.y * N;
+  T* __restrict__ out = spec + ((int64_t)blockIdx.y << logn);
   constexpr int LL = F::last_log_fwd(), RL = 1 << LL;
 #pragma unroll
   for (int i = 0; i < E / RL; ++i)
 #pragma unroll
     for (int r = 0; r < RL; ++r) {
-      const int64_t k = b + (int64_t)B * (t + i * F::NT + r * (M >> LL));
+      const uint32_t k = (uint32_t)(b + B * (t + i * F::NT + r * (M >> LL)));
       out[((k & ((1 << rowlog) - 1)) << (logn - rowlog)) + (k >> rowlog)] = (T)(v[i * RL + r].re * scale);
     }
 }

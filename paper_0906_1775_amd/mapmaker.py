@@ -53,7 +53,8 @@ def noise_lags(params: torch.Tensor, f_samp: float, n_c: int, lag_dft_len: int =
         raise ValueError("params must be a contiguous float64 CUDA tensor [n_filters, 3]")
     n = ctypes.c_size_t(0)
     L.check(lib.mm_noise_lags_workspace_size(int(n_c), int(lag_dft_len), ctypes.byref(n)), lib)
-    ws = torch.empty(int(n.value), dtype=torch.uint8, device=params.device)
+    # room for a few filters: the library then takes more of them per launch
+    ws = torch.empty(int(n.value) * max(1, min(4, int(params.shape[0]))), dtype=torch.uint8, device=params.device)
     out = torch.empty((params.shape[0], int(n_c)), dtype=torch.float64, device=params.device)
     L.check(lib.mm_noise_lags(_ptr(params), int(params.shape[0]), float(f_samp), int(n_c), int(lag_dft_len),
                               int(deriv), _ptr(out), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()), lib)
