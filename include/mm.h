@@ -131,12 +131,12 @@ typedef struct {
   const double* filter_lags;    /* host [n_filters][n_c] explicit f(tau), or NULL */
   double f_samp;                /* sampling frequency in Hz (used with filter_params) */
   int32_t n_c;                  /* correlation length: f(tau) = 0 for tau >= n_c; >= 1 */
-  int32_t n_f;                  /* overlap-save FFT length: 0 = library default (the
-                                   paper's rule capped at 2^14, or the smallest power of
-                                   two above 2 n_c when that is longer; in float32 with the
-                                   default shape, twice that, 2^16, where the chunks of the
-                                   2^15-point transform take fewer full rounds of one
-                                   workgroup per compute unit at 2.25 times the work each),
+  int32_t n_f;                  /* overlap-save FFT length: 0 = library default (the on-chip
+                                   power of two above 2 n_c with the least predicted time for
+                                   the intervals and n_rhs; where that power is 2^15 or more,
+                                   the smallest one, or in float32 with the default shape 2^16
+                                   instead of 2^15 where its windows take fewer full rounds of
+                                   one workgroup per compute unit at 2.25 times the work each),
                                    -1 = autotune
                                    (time every length with a transform on the plan's
                                    intervals and keep the fastest), > 0 = forced power of

@@ -80,8 +80,6 @@ int ilog2(int64_t x) {
   return l;
 }
 
-// transform length the plan prefers when the descriptor leaves n_f open
-constexpr int kPreferredMaxLogN = 13;   // n_f = 2^14
 constexpr int kMinLogN = 6;
 
 int32_t fft_length_rule(int32_t n_c, int64_t longest) {
@@ -512,31 +510,56 @@ int compute_units() {
 // for 16,384 at 2^15)
 constexpr double kWave15Cost = 2.25;
 
+// Filter pass over c chunks with transforms of 2^logn points, in us: about
+// kOlsLatency + c * kOlsChunkNs / 1000, the time of one chunk alone and its share of a full
+// chip (measured per length: one-interval TODs of 65,536 samples, and 2^24 to 2^26 samples
+// at n_c = 64 and 8192; 2^6 .. 2^9 points are the workgroup transforms).  A TOD of a few
+// windows is done in one latency of the shortest ones, a long one at the rate that its halo
+// 2 n_c leaves.
+struct OlsCost {
+  double latency_us, chunk_ns;
+};
+constexpr OlsCost kOlsCost[2][10] = {
+    // float32: 2^6 .. 2^15 points
+    {{5.0, 0.5}, {5.0, 0.7}, {5.0, 0.95}, {5.0, 2.1}, {4.5, 3.3}, {4.5, 7.5}, {5.0, 15.6}, {5.5, 31.0}, {9.0, 65.0}, {20.0, 140.0}},
+    // float64: 2^6 .. 2^14 points
+    {{5.5, 0.8}, {5.5, 1.2}, {6.0, 1.9}, {6.5, 4.7}, {5.0, 6.0}, {6.0, 13.7}, {8.0, 30.0}, {12.5, 59.0}, {21.0, 130.0}, {0.0, 0.0}}};
+
 // n_f of a filter set-up that is not autotuned (secondary: the float64 filter of a
-// mixed plan, which takes a forced n_f only when it has a float64 transform).  The
-// length rule, capped at 2^14; where that leaves no valid outputs, the smallest power
-// of two above 2 n_c, or in float32 with the wavefront-private transforms twice that when
-// its chunks (one workgroup each, one workgroup per CU) take less time in full rounds
-// over the chip: fewer chunks, no more than 2.25 times the work each.
+// mixed plan, which takes a forced n_f only when it has a float64 transform): the on-chip
+// length above 2 n_c of the least predicted time, of those a forced shape has.  Where 2^15 is the smallest one (the
+// workloads' n_c = 8192) and the wavefront-private shapes may be taken, the choice between
+// 2^15 and 2^16 goes by full rounds over the chip, one workgroup per CU in both: fewer
+// chunks, no more than 2.25 times the work each.
 int64_t choose_nf(int nf_req, int n_c, const std::vector<int64_t>& iv_start, int R, int shape_req, bool fp64,
                   bool secondary) {
   const int maxlog = ols_max_logn(fp64);
   if (nf_req > 0 && !(secondary && ilog2(nf_req) - 1 > maxlog)) return nf_req;
-  int64_t nf = fft_length_rule(n_c, longest_interval(iv_start));
-  nf = std::min<int64_t>(nf, int64_t(1) << (kPreferredMaxLogN + 1));
-  if (nf <= 2 * (int64_t)n_c) {
-    nf = 1;
-    while (nf <= 2 * (int64_t)n_c) nf <<= 1;
-    const bool wave_shape = shape_req == 0 || shape_req == 10;
-    if (!fp64 && wave_shape && ilog2(nf) - 1 == 14 && ols_wave_exists(15, false)) {
+  int64_t lo = int64_t(1) << (kMinLogN + 1);
+  while (lo <= 2 * (int64_t)n_c) lo <<= 1;
+  if (ilog2(lo) - 1 >= 14) {
+    if (!fp64 && (shape_req == 0 || shape_req == 10) && ilog2(lo) - 1 == 14 && ols_wave_exists(15, false)) {
       const double cu = compute_units();
       auto rounds = [&](int64_t f) {
         return std::ceil((double)count_chunks(iv_start, f - 2 * (int64_t)n_c) * std::max(R, 1) / cu);
       };
-      if (kWave15Cost * rounds(2 * nf) < rounds(nf)) nf *= 2;
+      if (kWave15Cost * rounds(2 * lo) < rounds(lo)) lo *= 2;
+    }
+    return lo;
+  }
+  int64_t best = 0;
+  double best_us = 0.0;
+  for (int64_t nf = lo; ilog2(nf) - 1 <= maxlog; nf <<= 1) {
+    if (shape_req > 0 && !transform_exists(ilog2(nf) - 1, fp64, shape_req - 1)) continue;
+    const OlsCost& c = kOlsCost[fp64 ? 1 : 0][ilog2(nf) - 1 - kMinLogN];
+    const double us = c.latency_us + 1e-3 * c.chunk_ns * std::max(R, 1) *
+                                         (double)count_chunks(iv_start, nf - 2 * (int64_t)n_c);
+    if (best == 0 || us < best_us) {
+      best = nf;
+      best_us = us;
     }
   }
-  return std::max<int64_t>(nf, int64_t(1) << (kMinLogN + 1));
+  return best ? best : lo;
 }
 
 int choose_variant(int shape_req, int64_t nf, bool fp64) {
