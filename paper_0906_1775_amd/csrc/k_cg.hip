@@ -12,6 +12,8 @@
 //   q = H p;  alpha = rho / (p.q);  x += alpha p;  r -= alpha q;
 //   rel = ||r|| / ||b||;  keep x if rel is the lowest so far;  stop if rel <= tol;
 //   z = M r;  rho' = r.z;  beta = rho'/rho;  p = z + beta p.
+#include <algorithm>
+
 #include "mm_internal.h"
 
 namespace mm {
@@ -280,8 +282,14 @@ __device__ __forceinline__ bool cg_scalar_step(CgState& s, double rz, double rr)
 // buffer, else in place, so the best iterate is kept without a copy.  Tx = float: x
 // holds the float32 increment of the iterate since its last float64 fold (reliable
 // updates), and no best iterate is kept.
+//
+// Bound by memory (20 to 40 bytes an element).  A block folds 4 KiB of partial sums before it
+// starts, so the grid stops at kStepBlocks over all right-hand sides, enough to fill the chip,
+// and walks the rest (a block per 256 elements: 295,000 folds for 8 rows of 9.4 M elements).
+constexpr int kStepAhead = 4;
+constexpr int kStepBlocks = 2048;
 template <typename Tx, typename Tp, typename Tz>
-__global__ void k_cg_step_next(Tx* __restrict__ x, double* __restrict__ xbest, Tp* __restrict__ p,
+__global__ __launch_bounds__(kDotThreads) void k_cg_step_next(Tx* __restrict__ x, double* __restrict__ xbest, Tp* __restrict__ p,
                                const Tz* __restrict__ z, CgState* __restrict__ st,
                                const CgState* __restrict__ st_prev,
                                const double* __restrict__ prz, const double* __restrict__ prr,
@@ -312,14 +320,29 @@ __global__ void k_cg_step_next(Tx* __restrict__ x, double* __restrict__ xbest, T
   // source and destination rows of the iterate (the same buffer, or x and xbest)
   const Tx* xs = src ? reinterpret_cast<const Tx*>(xbest) : x;
   Tx* xd = dst ? reinterpret_cast<Tx*>(xbest) : x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nu; i += stride) {
-    const int64_t j = (int64_t)r * nu + i;
-    const double pj = (double)p[j];
-    xd[j] = (Tx)((double)xs[j] + alpha * pj);
-    const double pn = (double)z[j] + beta * pj;
-    p[j] = (Tp)pn;
-    if (p32 && i < n32) p32[(int64_t)r * vs32 + i] = (float)pn;
+  // the loads of kStepAhead elements are issued before the first is used
+  const int64_t row = (int64_t)r * nu, span = (int64_t)kStepAhead * kDotThreads;
+  for (int64_t i0 = (int64_t)blockIdx.x * span + threadIdx.x; i0 < nu; i0 += (int64_t)gridDim.x * span) {
+    Tp pv[kStepAhead];
+    Tx xv[kStepAhead];
+    Tz zv[kStepAhead];
+#pragma unroll
+    for (int k = 0; k < kStepAhead; ++k) {
+      const int64_t i = i0 + k * kDotThreads, j = row + (i < nu ? i : i0);
+      pv[k] = p[j];
+      xv[k] = xs[j];
+      zv[k] = z[j];
+    }
+#pragma unroll
+    for (int k = 0; k < kStepAhead; ++k) {
+      const int64_t i = i0 + k * kDotThreads, j = row + i;
+      if (i >= nu) break;
+      const double pj = (double)pv[k];
+      xd[j] = (Tx)((double)xv[k] + alpha * pj);
+      const double pn = (double)zv[k] + beta * pj;
+      p[j] = (Tp)pn;
+      if (p32 && i < n32) p32[(int64_t)r * vs32 + i] = (float)pn;
+    }
   }
 }
 
@@ -327,8 +350,9 @@ hipError_t launch_cg_step_next(void* x, bool x_f32, double* xbest, void* p, bool
                                CgState* st, const CgState* st_prev, const double* partial_rz,
                                const double* partial_rr, double* history, int hist_stride, int64_t nu, int n_rhs,
                                hipStream_t s, float* p32, int64_t n32, int64_t vs32) {
-  dim3 g = grid_for(nu);
-  g.y = n_rhs;
+  const int64_t per = (int64_t)kStepAhead * kDotThreads;
+  const int64_t most = std::max(1, kStepBlocks / std::max(1, n_rhs));
+  const dim3 g((unsigned)std::max<int64_t>(1, std::min<int64_t>((nu + per - 1) / per, most)), n_rhs);
   if (x_f32 && p_f32 && z_f32)
     hipLaunchKernelGGL((k_cg_step_next<float, float, float>), g, dim3(256), 0, s, (float*)x, xbest, (float*)p,
                        (const float*)z, st, st_prev, partial_rz, partial_rr, history, hist_stride, nu, p32, n32,
