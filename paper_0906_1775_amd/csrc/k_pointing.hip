@@ -329,8 +329,8 @@ constexpr int kBatch = 4;
 // RG right-hand sides share one pass over the sliced pointing: the entries are
 // loaded once per group and each RHS keeps its own accumulators, so the
 // pointing is streamed ceil(R / RG) times instead of R times.  WPS wavefronts
-// split a slice's entries (the plan picks 8 for pixels with hundreds of hits, 1
-// for a few tens, where the cross-wave combine would dominate); a block of 8
+// split a slice's entries (the plan picks 8 where the slices alone leave the chip idle,
+// 1 for many short ones, where the cross-wave combine would dominate); a block of 8
 // wavefronts works on 8 / WPS slices at a time.  Every (pixel, RHS) sum has a
 // fixed order for a given WPS.  Tq: the element type q is stored in (the float64 sum is
 // rounded to it); p (element type Tp, rows of stride ps) times the stored q gives the p.q
@@ -455,29 +455,30 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter(
   }
 }
 
-// q = P^T y over the plain pixel-major layout: a wavefront takes 64 / kSegLanes
-// neighbouring pixels at a time, kSegLanes lanes per pixel reading consecutive
+// q = P^T y over the plain pixel-major layout: G lanes share a pixel, 16 or 64 of
+// a wavefront or the whole block of 512 (seg_lanes() chooses), and read consecutive
 // hits.  Those come from a few sweeps, which also hit the neighbours, so a TOD
 // load touches fewer cache lines than the sliced layout's j-th hits of 64
 // pixels (22.5 against 34.7 on a 2^24-sample raster).  For pixels with
-// hundreds of hits, where the lanes stay busy, and a TOD the last-level cache
-// mostly holds (neighbouring pixels' hits share TOD lines that this layout
-// reads from different wavefronts).  Each lane sums its hits in order, then the
-// lanes of a pixel are combined by a fixed butterfly in float64, so every
-// (pixel, RHS) sum has a fixed order.
-constexpr int kSegLanes = 16;
-constexpr int kSegBatch = 4;   // loads in flight per lane
-template <typename Ty, typename Tq, typename Tp, int NS, int RG>
+// hundreds of hits, where the lanes stay busy, and a TOD the last-level cache mostly holds (neighbouring
+// pixels' hits share TOD lines that this layout reads from different wavefronts).
+// Each lane sums its hits in order, then the lanes of a pixel are combined in a
+// fixed order in float64, so every (pixel, RHS) sum has a fixed order.
+// Bound by the latency of the entry and then the TOD load, hence 4 (8) in flight.
+template <typename Ty, typename Tq, typename Tp, int NS, int RG, int G>
 __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
     const int64_t* __restrict__ pix_ptr, const int32_t* __restrict__ perm, const float2* __restrict__ w_pm,
     const Ty* __restrict__ y, Tq* __restrict__ q, int64_t vs, int64_t n_obs, int64_t n_t, int n_rhs,
     const Tp* __restrict__ p, int64_t ps, double* __restrict__ pq_part, int pq_stride, int pq_slot,
     const CgState* __restrict__ st) {
-  constexpr int NW = kBlockWaves, G = kSegLanes, PPW = 64 / G;
+  constexpr int NW = kBlockWaves, NT = 64 * NW, PPB = NT / G;   // PPB pixels per block
+  constexpr bool kWide = G > 64;
+  constexpr int kSegBatch = kWide && NS * RG == 1 ? 8 : 4;      // loads in flight per lane
   __shared__ double sh[NW][RG];
+  __shared__ double part[kWide ? NW : 1][RG * NS];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
-  const int gl = lane % G;   // lane within its pixel's group
+  const int gl = tid % G;    // lane within its pixel's group
   for (int r0 = 0; r0 < n_rhs; r0 += RG) {
     bool act[RG];
     bool any = false;
@@ -490,13 +491,13 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
     double pq[RG];
 #pragma unroll
     for (int g = 0; g < RG; ++g) pq[g] = 0.0;
-    for (int64_t o0 = ((int64_t)blockIdx.x * NW + wv) * PPW; o0 < n_obs; o0 += (int64_t)gridDim.x * NW * PPW) {
-      const int64_t o = o0 + lane / G;
+    for (int64_t b0 = (int64_t)blockIdx.x * PPB; b0 < n_obs; b0 += (int64_t)gridDim.x * PPB) {   // uniform over the block
+      const int64_t o = b0 + tid / G;
       const bool ov = o < n_obs;
       const int64_t k0 = ov ? pix_ptr[o] : 0, k1 = ov ? pix_ptr[o + 1] : 0;   // k1 > k0 for an observed pixel
       int span = (int)(k1 - k0);            // the wavefront walks its longest pixel
 #pragma unroll
-      for (int off = G; off < 64; off <<= 1) span = max(span, __shfl_xor(span, off, 64));
+      for (int off = G; off < 64; off <<= 1) span = max(span, __shfl_xor(span, off, 64));   // none for G >= 64
       Acc<Ty> a[RG][NS];
       for (int64_t j0 = 0; j0 < span; j0 += G * kSegBatch) {
         // loads issued unconditionally (a slot past the pixel's hits re-reads its
@@ -536,19 +537,50 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
           }
         }
       }
+      if constexpr (kWide) {   // wavefront sums, then one thread per value adds them in wavefront order
 #pragma unroll
-      for (int g = 0; g < RG; ++g) {
-        if (!act[g]) continue;
-        const int64_t i = (int64_t)(r0 + g) * vs + o * NS;
-        const int64_t ip = (int64_t)(r0 + g) * ps + o * NS;
+        for (int g = 0; g < RG; ++g)
 #pragma unroll
-        for (int c = 0; c < NS; ++c) {
-          double v = a[g][c].value();
+          for (int c = 0; c < NS; ++c) {
+            double v = a[g][c].value();
 #pragma unroll
-          for (int off = 1; off < G; off <<= 1) v += __shfl_xor(v, off, 64);   // same sum on the group's lanes
-          const Tq vq = (Tq)v;
-          if (ov && gl == c) q[i + c] = vq;
-          if (p && ov && gl == 0) pq[g] += (double)p[ip + c] * (double)vq;
+            for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+            if (lane == 0) part[wv][g * NS + c] = v;
+          }
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+          for (int g = 0; g < RG; ++g) {
+            if (!act[g]) continue;
+            const int64_t i = (int64_t)(r0 + g) * vs + o * NS;
+            const int64_t ip = (int64_t)(r0 + g) * ps + o * NS;
+#pragma unroll
+            for (int c = 0; c < NS; ++c) {
+              double v = part[0][g * NS + c];
+#pragma unroll
+              for (int w = 1; w < NW; ++w) v += part[w][g * NS + c];
+              const Tq vq = (Tq)v;
+              q[i + c] = vq;
+              if (p) pq[g] += (double)p[ip + c] * (double)vq;
+            }
+          }
+        }
+        __syncthreads();
+      } else {
+#pragma unroll
+        for (int g = 0; g < RG; ++g) {
+          if (!act[g]) continue;
+          const int64_t i = (int64_t)(r0 + g) * vs + o * NS;
+          const int64_t ip = (int64_t)(r0 + g) * ps + o * NS;
+#pragma unroll
+          for (int c = 0; c < NS; ++c) {
+            double v = a[g][c].value();
+#pragma unroll
+            for (int off = 1; off < G; off <<= 1) v += __shfl_xor(v, off, 64);   // same sum on the group's lanes
+            const Tq vq = (Tq)v;
+            if (ov && gl == c) q[i + c] = vq;
+            if (p && ov && gl == 0) pq[g] += (double)p[ip + c] * (double)vq;
+          }
         }
       }
     }
@@ -571,32 +603,42 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
   }
 }
 
-int scatter_blocks(int64_t n_obs, int wps) {
-  if (wps == 0) {
-    const int64_t ppb = (int64_t)kBlockWaves * (64 / kSegLanes);   // pixels per block and step
-    return (int)std::max<int64_t>(1, std::min<int64_t>((n_obs + ppb - 1) / ppb, kScatterBlocks));
-  }
-  const int64_t n_sl = (n_obs + 63) / 64;
-  const int64_t spb = kBlockWaves / std::max(1, wps);
-  return (int)std::max<int64_t>(1, std::min<int64_t>((n_sl + spb - 1) / spb, kScatterBlocks));
+int scatter_blocks(int64_t n_obs, const SellLayout& L) {
+  const int64_t n_u = L.wps == 0 ? n_obs : (n_obs + 63) / 64;                                // pixels or slices
+  const int64_t per = L.wps == 0 ? 64 * kBlockWaves / L.lanes : kBlockWaves / L.wps;   // of a block and step
+  return (int)std::max<int64_t>(1, std::min<int64_t>((n_u + per - 1) / per, kScatterBlocks));
 }
 
-// wavefronts per slice for a layout whose pixels have `avg` entries on average
-// (the plan may still choose 8 wavefronts per slice over 0 for a large TOD)
-int scatter_waves_per_slice(double avg) { return avg >= 128 ? 0 : avg >= 64 ? 4 : avg >= 32 ? 2 : 1; }
+// Lanes per pixel of the pixel-major scatter (128 hits and more on average, or a sliced copy that
+// would not fit).  16 fill the chip from 2^15 pixels on; fewer pixels with more hits need more
+// lanes each (us, float32, one RHS, with 16, 64 and 512 lanes: 144 pixels of 1500 hits 45, 15,
+// 11; 1024 of 4096 neighbouring hits 68, 27, 11; 1024 of 400 17, 11, 11.5; 25,600 of 200 41, 30,
+// -; 16,384 of 160 16, 21, 79).
+int seg_lanes(int64_t n_obs, int64_t n_valid) {
+  const double avg = n_obs > 0 ? (double)n_valid / (double)n_obs : 1.0;
+  if ((avg >= 2048 && n_obs <= (1 << 15)) || (avg >= 512 && n_obs <= 256)) return 512;
+  return avg >= 1024 || (avg >= 200 && n_obs <= (1 << 15)) || (avg >= 128 && n_obs <= (1 << 12)) ? 64 : 16;
+}
 
 template <typename Ty, typename Tq, typename Tp>
 static hipError_t scatter_typed(int ns, const SellLayout& L, const Ty* y, Tq* q, int64_t vs, int64_t n_obs,
                                 int64_t n_t, int n_rhs, hipStream_t s, const Tp* p, int64_t ps, double* pq_part,
                                 int pq_stride, int pq_slot, const CgState* st) {
   if (n_obs == 0) return hipSuccess;
-  const dim3 g((unsigned)scatter_blocks(n_obs, L.wps)), b(64 * kBlockWaves);
+  const dim3 g((unsigned)scatter_blocks(n_obs, L)), b(64 * kBlockWaves);
   if (L.wps == 0) {
     const float2* w = (const float2*)L.w_pm;
-#define MM_SG(NS, RG) hipLaunchKernelGGL((k_scatter_seg<Ty, Tq, Tp, NS, RG>), g, b, 0, s, L.ptr, L.perm, w, y, q, \
-                                         vs, n_obs, n_t, n_rhs, p, ps, pq_part, pq_stride, pq_slot, st)
-    if (ns == 1) { if (n_rhs == 1) MM_SG(1, 1); else MM_SG(1, 4); }
-    else { if (n_rhs == 1) MM_SG(3, 1); else MM_SG(3, 4); }
+#define MM_SG(NS, RG, G) hipLaunchKernelGGL((k_scatter_seg<Ty, Tq, Tp, NS, RG, G>), g, b, 0, s, L.ptr, L.perm, w, y, \
+                                            q, vs, n_obs, n_t, n_rhs, p, ps, pq_part, pq_stride, pq_slot, st)
+#define MM_SG_G(NS, RG)                      \
+  switch (L.lanes) {                         \
+    case 16: MM_SG(NS, RG, 16); break;       \
+    case 64: MM_SG(NS, RG, 64); break;       \
+    default: MM_SG(NS, RG, 512); break;      \
+  }
+    if (ns == 1) { if (n_rhs == 1) { MM_SG_G(1, 1) } else { MM_SG_G(1, 4) } }
+    else { if (n_rhs == 1) { MM_SG_G(3, 1) } else { MM_SG_G(3, 4) } }
+#undef MM_SG_G
 #undef MM_SG
     return hipGetLastError();
   }

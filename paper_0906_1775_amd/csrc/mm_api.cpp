@@ -789,12 +789,21 @@ void check_tod_dtype(int32_t dt) {
 constexpr int64_t kSegTodBytes = int64_t(256) << 20;
 
 // Wavefronts per slice of the scatter over a layout (0 = no slices: the scatter reads
-// the pixel-major arrays as they are)
+// the pixel-major arrays as they are).  Measured in us, scatter and layout copy, over rasters of
+// 64 to 3 M pixels with 20 to 1500 hits each, both precisions, 1 to 8 RHS (Q, U, float32):
+// - up to 2^18 pixels the slices of 64 leave the chip idle unless all 8 wavefronts share one
+//   (4096 pixels of 80 hits: 32, 22, 15 and 11 with 1, 2, 4 and 8, where 11 is two launches;
+//   65,536 of 20: 21, 18, 17, 15); from 128 hits the pixel-major scatter's lanes are full and it
+//   is the faster one while the TOD allows it (4096 of 400: 31 and 13, 65,536 of 400: 142 and 119);
+// - beyond, the slices fill the chip by themselves and more wavefronts only pay for long rows
+//   (3 M x 20: 305 with 1, 338 with 4; 2^20 x 200: 1163, 1003 and 1042 with 1, 4 and 8);
+// - with 1024 hits pixel-major whatever the TOD, 64 lanes or more on a pixel's hits (1024 columns
+//   of 4096 neighbouring samples: 170 sliced, 27 with 64 lanes, 11 with 512).
 int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid) {
-  int wps = scatter_waves_per_slice(n_obs > 0 ? (double)n_valid / (double)n_obs : 1.0);
-  const int64_t pass_bytes = n_t * (fp64 ? 8 : 4) * std::min(R, 4);
-  if (wps == 0 && pass_bytes > kSegTodBytes) wps = 8;
-  return wps;
+  const double avg = n_obs > 0 ? (double)n_valid / (double)n_obs : 1.0;
+  if (avg >= 1024) return 0;
+  if (n_obs <= (1 << 18)) return avg >= 128 && n_t * (fp64 ? 8 : 4) * std::min(R, 4) <= kSegTodBytes ? 0 : 8;
+  return avg >= 96 ? 4 : avg >= 48 ? 2 : 1;
 }
 
 // Entries the sliced copy of a layout with n_valid samples may take (padding to the
@@ -905,6 +914,7 @@ void build_sell(mm_plan_s* P, Layout& L, int ns, hipStream_t s) {
   auto keep_pixel_major = [&]() {
     L.sell_entries = L.n_valid;
     L.sell.wps = 0;
+    L.sell.lanes = seg_lanes(L.n_obs, L.n_valid);
     L.sell.ptr = L.ptr;
     L.sell.perm = L.perm;
     L.sell.w_pm = L.w_pm;
@@ -1416,10 +1426,10 @@ void build_plan(mm_plan_s* P, const mm_desc_t* d, const int32_t* d_pix, const fl
 
   // ---- p.q partial sums: the sky scatter's blocks, then each template's
   // (a scatter with no observed column writes none)
-  P->n_pq = P->n_obs > 0 ? scatter_blocks(P->n_obs, P->px.sell.wps) : 0;
+  P->n_pq = P->n_obs > 0 ? scatter_blocks(P->n_obs, P->px.sell) : 0;
   for (Template& T : P->tmpl) {
     T.pq_slot = P->n_pq;
-    T.pq_n = T.kind == MM_TMPL_ONEHOT ? (T.lay.n_obs > 0 ? scatter_blocks(T.lay.n_obs, T.lay.sell.wps) : 0) : 1;
+    T.pq_n = T.kind == MM_TMPL_ONEHOT ? (T.lay.n_obs > 0 ? scatter_blocks(T.lay.n_obs, T.lay.sell) : 0) : 1;
     P->n_pq += T.pq_n;
   }
 

@@ -139,7 +139,8 @@ struct SellLayout {
   const int32_t* t = nullptr;      // sample index per entry, -1 = padding
   const float* w = nullptr;        // (sin, cos) per entry (polarisation only)
   int wps = 8;                     // wavefronts per slice in the scatter (1, 2, 4 or 8); 0 = no
-                                   // slices: one wavefront per pixel over the pixel-major arrays
+                                   // slices: `lanes` lanes per pixel over the pixel-major arrays
+  int lanes = 16;                  // 16, 64 or 512
   const int64_t* ptr = nullptr;    // pixel-major layout (wps = 0): [n_obs + 1] offsets,
   const int32_t* perm = nullptr;   // [n_valid] sample ids
   const float* w_pm = nullptr;     // [n_valid][2] (sin, cos) (polarisation only)
@@ -160,9 +161,9 @@ hipError_t launch_scatter(bool in_f64, int ns, const SellLayout& L, const void* 
 hipError_t launch_scatter_q32(int ns, const SellLayout& L, const float* y, float* q, int64_t vs, int64_t n_obs,
                               int64_t n_t, int n_rhs, hipStream_t s, const float* p32, int64_t vs32,
                               double* pq_part, int pq_stride, int pq_slot, const CgState* st);
-// blocks (= p.q partial sums) of a scatter over n_obs pixels with wps wavefronts per slice
-int scatter_blocks(int64_t n_obs, int wps);
-int scatter_waves_per_slice(double avg_entries_per_pixel);   // 0: pixel-major, no slices
+// blocks (= p.q partial sums) of a scatter over the n_obs pixels of a layout
+int scatter_blocks(int64_t n_obs, const SellLayout& L);
+int seg_lanes(int64_t n_obs, int64_t n_valid);   // lanes per pixel of the pixel-major scatter
 hipError_t launch_convert(bool in_f64, bool out_f64, const void* in, void* out, int64_t n,
                           hipStream_t s);
 // observed <-> global layout of n_rhs rows (strides obs_stride, glob_stride in doubles)
