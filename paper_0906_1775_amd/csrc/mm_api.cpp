@@ -1235,7 +1235,7 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
       B.pers += block_bytes(n_tiles, sizeof(SampleTile)) + block_bytes(D.n_seg + 1, 8) + block_bytes(D.n_seg + 1, 4) +
                 block_bytes(std::max<int64_t>(n_tiles, 1) * R * kHwpColumns, 8);
       n_tunk += (int64_t)kHwpColumns * D.n_seg;
-      n_pq += 1;
+      n_pq += kHwpReduceBlocks;
       B.temps += block_bytes((int64_t)kHwpColumns * D.n_seg, 8);  // preconditioner diagonal
     }
   }
@@ -1429,7 +1429,8 @@ void build_plan(mm_plan_s* P, const mm_desc_t* d, const int32_t* d_pix, const fl
   P->n_pq = P->n_obs > 0 ? scatter_blocks(P->n_obs, P->px.sell) : 0;
   for (Template& T : P->tmpl) {
     T.pq_slot = P->n_pq;
-    T.pq_n = T.kind == MM_TMPL_ONEHOT ? (T.lay.n_obs > 0 ? scatter_blocks(T.lay.n_obs, T.lay.sell) : 0) : 1;
+    T.pq_n = T.kind == MM_TMPL_ONEHOT ? (T.lay.n_obs > 0 ? scatter_blocks(T.lay.n_obs, T.lay.sell) : 0)
+                                               : hwp_reduce_blocks(T.n_tiles, T.n_seg);
     P->n_pq += T.pq_n;
   }
 

@@ -51,6 +51,7 @@ constexpr int kMaxRhs = 64;
 
 constexpr int kDotBlocks = 256;     // partial sums per dot product (fixed => deterministic)
 constexpr int kDotThreads = 256;
+constexpr int kHwpReduceBlocks = 64; // bound on the half-wave-plate reduction's grid (and its p.q partial sums)
 constexpr int kScatterBlocks = 2048; // bound on the scatter grid (and its p.q partial sums)
 
 // sum over aligned groups of G lanes (G a power of two <= 64)
@@ -264,12 +265,14 @@ hipError_t launch_hwp_gather(bool y_f64, const SampleTile* tiles, int n_tiles, c
                              const float* omega, const double* p, int64_t vs, int64_t off, void* y, int64_t n_t,
                              int n_rhs, hipStream_t s, const CgState* st = nullptr);
 // q[r * vs + off + 32 g + i] = sum over segment g of C[t][i] y[r][t] (tile partials in `partial`,
-// [n_tiles][n_rhs][32]); with p also the block's p.q in pq_part[r * pq_stride + pq_slot]
+// [n_tiles][n_rhs][32]); with p also the p.q of each of hwp_reduce_blocks() blocks
+// in pq_part[r * pq_stride + pq_slot + block]
 hipError_t launch_hwp_scatter(bool y_f64, const SampleTile* tiles, int n_tiles, const int32_t* seg_tile, int n_seg,
                               const int64_t* seg_start, const float* omega, const void* y, int64_t n_t, int n_rhs,
                               double* partial, double* q, int64_t vs, int64_t off, const double* p,
                               double* pq_part, int pq_stride, int pq_slot, hipStream_t s,
                               const CgState* st = nullptr);
+int hwp_reduce_blocks(int n_tiles, int n_seg);   // p.q partial sums of launch_hwp_scatter
 // diag[32 g + i] = sum over segment g of C[t][i]^2 w_t, w_t = f_b(0) (kind 0) or 1 (kind 1)
 hipError_t launch_hwp_diag(int kind, const SampleTile* tiles, int n_tiles, const int32_t* seg_tile, int n_seg,
                            const int64_t* seg_start, const float* omega, const int64_t* iv_start, int n_iv,
