@@ -376,6 +376,135 @@ hipError_t launch_cg_step_next(void* x, bool x_f32, double* xbest, void* p, bool
   return hipGetLastError();
 }
 
+// k_cg_update and k_cg_step_next in one launch for a small map: one block of 1024 threads per
+// right-hand side holds the whole row in registers (KP pixels a thread), so the dot products need
+// no partial sums in memory, z is not stored, and every load is issued before the p.q partial sums
+// are folded.  Bound by two memory round trips and the launch.
+constexpr int kRowThreads = 1024;
+template <int NS, int KP, typename Tx, typename Tv>
+__global__ __launch_bounds__(kRowThreads) void k_cg_row(
+    double* __restrict__ rv, const Tv* __restrict__ q, const double* __restrict__ minv, Tx* __restrict__ x,
+    Tx* __restrict__ xbest, Tv* __restrict__ p, CgState* __restrict__ st, int n_obs, int64_t vs,
+    const double* __restrict__ pq_part, int n_pq, double* __restrict__ history, int hist_stride) {
+  constexpr int NM = NS == 1 ? 1 : 6;
+  constexpr bool kBest = sizeof(Tx) == sizeof(double);   // the iterate lives in x or xbest
+  __shared__ double sh[2][kRowThreads / 64];
+  const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = (int)blockDim.x >> 6;
+  CgState s = st[r];
+  double pq = 0.0;
+  for (int i = tid; i < n_pq; i += (int)blockDim.x) pq += pq_part[(int64_t)r * n_pq + i];
+  double rr[KP][NS], m[KP][NM];
+  Tv qq[KP][NS], pp[KP][NS];
+  Tx xx[KP][NS], xo[KP][NS];
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const int o = tid + k * (int)blockDim.x, oc = o < n_obs ? o : 0;
+    const int64_t b = (int64_t)r * vs + (int64_t)oc * NS;
+#pragma unroll
+    for (int c = 0; c < NM; ++c) m[k][c] = minv[(int64_t)oc * NM + c];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      rr[k][c] = rv[b + c];
+      qq[k][c] = q[b + c];
+      pp[k][c] = p[b + c];
+      xx[k][c] = x[b + c];
+      xo[k][c] = kBest ? xbest[b + c] : xx[k][c];
+    }
+  }
+  // sums over the block, the same on every thread and in a fixed order
+  auto wave_sum = [&](double v) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+  };
+  pq = wave_sum(pq);
+  if (lane == 0) sh[0][wv] = pq;
+  __syncthreads();
+  pq = 0.0;
+  for (int w = 0; w < nw; ++w) pq += sh[0][w];
+  __syncthreads();
+  s.alpha = 0.0;
+  s.breakdown = 0;
+  if (s.active) {
+    if (pq > 0.0 && isfinite(pq)) s.alpha = s.rho / pq;
+    else s.breakdown = 1;
+  }
+  const bool act = s.active && s.alpha != 0.0;
+  double zz[KP][NS];
+  double rz = 0.0, r2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+#pragma unroll
+    for (int c = 0; c < NS; ++c) rr[k][c] -= s.alpha * (double)qq[k][c];
+    precond_apply<NS>(m[k], rr[k], zz[k]);
+    if (!act || tid + k * (int)blockDim.x >= n_obs) continue;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      rz += rr[k][c] * zz[k][c];
+      r2 += rr[k][c] * rr[k][c];
+    }
+  }
+  rz = wave_sum(rz);
+  r2 = wave_sum(r2);
+  if (lane == 0) sh[0][wv] = rz, sh[1][wv] = r2;
+  __syncthreads();
+  rz = r2 = 0.0;
+  for (int w = 0; w < nw; ++w) rz += sh[0][w], r2 += sh[1][w];
+  const bool stepped = cg_scalar_step(s, rz, r2);
+  int src = 0, dst = 0;
+  if (kBest && stepped) {
+    src = s.xcur;
+    dst = s.xcur == s.xbest ? 1 - s.xcur : s.xcur;
+    s.xcur = dst;
+    if (s.copy_best) s.xbest = dst;
+  }
+  if (tid == 0) {
+    st[r] = s;
+    if (stepped && history) history[(int64_t)r * hist_stride + s.iter % hist_stride] = s.rel;
+  }
+  Tx* __restrict__ xd = dst ? xbest : x;
+#pragma unroll
+  for (int k = 0; k < KP; ++k) {
+    const int o = tid + k * (int)blockDim.x;
+    if (o >= n_obs) break;
+    const int64_t b = (int64_t)r * vs + (int64_t)o * NS;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+      if (act) rv[b + c] = rr[k][c];
+      if (!stepped) continue;
+      const double pj = (double)pp[k][c];
+      const Tx x0 = xx[k][c], x1 = xo[k][c];
+      xd[b + c] = (Tx)((double)(src ? x1 : x0) + s.alpha * pj);
+      p[b + c] = (Tv)((double)(Tv)zz[k][c] + s.beta * pj);
+    }
+  }
+}
+
+// pixels of the largest map that launch_cg_row takes: a row of 4 (2) pixels a thread (T; I, Q, U)
+bool cg_row_fits(int ns, int64_t n_obs, int64_t n_tail) {
+  return n_tail == 0 && n_obs > 0 && n_obs <= (ns == 1 ? 4 : 2) * kRowThreads;
+}
+
+hipError_t launch_cg_row(int ns, double* r, const void* q, bool v_f32, const double* minv, void* x, bool x_f32,
+                         double* xbest, void* p, CgState* st, int64_t n_obs, int64_t vs, int n_rhs,
+                         const double* pq_part, int n_pq, double* history, int hist_stride, hipStream_t s) {
+  if (!cg_row_fits(ns, n_obs, 0) || (x_f32 && !v_f32)) return hipErrorInvalidValue;
+  const dim3 g((unsigned)n_rhs), b((unsigned)std::min<int64_t>(kRowThreads, (n_obs + 63) / 64 * 64));
+#define MM_ROW(NS, KP, TX, TV)                                                                                  \
+  hipLaunchKernelGGL((k_cg_row<NS, KP, TX, TV>), g, b, 0, s, r, (const TV*)q, minv, (TX*)x, (TX*)xbest, (TV*)p, st, \
+                     (int)n_obs, vs, pq_part, n_pq, history, hist_stride)
+#define MM_ROW_T(TX, TV)                                                                     \
+  if (n_obs <= kRowThreads) { if (ns == 1) MM_ROW(1, 1, TX, TV); else MM_ROW(3, 1, TX, TV); } \
+  else if (ns == 1) MM_ROW(1, 4, TX, TV);                                                    \
+  else MM_ROW(3, 2, TX, TV)
+  if (!v_f32) { MM_ROW_T(double, double); }
+  else if (x_f32) { MM_ROW_T(float, float); }
+  else { MM_ROW_T(double, float); }
+#undef MM_ROW_T
+#undef MM_ROW
+  return hipGetLastError();
+}
+
 template <int NS>
 __global__ void k_apply_precond(const double* __restrict__ minv, const double* __restrict__ r,
                                 double* __restrict__ z, int64_t n_obs, int64_t vs,

@@ -1506,6 +1506,15 @@ void enqueue_iteration(mm_plan_s* P, hipStream_t s) {
            "scatter");
   else
     scatter_all(P, P->fs_main.fp64, P->y2, P->vq, R, s, P->vp, P->st);
+  // a small map's vectors take one launch (4.7 + 4.2 us as two, at 1024 pixels)
+  if ((v32 || !P->vp32) && cg_row_fits(P->ns, P->n_obs, P->n_tunk)) {
+    const bool inc = v32 && P->x_inc32;
+    hipchk(launch_cg_row(P->ns, P->vr, P->vq, v32, P->minv, inc ? (void*)P->vdx32() : P->vx, inc, inc ? nullptr : P->vxb,
+                         v32 ? (void*)P->vp32 : P->vp, P->st, P->n_obs, P->nu(), R, P->part_pq, P->n_pq, P->hist,
+                         kHistRing, s),
+           "update, scalar step and next direction");
+    return;
+  }
   hipchk(launch_cg_update(P->ns, P->vr, P->vq, P->vz, v32, P->minv, P->st, P->st_prev, P->n_obs,
                           P->nu(), P->minv_t, P->n_tunk, R, P->part_pq, P->n_pq, P->part2, P->part3, s),
          "update");

@@ -248,6 +248,12 @@ hipError_t launch_cg_step_next(void* x, bool x_f32, double* xbest, void* p, bool
                                CgState* st, const CgState* st_prev, const double* partial_rz,
                                const double* partial_rr, double* history, int hist_stride, int64_t nu, int n_rhs,
                                hipStream_t s, float* p32 = nullptr, int64_t n32 = 0, int64_t vs32 = 0);
+// launch_cg_update and launch_cg_step_next in one launch, for maps that cg_row_fits accepts (no
+// template amplitudes); v_f32: q and p are float32 (rows of stride vs, as all vectors)
+bool cg_row_fits(int ns, int64_t n_obs, int64_t n_tail);
+hipError_t launch_cg_row(int ns, double* r, const void* q, bool v_f32, const double* minv, void* x, bool x_f32,
+                         double* xbest, void* p, CgState* st, int64_t n_obs, int64_t vs, int n_rhs,
+                         const double* pq_part, int n_pq, double* history, int hist_stride, hipStream_t s);
 hipError_t launch_apply_precond(int ns, const double* minv, const double* r, double* z,
                                 int64_t n_obs, int64_t vs, const double* minv_t, int64_t n_tail,
                                 int n_rhs, hipStream_t s);
