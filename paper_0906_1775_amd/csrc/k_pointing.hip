@@ -326,6 +326,20 @@ hipError_t launch_sell_fill(const int64_t* pix_ptr, const int32_t* perm, const f
 constexpr int kBlockWaves = 8;   // wavefronts per scatter block
 constexpr int kBatch = 4;
 
+// Units of work of a scatter block (the grid is a multiple of 8): the hardware deals blocks to
+// the 8 XCDs in turn, and an XCD takes runs of `run` neighbouring units (0: one run, an eighth
+// of the map), so that a TOD line that neighbouring pixels share is fetched into one L2.
+struct XcdUnits {
+  uint32_t i, n, step, units, run;   // i = first, step, .. < n: an XCD's units in its own order
+  __device__ __forceinline__ uint32_t unit(uint32_t i) const {
+    return ((i / run) * 8 + (blockIdx.x & 7)) * run + i % run;
+  }
+};
+__device__ __forceinline__ XcdUnits xcd_units(int64_t n_units, int run) {
+  const uint32_t u = (uint32_t)n_units, r = run ? (uint32_t)run : (u + 7) >> 3;
+  return {blockIdx.x >> 3, (u + 8 * r - 1) / (8 * r) * r, gridDim.x >> 3, u, r};
+}
+
 // RG right-hand sides share one pass over the sliced pointing: the entries are
 // loaded once per group and each RHS keeps its own accumulators, so the
 // pointing is streamed ceil(R / RG) times instead of R times.  WPS wavefronts
@@ -340,7 +354,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter(
     const uint32_t* __restrict__ slice_end, const uint32_t* __restrict__ slice_len,
     const int32_t* __restrict__ sell_t, const float2* __restrict__ sell_w, const Ty* __restrict__ y,
     Tq* __restrict__ q, int64_t vs, int64_t n_obs, int64_t n_t, int n_rhs, const Tp* __restrict__ p, int64_t ps,
-    double* __restrict__ pq_part, int pq_stride, int pq_slot, const CgState* __restrict__ st) {
+    double* __restrict__ pq_part, int pq_stride, int pq_slot, const CgState* __restrict__ st, int run) {
   constexpr int NW = kBlockWaves, SPB = NW / WPS;
   __shared__ double part[WPS > 1 ? NW : 1][RG * NS][64];
   __shared__ double sh[NW][RG];
@@ -360,8 +374,11 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter(
     double pq[RG];
 #pragma unroll
     for (int g = 0; g < RG; ++g) pq[g] = 0.0;
-    for (int64_t s0 = (int64_t)blockIdx.x * SPB; s0 < n_sl; s0 += (int64_t)gridDim.x * SPB) {
-      const int64_t s = s0 + sg;
+    const XcdUnits xu = xcd_units((n_sl + SPB - 1) / SPB, run);
+    for (uint32_t xi = xu.i; xi < xu.n; xi += xu.step) {   // uniform over the block
+      const int64_t u = xu.unit(xi);
+      if (u >= xu.units) continue;
+      const int64_t s = u * SPB + sg;
       const bool sv = s < n_sl;
       const int64_t base = sv ? (int64_t)slice_end[s] - slice_len[s] + lane : 0;
       const int width = sv ? (int)(slice_len[s] >> 6) : 0;
@@ -470,7 +487,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
     const int64_t* __restrict__ pix_ptr, const int32_t* __restrict__ perm, const float2* __restrict__ w_pm,
     const Ty* __restrict__ y, Tq* __restrict__ q, int64_t vs, int64_t n_obs, int64_t n_t, int n_rhs,
     const Tp* __restrict__ p, int64_t ps, double* __restrict__ pq_part, int pq_stride, int pq_slot,
-    const CgState* __restrict__ st) {
+    const CgState* __restrict__ st, int run) {
   constexpr int NW = kBlockWaves, NT = 64 * NW, PPB = NT / G;   // PPB pixels per block
   constexpr bool kWide = G > 64;
   constexpr int kSegBatch = kWide && NS * RG == 1 ? 8 : 4;      // loads in flight per lane
@@ -491,8 +508,11 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
     double pq[RG];
 #pragma unroll
     for (int g = 0; g < RG; ++g) pq[g] = 0.0;
-    for (int64_t b0 = (int64_t)blockIdx.x * PPB; b0 < n_obs; b0 += (int64_t)gridDim.x * PPB) {   // uniform over the block
-      const int64_t o = b0 + tid / G;
+    const XcdUnits xu = xcd_units((n_obs + PPB - 1) / PPB, run);
+    for (uint32_t xi = xu.i; xi < xu.n; xi += xu.step) {   // uniform over the block
+      const int64_t u = xu.unit(xi);
+      if (u >= xu.units) continue;
+      const int64_t o = u * PPB + tid / G;
       const bool ov = o < n_obs;
       const int64_t k0 = ov ? pix_ptr[o] : 0, k1 = ov ? pix_ptr[o + 1] : 0;   // k1 > k0 for an observed pixel
       int span = (int)(k1 - k0);            // the wavefront walks its longest pixel
@@ -606,7 +626,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
 int scatter_blocks(int64_t n_obs, const SellLayout& L) {
   const int64_t n_u = L.wps == 0 ? n_obs : (n_obs + 63) / 64;                                // pixels or slices
   const int64_t per = L.wps == 0 ? 64 * kBlockWaves / L.lanes : kBlockWaves / L.wps;   // of a block and step
-  return (int)std::max<int64_t>(1, std::min<int64_t>((n_u + per - 1) / per, kScatterBlocks));
+  return (int)std::min<int64_t>(8 * ((n_u + 8 * per - 1) / (8 * per)), kScatterBlocks);   // n_obs > 0
 }
 
 // Lanes per pixel of the pixel-major scatter (128 hits and more on average, or a sliced copy that
@@ -629,7 +649,7 @@ static hipError_t scatter_typed(int ns, const SellLayout& L, const Ty* y, Tq* q,
   if (L.wps == 0) {
     const float2* w = (const float2*)L.w_pm;
 #define MM_SG(NS, RG, G) hipLaunchKernelGGL((k_scatter_seg<Ty, Tq, Tp, NS, RG, G>), g, b, 0, s, L.ptr, L.perm, w, y, \
-                                            q, vs, n_obs, n_t, n_rhs, p, ps, pq_part, pq_stride, pq_slot, st)
+                                            q, vs, n_obs, n_t, n_rhs, p, ps, pq_part, pq_stride, pq_slot, st, L.run)
 #define MM_SG_G(NS, RG)                      \
   switch (L.lanes) {                         \
     case 16: MM_SG(NS, RG, 16); break;       \
@@ -644,7 +664,7 @@ static hipError_t scatter_typed(int ns, const SellLayout& L, const Ty* y, Tq* q,
   }
   const float2* w = (const float2*)L.w;
 #define MM_SC(NS, RG, WPS) hipLaunchKernelGGL((k_scatter<Ty, Tq, Tp, NS, RG, WPS>), g, b, 0, s, L.end, L.len, L.t, \
-                                              w, y, q, vs, n_obs, n_t, n_rhs, p, ps, pq_part, pq_stride, pq_slot, st)
+                                              w, y, q, vs, n_obs, n_t, n_rhs, p, ps, pq_part, pq_stride, pq_slot, st, L.run)
 #define MM_SC_W(NS, RG)                        \
   switch (L.wps) {                             \
     case 1: MM_SC(NS, RG, 1); break;           \

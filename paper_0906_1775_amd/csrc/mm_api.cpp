@@ -806,6 +806,20 @@ int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid) 
   return avg >= 96 ? 4 : avg >= 48 ? 2 : 1;
 }
 
+// Neighbouring blocks' worth of pixels that one XCD takes in the scatter (0 = an eighth of the
+// map).  Pixels next to each other along either axis of the map share lines of the TOD; with
+// blocks dealt to the XCDs one by one every XCD fetches every line.  Eighths: 157 x 157 pixels of
+// 73 hits, 3 float64 RHS 39 -> 31 us, 400 x 400 233 -> 148, 1000 x 1000 of 20, 8 float32 RHS
+// 1467 -> 1029.  Not where rows are a power of two long (told by the pixel count): there blocks
+// dealt one by one already give an XCD a stripe of columns, and an eighth's lines, a power of
+// two apart, meet in a few channels of its L2 (256 x 256 of 256 hits, 8 RHS 762 -> 1393;
+// 1024 x 1024 1267 -> 1927).  Past 2^18 pixels one float32 row gains nothing (1000 x 1000 of
+// 256: 1503 -> 1605).
+int scatter_run(int64_t n_keys, int64_t n_obs, bool fp64, int R) {
+  if ((n_keys & ((1 << 14) - 1)) == 0) return 1;
+  return n_obs <= (1 << 18) || R * (fp64 ? 8 : 4) >= 16 ? 0 : 1;
+}
+
 // Entries the sliced copy of a layout with n_valid samples may take (padding to the
 // widest pixel of each slice included); a layout whose slices need more keeps the
 // pixel-major arrays for the scatter.  Bounds the workspace from the descriptor alone.
@@ -851,6 +865,7 @@ void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, co
     L.n_obs = *P->slot<uint32_t>(kPinObs);
     L.n_valid = *P->slot<int64_t>(kPinValid);
     L.wps = layout_waves(n, P->main_fp64(), P->R, L.n_obs, L.n_valid);
+    L.sell.run = scatter_run(n_keys, L.n_obs, P->main_fp64(), P->R);
     L.ptr = P->alloc<int64_t>(L.n_obs + 1);
     L.obs2glob = P->alloc<int32_t>(L.n_obs);
     if (L.wps > 0) {

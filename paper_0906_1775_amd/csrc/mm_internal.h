@@ -142,6 +142,7 @@ struct SellLayout {
   int wps = 8;                     // wavefronts per slice in the scatter (1, 2, 4 or 8); 0 = no
                                    // slices: `lanes` lanes per pixel over the pixel-major arrays
   int lanes = 16;                  // 16, 64 or 512
+  int run = 1;                     // neighbouring blocks' worth of pixels that one XCD takes; 0 = an eighth of all
   const int64_t* ptr = nullptr;    // pixel-major layout (wps = 0): [n_obs + 1] offsets,
   const int32_t* perm = nullptr;   // [n_valid] sample ids
   const float* w_pm = nullptr;     // [n_valid][2] (sin, cos) (polarisation only)

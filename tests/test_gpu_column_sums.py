@@ -53,7 +53,7 @@ def test_scatter_of_few_pixels(n_pix, hits, n_stokes, n_rhs, precision, tol):
 @pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-5)])
 @pytest.mark.parametrize("n_pix,hits,n_stokes,n_rhs", [(16385, 3, 3, 5), (40000, 50, 1, 3), (40000, 129, 3, 1),
                                                       (70000, 4, 3, 1), (262209, 3, 3, 2), (262209, 49, 1, 1),
-                                                      (262209, 97, 1, 1)])
+                                                      (262209, 97, 1, 1), (32768, 5, 3, 2), (49152, 140, 1, 1)])
 def test_scatter_of_many_pixels(n_pix, hits, n_stokes, n_rhs, precision, tol):
     test_scatter_of_few_pixels(n_pix, hits, n_stokes, n_rhs, precision, tol)
 
