@@ -288,17 +288,19 @@ __device__ __forceinline__ double inv_psd(uint32_t j, uint32_t L, const PsdParam
 // part[filter][g][tau].  Every F_r stays on chip (written out and read back they were 16 bytes
 // per frequency and filter, and the sum over r ran serially in n_c threads).
 template <int LOGM, int NB>
-__global__ __launch_bounds__(Shape<LOGM>::NT) void k_lag_sums(const double* __restrict__ params, int f0, double f_samp,
-                                                              int64_t L, int n_c, const cx<double>* __restrict__ ptw,
+__global__ __launch_bounds__(Shape<LOGM>::NT) void k_lag_sums(const double* __restrict__ params, int n_filters, int f0,
+                                                              double f_samp, int64_t L, int n_c,
+                                                              const cx<double>* __restrict__ ptw,
                                                               const double* __restrict__ tab,
-                                                              double* __restrict__ part, int mode) {
+                                                              double* __restrict__ part, int mode0) {
   using F = ShapeFFT<double, LOGM>;
   __shared__ __align__(16) char lds[F::LDS_BYTES];
   constexpr int M = F::N, E = F::E;
   const int t = threadIdx.x;
   const uint32_t R = (uint32_t)(L >> LOGM), mask = (uint32_t)L - 1;   // (L <= 2^30)
   const double unit = 2.0 / (double)L;   // exact: L is a power of two
-  const PsdParams P = psd_params(params + 3 * (int64_t)(f0 + blockIdx.y), f_samp, L);
+  const int set = f0 + (int)blockIdx.y, mode = mode0 + set / n_filters;   // sets: filters of mode0, of the next, ..
+  const PsdParams P = psd_params(params + 3 * (int64_t)(set % n_filters), f_samp, L);
   constexpr int L0 = F::first_log_fwd(), R0 = 1 << L0;
   constexpr int LL = F::last_log_fwd(), RL = 1 << LL;
   double acc[NB][E];
@@ -400,7 +402,7 @@ static LagSplit lag_split(int n_c, int64_t lag_len) {
 
 hipError_t launch_lags(const double* params, int n_filters, double f_samp, int n_c,
                        int64_t lag_len, double* lags, void* scratch, size_t scratch_bytes,
-                       hipStream_t s, int mode) {
+                       hipStream_t s, int mode, int n_modes) {
   if (lag_min_logm(n_c) > kMaxLogNF64) return hipErrorInvalidValue;
   const int64_t R0 = lag_len >> lag_min_logm(n_c);
   if (R0 < 2 || (R0 << lag_min_logm(n_c)) != lag_len) return hipErrorInvalidValue;
@@ -425,14 +427,15 @@ hipError_t launch_lags(const double* params, int n_filters, double f_samp, int n
   }
   double* part = (double*)((char*)scratch + off);
   const size_t fit = (scratch_bytes - off) / per_filter;
-  const int batch = (int)(fit < 65535 ? fit : 65535);   // filters per launch (grid y)
-  for (int f0 = 0; f0 < n_filters; f0 += batch) {
-    const int nb = (n_filters - f0) < batch ? (n_filters - f0) : batch;
+  const int batch = (int)(fit < 65535 ? fit : 65535);   // sets per launch (grid y)
+  const int n_sets = n_filters * n_modes;
+  for (int f0 = 0; f0 < n_sets; f0 += batch) {
+    const int nb = (n_sets - f0) < batch ? (n_sets - f0) : batch;
     e = with_plain(sp.logm, [&](auto LC) -> hipError_t {
       constexpr int LOGM = decltype(LC)::value < kLagLogM ? decltype(LC)::value : kLagLogM;
       const dim3 g((unsigned)sp.groups, (unsigned)nb), b(Shape<LOGM>::NT);
 #define MM_LAGS(NB) \
-  hipLaunchKernelGGL((k_lag_sums<LOGM, NB>), g, b, 0, s, params, f0, f_samp, lag_len, n_c, ptw, tab, part, mode)
+  hipLaunchKernelGGL((k_lag_sums<LOGM, NB>), g, b, 0, s, params, n_filters, f0, f_samp, lag_len, n_c, ptw, tab, part, mode)
       if (n_c <= (1 << LOGM)) MM_LAGS(1);
       else if (n_c <= (2 << LOGM)) MM_LAGS(2);
       else if (n_c <= (4 << LOGM)) MM_LAGS(4);

@@ -1315,8 +1315,9 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
   // noise gradient
   if (d->filter_params) {
     const int64_t N64 = int64_t(1) << logn64;
-    B.call_temps = block_bytes(std::max<int64_t>(n, 1), 8) + block_bytes((int64_t)nf_filt * n_c, 8) +
-                   block_bytes(3 * (int64_t)nf_filt * N64, 8) + block_bytes(3 * (int64_t)std::max(d->n_intervals, 1), 8) +
+    const int64_t n_dots = (int64_t)std::max(d->n_intervals, 1) * interval_dot_parts(d->n_intervals, longest);
+    B.call_temps = block_bytes(std::max<int64_t>(n, 1), 8) + block_bytes(3 * (int64_t)nf_filt * n_c, 8) +
+                   block_bytes(3 * (int64_t)nf_filt * N64, 8) + block_bytes(3 * n_dots, 8) +
                    block_bytes((int64_t)std::max(lags_scratch_bytes(n_c, lag_len, batch),
                                                  spectra_scratch_bytes(logn64)), 1);
   }
@@ -2368,9 +2369,10 @@ mm_status_t mm_noise_gradient(mm_plan_t P, const void* d_tod, int32_t tod_dtype,
     const size_t lsb = lags_scratch_bytes(P->n_c, P->lag_len, batch);
     // temporaries above the work vectors, released in reverse order on every exit
     double* v64 = P->temp<double>(std::max<int64_t>(P->n_t, 1));               // v_r = d_r - P m_r
-    double* dlags = P->temp<double>((int64_t)nfl * P->n_c);
+    const int parts = interval_dot_parts(P->n_iv, longest_interval(P->iv_start));
+    double* dlags = P->temp<double>(3 * (int64_t)nfl * P->n_c);
     double* dspec = P->temp<double>(3 * spec_n);                                   // one symbol per theta
-    double* ivd = P->temp<double>(3 * (int64_t)n_iv);
+    double* ivd = P->temp<double>(3 * (int64_t)n_iv * parts);
     char* lscr = P->temp<char>((int64_t)std::max(lsb, spectra_scratch_bytes(f64.logn)));
     auto release_all = [&]() {
       P->release(lscr);
@@ -2379,14 +2381,11 @@ mm_status_t mm_noise_gradient(mm_plan_t P, const void* d_tod, int32_t tod_dtype,
       P->release(dlags);
       P->release(v64);
     };
-    std::vector<double> hd(3 * (size_t)n_iv);
+    std::vector<double> hd(3 * (size_t)n_iv * parts);
     std::vector<double> grad((size_t)nfl * 3, 0.0);
     try {
-      for (int mode = 1; mode <= 3; ++mode) {
-        hipchk(launch_lags(P->d_params, nfl, P->f_samp, P->n_c, P->lag_len, dlags, lscr, lsb, s, mode),
-               "derivative lags");
-        build_symbols(f64, dlags, nfl, P->n_c, dspec + (mode - 1) * spec_n, lscr, s);
-      }
+      hipchk(launch_lags(P->d_params, nfl, P->f_samp, P->n_c, P->lag_len, dlags, lscr, lsb, s, 1, 3), "derivative lags");
+      build_symbols(f64, dlags, 3 * nfl, P->n_c, dspec, lscr, s);
       for (int r = 0; r < P->R; ++r) {
         // v_r = d_r - P m_r and u_r = P lambda_r, both in float64
         to_obs(P, d_m + (int64_t)r * P->ng(), P->vz, 1, s);
@@ -2397,13 +2396,15 @@ mm_status_t mm_noise_gradient(mm_plan_t P, const void* d_tod, int32_t tod_dtype,
         gather_all(P, true, P->vz, ya, 1, s);
         for (int mode = 0; mode < 3; ++mode) {
           apply_ols(P, f64, true, v64, yb, dspec + mode * spec_n, 1, s);
-          hipchk(launch_interval_dots(ya, yb, P->d_iv_start, P->n_iv, ivd + (int64_t)mode * n_iv, s),
+          hipchk(launch_interval_dots(ya, yb, P->d_iv_start, P->n_iv, parts, ivd + (int64_t)mode * n_iv * parts, s),
                  "interval dots");
         }
-        hipchk(hipMemcpyAsync(hd.data(), ivd, sizeof(double) * 3 * n_iv, hipMemcpyDeviceToHost, s), "copy");
+        hipchk(hipMemcpyAsync(hd.data(), ivd, sizeof(double) * hd.size(), hipMemcpyDeviceToHost, s), "copy");
         hipchk(hipStreamSynchronize(s), "noise gradient");
         for (int mode = 0; mode < 3; ++mode)
-          for (int b = 0; b < P->n_iv; ++b) grad[(size_t)P->iv_filter[b] * 3 + mode] += hd[(size_t)mode * n_iv + b];
+          for (int b = 0; b < P->n_iv; ++b)
+            for (int i = 0; i < parts; ++i)
+              grad[(size_t)P->iv_filter[b] * 3 + mode] += hd[((size_t)mode * n_iv + b) * parts + i];
       }
     } catch (...) {
       release_all();

@@ -77,8 +77,8 @@ bool ols_variant_exists(int logn, bool fp64, int variant);
 bool ols_variant_wave(int logn, bool fp64, int variant);
 // lags (mode 0) or their derivative with respect to sigma (1), f_knee (2), alpha (3)
 hipError_t launch_lags(const double* params /*dev [nf][3]*/, int n_filters, double f_samp, int n_c,
-                       int64_t lag_len, double* lags /*dev [nf][n_c]*/, void* scratch,
-                       size_t scratch_bytes, hipStream_t s, int mode = 0);
+                       int64_t lag_len, double* lags /*dev [n_modes][nf][n_c]*/, void* scratch,
+                       size_t scratch_bytes, hipStream_t s, int mode = 0, int n_modes = 1);
 size_t lags_scratch_bytes(int n_c, int64_t lag_len, int filters_per_batch);
 // the symbol of filter f at the shifted frequencies k + 1/4 of N = 2^logn points, times 1/N:
 // F_k at spec[f][(k mod 2^rowlog) 2^(logn - rowlog) + (k >> rowlog)]
@@ -208,8 +208,10 @@ hipError_t launch_build_layout(const uint32_t* keys, const int32_t* vals, const 
 hipError_t launch_obs_index(const int32_t* key, int64_t n, const int32_t* obs2glob, int64_t n_obs,
                             int32_t* glob2obs, int64_t n_keys, int32_t* pix_obs, hipStream_t s);
 
-// out[b] = sum over interval b of u_t v_t (one workgroup per interval, fixed order)
-hipError_t launch_interval_dots(const double* u, const double* v, const int64_t* iv_start, int n_iv,
+// partial sums over interval b of u_t v_t, in a fixed order
+// (interval_dot_parts() of them per interval, in out[interval][part])
+int interval_dot_parts(int n_iv, int64_t longest);
+hipError_t launch_interval_dots(const double* u, const double* v, const int64_t* iv_start, int n_iv, int parts,
                                 double* out, hipStream_t s);
 
 // ---------------------------------------------------------------- CG (k_cg.hip)
