@@ -369,6 +369,12 @@ __device__ __forceinline__ void buffer_get(Rsrc b, uint32_t off, float& x) {
 __device__ __forceinline__ void buffer_get(Rsrc b, uint32_t off, double& x) {
   x = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, 0));
 }
+__device__ __forceinline__ void buffer_get(Rsrc b, uint32_t off, int32_t& x) {
+  x = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, 0);
+}
+__device__ __forceinline__ void buffer_get(Rsrc b, uint32_t off, float2& x) {
+  x = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, 0));
+}
 __device__ __forceinline__ void buffer_put(Rsrc b, uint32_t off, float x) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), b, (int)off, 0, 0);
 }

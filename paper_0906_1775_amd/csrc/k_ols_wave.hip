@@ -42,6 +42,7 @@
 
 #include "fft.hpp"
 #include "mm_internal.h"
+#include "sky.hpp"
 
 namespace mm {
 
@@ -446,12 +447,16 @@ __device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row
 // (RHS, chunk) pairs instead, so that neighbouring chunks, whose windows overlap by 2 n_c
 // samples, read the shared samples through the same L2.  16 wavefronts per CU (4 per SIMD)
 // whatever NO: LDS holds 16 rows.
-template <typename T, typename Tin, int NO, int RPW>
+//
+// SKY = 1 or 3: the window is looked up: yin is a map of SKY Stokes parameters (rows of stride
+// sky.vs), sample t the value of pixel sky.idx[t] (-1: none) rounded to T, as the gather
+// kernel would have stored it (the plan's sees_map says when, with both sides' times).
+template <typename T, typename Tin, int NO, int RPW, int SKY>
 __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, WaveShape<NO, RPW>::NT),
                           amdgpu_waves_per_eu(4))) void k_ols_wave(
     const Tin* __restrict__ yin, T* __restrict__ yout, const OlsChunk* __restrict__ chunks,
     const T* __restrict__ spec, const cx<T>* __restrict__ tab, int64_t n_t, int n_c, int m,
-    const CgState* __restrict__ st) {
+    const CgState* __restrict__ st, SkyView sky) {
   using S = WaveShape<NO, RPW>;
   constexpr int N = S::N, NT = S::NT;
   constexpr int LOGNO = S::LOGNO;
@@ -471,7 +476,38 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
   // them gives the zeros (every constant beside a column's offset is a multiple of 4096
   // bytes, which the instruction's offset field cannot hold)
   cx<T> v[S::E];
-  {
+  if constexpr (SKY > 0) {
+    const int64_t s0 = ch.out_start - n_c;
+    const int a = (int)(ch.iv_lo > s0 ? ch.iv_lo - s0 : 0);
+    const int b = (int)(ch.iv_hi - s0 < 2 * N ? ch.iv_hi - s0 : 2 * N);
+    const Rsrc ids = buffer_of(sky.idx + s0 + a, (b - a) * 4);
+    const Rsrc ang = buffer_of(SKY == 3 ? sky.w + (s0 + a) : nullptr, SKY == 3 ? (b - a) * 8 : 0);
+    const Tin* __restrict__ map = yin + (int64_t)rhs * sky.vs;
+    constexpr int K = 2 * NO < 32 ? 2 * NO : 32;   // samples whose pixels are in registers at once
+#pragma unroll
+    for (int c = 0; c < S::C; ++c) {
+      const uint32_t i = opaque((uint32_t)(t + NT * c - a));
+#pragma unroll
+      for (int e0 = 0; e0 < 2 * NO; e0 += K) {
+        int32_t p[K];   // -1 outside the data (there the buffer reads 0)
+#pragma unroll
+        for (int e = 0; e < K; ++e) {
+          const uint32_t k = i + 1024 * ((e0 + e) % NO) + ((e0 + e) / NO) * N;
+          buffer_get(ids, 4 * k, p[e]);
+          p[e] = k < (uint32_t)(b - a) ? p[e] : -1;
+        }
+#pragma unroll
+        for (int e = 0; e < K; ++e) {
+          const int n_o = (e0 + e) % NO, half = (e0 + e) / NO;
+          float2 sc = make_float2(0.f, 0.f);
+          if constexpr (SKY == 3) buffer_get(ang, 8 * (i + 1024 * n_o + half * N), sc);
+          const double val = sky_value<SKY, Tin>(map, p[e] >= 0 ? p[e] : 0, sc.x, sc.y);
+          const T x = p[e] >= 0 ? (T)val : (T)0;
+          if (half) v[c * NO + n_o].im = -x; else v[c * NO + n_o].re = x;
+        }
+      }
+    }
+  } else {
     const int64_t s0 = ch.out_start - n_c;
     const int64_t lo = ch.iv_lo, hi = ch.iv_hi;
     const int a = (int)(lo > s0 ? lo - s0 : 0);   // (lo <= out_start: a <= n_c)
@@ -557,12 +593,14 @@ hipError_t tables_launch(void* tab, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, typename Tin, int NO>
+template <typename T, typename Tin, int NO, int SKY = 0>
 hipError_t wave_launch(const void* y_in, void* y_out, const OlsChunk* chunks, int n_chunks, const void* spec,
-                       const void* tab, int64_t n_t, int n_c, int m, int n_rhs, hipStream_t s, const CgState* st) {
+                       const void* tab, int64_t n_t, int n_c, int m, int n_rhs, hipStream_t s, const CgState* st,
+                       const SkyView& sky = {}) {
   constexpr int RPW = NO == 32 ? 2 : 1;   // (16 wavefronts at most)
-  hipLaunchKernelGGL((k_ols_wave<T, Tin, NO, RPW>), dim3((unsigned)n_chunks, (unsigned)n_rhs),
-                     dim3(WaveShape<NO, RPW>::NT), 0, s, (const Tin*)y_in, (T*)y_out, chunks, (const T*)spec, (const cx<T>*)tab, n_t, n_c, m, st);
+  hipLaunchKernelGGL((k_ols_wave<T, Tin, NO, RPW, SKY>), dim3((unsigned)n_chunks, (unsigned)n_rhs),
+                     dim3(WaveShape<NO, RPW>::NT), 0, s, (const Tin*)y_in, (T*)y_out, chunks, (const T*)spec,
+                     (const cx<T>*)tab, n_t, n_c, m, st, sky);
   return hipGetLastError();
 }
 
@@ -611,6 +649,24 @@ hipError_t launch_ols_wave(int logn, bool fp64, bool in_f64, const void* y_in, v
   };
   if (fp64) return in_f64 ? go(double{}, double{}) : go(double{}, float{});
   return in_f64 ? go(float{}, double{}) : go(float{}, float{});
+}
+
+hipError_t launch_ols_sky(int logn, bool fp64, bool map_f64, int ns, const void* map, const SkyView& sky, void* y_out,
+                          const OlsChunk* chunks, int n_chunks, const void* spec, const void* tab, int64_t n_t, int n_c,
+                          int m, int n_rhs, hipStream_t s, const CgState* st) {
+  if (!ols_wave_exists(logn, fp64)) return hipErrorInvalidValue;
+  if (n_chunks == 0 || n_rhs == 0) return hipSuccess;
+  auto go = [&](auto tc, auto tin) -> hipError_t {
+    using T = decltype(tc);
+    using Tin = decltype(tin);
+    return wave_dispatch<T>(logn, [&](auto no) -> hipError_t {
+      constexpr int NO = decltype(no)::value;
+      return ns == 1 ? wave_launch<T, Tin, NO, 1>(map, y_out, chunks, n_chunks, spec, tab, n_t, n_c, m, n_rhs, s, st, sky)
+                     : wave_launch<T, Tin, NO, 3>(map, y_out, chunks, n_chunks, spec, tab, n_t, n_c, m, n_rhs, s, st, sky);
+    });
+  };
+  if (fp64) return map_f64 ? go(double{}, double{}) : hipErrorInvalidValue;
+  return map_f64 ? go(float{}, double{}) : go(float{}, float{});
 }
 
 }  // namespace mm

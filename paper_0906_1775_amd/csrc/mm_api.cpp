@@ -708,6 +708,43 @@ void gather_all(mm_plan_s* P, bool y_f64, const double* x, void* y, int R, hipSt
   }
 }
 
+// Whether the filter looks its windows up in the map itself (launch_ols_sky) instead of reading
+// the TOD a gather wrote.  It saves the gather's launch and round trip and the TOD's way out and
+// back, and looks up the samples that windows share twice (halo times the lookups).  Per
+// iteration, separate / fused (us): up to 2^20 samples everywhere 1.05 to 1.24 (65,536 samples,
+// T 30.8 / 26.9, polarisation 35.2 / 32.6); temperature at every size (float64, 2^26 samples of
+// 2000 x 2000 pixels 1003 / 744, 3 x 1.8 M 124 / 104); polarisation in float64 with short
+// halos (2^24: 299 / 280; halo 2: 596 / 625) and in float32 while the TOD is small or, for
+// one row, past the last-level cache (2^22: 72 / 64; 2^24: 232 / 237; 2^26: 855 / 809); not
+// with many rows, each of which reads the pointing again (8 x 2^26: 4004 / 4694), and not from
+// a float64 map of float32 TODs (2^24: 201 / 219).
+bool sees_map(const mm_plan_s* P, const FilterSetup& fs, int R, bool map_f32) {
+  if (P->n_c <= 1 || fs.long_path || !ols_variant_wave(fs.logn, fs.fp64, fs.variant) || !P->tmpl.empty() ||
+      P->n_obs == 0 || (fs.fp64 && map_f32))
+    return false;
+  const int64_t total = R * P->n_t;
+  if (total <= (1 << 20) || P->ns == 1) return true;
+  const double halo = 2.0 * (double)fs.N / (double)fs.m;
+  if (fs.fp64) return halo <= 1.15 && (R <= 2 || total <= (1 << 24));
+  if (!map_f32) return halo <= 1.34 && total <= (1 << 21);
+  if (R > 1) return halo <= 1.15 && total <= (1 << 24);
+  return halo <= 1.34 && (total <= (1 << 22) || (halo <= 1.15 && total >= (1 << 26)));
+}
+
+// y_out = N^-1 P x (rows as gather_all), by way of the TOD y unless one kernel does both
+void weight_of_map(mm_plan_s* P, const FilterSetup& fs, const double* x, void* y, void* y_out, int R, hipStream_t s,
+                   const CgState* st = nullptr, const float* x32 = nullptr) {
+  if (sees_map(P, fs, R, x32 != nullptr)) {
+    const SkyView sky{P->px.obs_idx, (const float2*)P->w, x32 ? P->vs32() : P->nu()};
+    hipchk(launch_ols_sky(fs.logn, fs.fp64, !x32, P->ns, x32 ? (const void*)x32 : x, sky, y_out, fs.chunks, fs.n_chunks,
+                          fs.spec, fs.ptw, P->n_t, P->n_c, fs.m, R, s, st),
+           "gather and filter");
+    return;
+  }
+  gather_all(P, fs.fp64, x, y, R, s, st, x32);
+  weight(P, fs, y, fs.fp64, y_out, R, s, st);
+}
+
 // refresh the float32 copy of p after p was set outside the iteration kernels
 void sync_p32(mm_plan_s* P, hipStream_t s) {
   if (P->vp32) hipchk(launch_rows_to_f32(P->vp, P->nu(), P->vp32, P->vs32(), P->nmap(), P->R, s), "p copy");
@@ -763,8 +800,7 @@ void to_glob(mm_plan_s* P, const double* obs, double* glob, int R, hipStream_t s
 // out = [P B]^T N^-1 [P B] in (iteration layout), R right-hand sides, precision of fs
 void apply_H_obs(mm_plan_s* P, const FilterSetup& fs, const double* in, double* out, void* ya, void* yb,
                  int R, hipStream_t s) {
-  gather_all(P, fs.fp64, in, ya, R, s);
-  weight(P, fs, ya, fs.fp64, yb, R, s);
+  weight_of_map(P, fs, in, ya, yb, R, s);
   scatter_all(P, fs.fp64, yb, out, R, s);
 }
 
@@ -1509,8 +1545,7 @@ void enqueue_iteration(mm_plan_s* P, hipStream_t s) {
   // q = H p, with the partial sums of p.q formed by the scatters
   // (RHS that stopped iterating skip the TOD work: convergence is checked by
   // the host only every check_every iterations)
-  gather_all(P, P->fs_main.fp64, P->vp, P->y1, R, s, P->st, P->vp32);
-  weight(P, P->fs_main, P->y1, P->fs_main.fp64, P->y2, R, s, P->st);
+  weight_of_map(P, P->fs_main, P->vp, P->y1, P->y2, R, s, P->st, P->vp32);
   // the mixed-precision iteration without templates keeps q, z and p in float32 (q and z
   // in the first half of their float64 buffers, p in vp32): q is a float32 operator's
   // output, z only builds the next direction, and p is the direction the operator is

@@ -116,6 +116,15 @@ hipError_t launch_wave_tables(int logn, bool fp64, void* tab, hipStream_t s);
 hipError_t launch_ols_wave(int logn, bool fp64, bool in_f64, const void* y_in, void* y_out, const OlsChunk* chunks,
                            int n_chunks, const void* spec, const void* tab, int64_t n_t, int n_c, int m, int n_rhs,
                            hipStream_t s, const CgState* st);
+// The same on the samples of a map: P, then the filter, in one launch
+struct SkyView {
+  const int32_t* idx = nullptr;   // [n_t] observed id of each sample, -1 = none
+  const float2* w = nullptr;      // [n_t] (sin, cos) (polarisation only)
+  int64_t vs = 0;                 // row stride of the map
+};
+hipError_t launch_ols_sky(int logn, bool fp64, bool map_f64, int ns, const void* map, const SkyView& sky, void* y_out,
+                          const OlsChunk* chunks, int n_chunks, const void* spec, const void* tab, int64_t n_t, int n_c,
+                          int m, int n_rhs, hipStream_t s, const CgState* st);
 
 // ---------------------------------------------------------------- pointing (k_pointing.hip)
 // y[r][t] = (P p_r)_t; p rows of stride vs (map values first, observed layout)
