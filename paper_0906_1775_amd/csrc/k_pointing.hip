@@ -78,16 +78,21 @@ __device__ __forceinline__ void gather_tile(const int32_t* __restrict__ pix_obs,
 // direction that mixed-precision iterations gather from); y rows have stride ys.
 // Requires n_obs >= 1 (pixel 0 exists).  Without `order` the blocks stride over
 // the tiles in time order; with it block b takes one tile, the tiles sorted by
-// the pixels they see: the hardware deals blocks to the 8 XCDs in turn, so block b
-// takes sorted position (b mod 8) * ceil(n_tiles / 8) + b / 8, and the blocks an
-// XCD runs at once read the map of one region of the sky through its L2.
+// the pixels they see, so that tiles that run at once look up the same part of the
+// map: dealt to the 8 XCDs in turn, or (eighths) each XCD a contiguous eighth of them,
+// b -> (b mod 8) * ceil(n_tiles / 8) + b / 8.  Eighths suit several rows of a map that is
+// swept along one axis (8 rows of 4096 x 768 pixels, a whole solve: 226 ms against
+// 233); else the lookups of one part of the map crowd one L2, and tiles are dealt
+// (2^27 samples of 1024 x 1024 pixels 499 us against 627, 2^26 of 1000 x 1000 251
+// against 313, where the streams alone take 365 and 180).
 template <typename Ty, int NS, typename Tp>
 __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ pix_obs,
                                                 const float2* __restrict__ w,
                                                 const Tp* __restrict__ p, int64_t vs,
                                                 Ty* __restrict__ y, int64_t n_t, int64_t ys, int n_rhs,
                                                 const CgState* __restrict__ st,
-                                                const int32_t* __restrict__ order, int64_t n_tiles) {
+                                                const int32_t* __restrict__ order, int64_t n_tiles,
+                                                bool eighths) {
   constexpr int U = kGatherUnroll;
   if (st) {   // every RHS has stopped: nothing to read
     bool any = false;
@@ -96,7 +101,7 @@ __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ pix_
   }
   if (order) {
     const int64_t per = (n_tiles + 7) / 8;
-    const int64_t pos = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+    const int64_t pos = eighths ? (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8 : blockIdx.x;
     if (pos >= n_tiles) return;
     gather_tile<Ty, NS, Tp>(pix_obs, w, p, vs, y, n_t, ys, n_rhs, st,
                             (int64_t)order[pos] * 256 * U + threadIdx.x);
@@ -110,7 +115,7 @@ __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ pix_
 hipError_t launch_gather(bool out_f64, int ns, const int32_t* pix_obs, const float* w,
                          const double* p, int64_t vs, void* y, int64_t n_t, int64_t n_obs, int n_rhs,
                          hipStream_t s, const CgState* st, const float* p32, int64_t vs32,
-                         const int32_t* order) {
+                         const int32_t* order, bool eighths) {
   if (n_t == 0) return hipSuccess;
   if (n_obs == 0)   // every sample excised: the TOD rows are zero (a fill kernel, safe under graph capture)
     return out_f64 ? launch_fill_f64((double*)y, 0.0, n_t * n_rhs, s)
@@ -122,7 +127,7 @@ hipError_t launch_gather(bool out_f64, int ns, const int32_t* pix_obs, const flo
   const dim3 g((unsigned)nb), b(256);
   const float2* w2 = (const float2*)w;
 #define MM_GA(TY, NS, TP, PP, VS) \
-  hipLaunchKernelGGL((k_gather<TY, NS, TP>), g, b, 0, s, pix_obs, w2, PP, VS, (TY*)y, n_t, n_t, n_rhs, st, order, n_tiles)
+  hipLaunchKernelGGL((k_gather<TY, NS, TP>), g, b, 0, s, pix_obs, w2, PP, VS, (TY*)y, n_t, n_t, n_rhs, st, order, n_tiles, eighths)
   if (p32) {
     if (out_f64) { if (ns == 1) MM_GA(double, 1, float, p32, vs32); else MM_GA(double, 3, float, p32, vs32); }
     else { if (ns == 1) MM_GA(float, 1, float, p32, vs32); else MM_GA(float, 3, float, p32, vs32); }
@@ -725,21 +730,28 @@ __global__ void k_to_observed(const double* __restrict__ glob, int64_t gs, doubl
   }
 }
 
+// observed id of pixel p, -1 if it has none (obs2glob is in raster order)
+__device__ __forceinline__ int64_t observed_id(const int32_t* __restrict__ obs2glob, int64_t n_obs, uint32_t p,
+                                               Raster raster) {
+  const uint32_t key = raster_key(raster, p);
+  int64_t lo = 0, hi = n_obs;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (raster_key(raster, (uint32_t)obs2glob[mid]) < key) lo = mid + 1; else hi = mid;
+  }
+  return lo < n_obs && (uint32_t)obs2glob[lo] == p ? lo : -1;
+}
+
 // global map = observed values at observed pixels, 0 elsewhere (one pass over the global map)
 __global__ void k_to_global(const double* __restrict__ obs, int64_t os, double* __restrict__ glob, int64_t gs,
                             const int32_t* __restrict__ obs2glob, int64_t n_obs, int64_t n_pix,
-                            int ns, int n_rhs) {
+                            int ns, int n_rhs, Raster raster) {
   const int64_t n = n_pix * n_rhs;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const int64_t r = i / n_pix, gp = i % n_pix;
-    // binary search of gp in the sorted obs2glob
-    int64_t lo = 0, hi = n_obs;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (obs2glob[mid] < gp) lo = mid + 1; else hi = mid;
-    }
-    const bool seen = lo < n_obs && obs2glob[lo] == gp;
+    const int64_t lo = observed_id(obs2glob, n_obs, (uint32_t)gp, raster);
+    const bool seen = lo >= 0;
     for (int c = 0; c < ns; ++c)
       glob[r * gs + gp * ns + c] = seen ? obs[r * os + lo * ns + c] : 0.0;
   }
@@ -758,31 +770,27 @@ hipError_t launch_to_observed(const double* glob, int64_t glob_stride, double* o
 
 hipError_t launch_to_global(const double* obs, int64_t obs_stride, double* glob, int64_t glob_stride,
                             const int32_t* obs2glob, int64_t n_obs, int64_t n_pix, int ns, int n_rhs,
-                            hipStream_t s) {
+                            hipStream_t s, const Raster& raster) {
   const int64_t n = n_pix * n_rhs;
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_to_global, grid_for(n), dim3(256), 0, s, obs, obs_stride, glob, glob_stride, obs2glob,
-                     n_obs, n_pix, ns, n_rhs);
+                     n_obs, n_pix, ns, n_rhs, raster);
   return hipGetLastError();
 }
 
 __global__ void k_hits(const int64_t* __restrict__ pix_ptr, const int32_t* __restrict__ obs2glob,
-                       int32_t* __restrict__ hits, int64_t n_obs, int64_t n_pix) {
+                       int32_t* __restrict__ hits, int64_t n_obs, int64_t n_pix, Raster raster) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_pix; i += stride) {
-    int64_t lo = 0, hi = n_obs;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (obs2glob[mid] < i) lo = mid + 1; else hi = mid;
-    }
-    hits[i] = (lo < n_obs && obs2glob[lo] == i) ? (int32_t)(pix_ptr[lo + 1] - pix_ptr[lo]) : 0;
+    const int64_t o = observed_id(obs2glob, n_obs, (uint32_t)i, raster);
+    hits[i] = o >= 0 ? (int32_t)(pix_ptr[o + 1] - pix_ptr[o]) : 0;
   }
 }
 
 hipError_t launch_hits(const int64_t* pix_ptr, const int32_t* obs2glob, int32_t* hits,
-                       int64_t n_obs, int64_t n_pix, hipStream_t s) {
+                       int64_t n_obs, int64_t n_pix, hipStream_t s, const Raster& raster) {
   if (n_pix == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_hits, grid_for(n_pix), dim3(256), 0, s, pix_ptr, obs2glob, hits, n_obs, n_pix);
+  hipLaunchKernelGGL(k_hits, grid_for(n_pix), dim3(256), 0, s, pix_ptr, obs2glob, hits, n_obs, n_pix, raster);
   return hipGetLastError();
 }
 

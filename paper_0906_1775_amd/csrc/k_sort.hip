@@ -51,6 +51,52 @@ hipError_t launch_check_pix(const int32_t* pix, int64_t n, int64_t n_pix, int32_
   return hipGetLastError();
 }
 
+// One workgroup, a sample a thread, spread over the TOD: the distances to the next other pixel
+// among the 16 samples that follow meet in LDS, every thread counts the equals of its own, and
+// the most frequent one wins, the smaller of equals.
+constexpr int kSteps = 1024, kStepLook = 16;
+__global__ __launch_bounds__(kSteps) void k_raster_step(const int32_t* __restrict__ pix, int64_t n,
+                                                        int32_t* __restrict__ step) {
+  __shared__ __align__(16) int32_t d[kSteps];
+  __shared__ unsigned long long best;
+  __shared__ int n_steps;
+  const int tid = threadIdx.x;
+  if (tid == 0) best = 0, n_steps = 0;
+  const int64_t t = (int64_t)((double)tid * (double)n / kSteps);
+  int32_t q[kStepLook + 1];
+#pragma unroll
+  for (int k = 0; k <= kStepLook; ++k) q[k] = pix[t + k < n ? t + k : n - 1];
+  int32_t v = 0;
+  bool on = q[0] >= 0;
+#pragma unroll
+  for (int k = 1; k <= kStepLook; ++k) {
+    on = on && v == 0 && q[k] >= 0;
+    if (on) v = q[k] > q[0] ? q[k] - q[0] : q[0] - q[k];
+  }
+  d[tid] = v;
+  __syncthreads();
+  if (v) atomicAdd(&n_steps, 1);
+  int c = 0;
+#pragma unroll 8
+  for (int k = 0; k < kSteps; k += 4) {
+    const int4 x = *reinterpret_cast<const int4*>(d + k);
+    c += (x.x == v) + (x.y == v) + (x.z == v) + (x.w == v);
+  }
+  if (v > 1) atomicMax(&best, (unsigned long long)c << 32 | (unsigned)(0x7fffffff - v));
+  __syncthreads();
+  if (tid == 0) {
+    step[0] = best ? 0x7fffffff - (int32_t)(best & 0xffffffffu) : 0;
+    step[1] = (int32_t)(best >> 32);
+    step[2] = n_steps;
+  }
+}
+
+hipError_t launch_raster_step(const int32_t* pix, int64_t n, int32_t* step, hipStream_t s) {
+  if (n < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_raster_step, dim3(1), dim3(kSteps), 0, s, pix, n, step);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- scan (uint32)
 // block scan of 4096 items; writes per-block totals
 __global__ __launch_bounds__(kScanThreads) void k_scan_block(const uint32_t* __restrict__ in,
@@ -216,12 +262,13 @@ hipError_t launch_segment_scan(const uint32_t* keys, int64_t n, uint32_t n_pix, 
 }
 
 // ---------------------------------------------------------------- radix sort
-__global__ void k_sort_init(const int32_t* __restrict__ pix, int64_t n, uint32_t n_pix,
+// (an index outside the range keeps its value: in bounds, and the plan fails before its use)
+__global__ void k_sort_init(const int32_t* __restrict__ pix, int64_t n, uint32_t n_keys, Raster raster,
                             uint32_t* __restrict__ keys, int32_t* __restrict__ vals) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const int32_t p = pix[i];
-    keys[i] = p >= 0 ? (uint32_t)p : n_pix;
+    keys[i] = p < 0 ? n_keys : (uint32_t)p < n_keys ? raster_key(raster, (uint32_t)p) : (uint32_t)p;
     vals[i] = (int32_t)i;
   }
 }
@@ -389,7 +436,7 @@ size_t sort_scratch_bytes(int64_t n) {
 }
 
 hipError_t launch_sort_by_pixel(const int32_t* pix, int64_t n, int64_t n_pix, uint32_t* keys_out,
-                                int32_t* vals_out, void* scratch, hipStream_t s) {
+                                int32_t* vals_out, void* scratch, hipStream_t s, const Raster& raster) {
   if (n == 0) return hipSuccess;
   const int64_t n_tiles = (n + kSortTile - 1) / kSortTile;
   char* p = (char*)scratch;
@@ -412,7 +459,7 @@ hipError_t launch_sort_by_pixel(const int32_t* pix, int64_t n, int64_t n_pix, ui
   const int dbits = (passes > 1 && passes <= 3 && (passes - 1) * kSortMaxBits >= bits) ? kSortMaxBits : 8;
   if (dbits == kSortMaxBits) passes -= 1;
 
-  hipLaunchKernelGGL(k_sort_init, grid_for(n), dim3(256), 0, s, pix, n, (uint32_t)n_pix, ka, va);
+  hipLaunchKernelGGL(k_sort_init, grid_for(n), dim3(256), 0, s, pix, n, (uint32_t)n_pix, raster, ka, va);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   uint32_t *kin = ka, *kout = kb;
@@ -450,7 +497,7 @@ __global__ void k_build_layout(const uint32_t* __restrict__ keys, const int32_t*
                                const uint32_t* __restrict__ seg_id, int64_t n, uint32_t n_pix,
                                const float2* __restrict__ w, int ns, int64_t* __restrict__ pix_ptr,
                                int32_t* __restrict__ obs2glob, float2* __restrict__ w_pm,
-                               int32_t* __restrict__ perm) {
+                               int32_t* __restrict__ perm, Raster raster) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const uint32_t k = keys[i];
@@ -459,7 +506,7 @@ __global__ void k_build_layout(const uint32_t* __restrict__ keys, const int32_t*
       const int32_t o = (int32_t)seg_id[i] - 1;
       if (i == 0 || keys[i - 1] != k) {
         pix_ptr[o] = i;
-        obs2glob[o] = (int32_t)k;
+        obs2glob[o] = (int32_t)raster_pixel(raster, k);
       }
       perm[i] = v;
       if (ns == 3) w_pm[i] = w[v];
@@ -499,10 +546,11 @@ hipError_t launch_obs_index(const int32_t* key, int64_t n, const int32_t* obs2gl
 
 hipError_t launch_build_layout(const uint32_t* keys, const int32_t* vals, const uint32_t* seg_id,
                                int64_t n, uint32_t n_pix, const float* w, int ns, int64_t* pix_ptr,
-                               int32_t* obs2glob, float* w_pm, int32_t* perm, hipStream_t s) {
+                               int32_t* obs2glob, float* w_pm, int32_t* perm, hipStream_t s,
+                               const Raster& raster) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_build_layout, grid_for(n), dim3(256), 0, s, keys, vals, seg_id, n, n_pix,
-                     (const float2*)w, ns, pix_ptr, obs2glob, (float2*)w_pm, perm);
+                     (const float2*)w, ns, pix_ptr, obs2glob, (float2*)w_pm, perm, raster);
   return hipGetLastError();
 }
 

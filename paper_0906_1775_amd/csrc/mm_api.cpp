@@ -180,7 +180,8 @@ struct Layout {
   int64_t n_obs = 0, n_valid = 0;
   int32_t* obs_idx = nullptr;    // [n_t] observed id of each sample, -1 = none (time-major)
   int64_t* ptr = nullptr;        // [n_obs + 1] CSR offsets of the pixel-major order
-  int32_t* obs2glob = nullptr;   // [n_obs] global id of each observed id (sorted)
+  int32_t* obs2glob = nullptr;   // [n_obs] global id of each observed id (in raster order)
+  Raster raster;
   int32_t* perm = nullptr;       // [n_valid] sample ids, pixel-major (released once sliced)
   float* w_pm = nullptr;         // [n_valid][2] (sin, cos), pixel-major (released once sliced)
   int group = 8;                 // lanes per pixel in the plan-time preconditioner build
@@ -696,7 +697,7 @@ void gather_all(mm_plan_s* P, bool y_f64, const double* x, void* y, int R, hipSt
                 const CgState* st = nullptr, const float* x32 = nullptr) {
   const int64_t vs = P->nu();
   hipchk(launch_gather(y_f64, P->ns, P->px.obs_idx, P->w, x, vs, y, P->n_t, P->n_obs, R, s, st, x32, P->vs32(),
-                       P->gather_order),
+                       P->gather_order, R > 1 && P->px.raster.w == 0),
          "gather");
   for (const Template& T : P->tmpl) {
     const int64_t off = P->nmap() + T.ooff;
@@ -786,7 +787,9 @@ void to_obs(mm_plan_s* P, const double* glob, double* obs, int R, hipStream_t s)
 }
 
 void to_glob(mm_plan_s* P, const double* obs, double* glob, int R, hipStream_t s) {
-  hipchk(launch_to_global(obs, P->nu(), glob, P->ng(), P->px.obs2glob, P->n_obs, P->n_pix, P->ns, R, s), "layout");
+  hipchk(launch_to_global(obs, P->nu(), glob, P->ng(), P->px.obs2glob, P->n_obs, P->n_pix, P->ns, R, s,
+                          P->px.raster),
+         "layout");
   for (const Template& T : P->tmpl) {
     double* g = glob + P->n_pix * P->ns + T.goff;
     const double* o = obs + P->nmap() + T.ooff;
@@ -834,9 +837,13 @@ constexpr int64_t kSegTodBytes = int64_t(256) << 20;
 // - beyond, the slices fill the chip by themselves and more wavefronts only pay for long rows
 //   (3 M x 20: 305 with 1, 338 with 4; 2^20 x 200: 1163, 1003 and 1042 with 1, 4 and 8);
 // - with 1024 hits pixel-major whatever the TOD, 64 lanes or more on a pixel's hits (1024 columns
-//   of 4096 neighbouring samples: 170 sliced, 27 with 64 lanes, 11 with 512).
-int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid) {
+//   of 4096 neighbouring samples: 170 sliced, 27 with 64 lanes, 11 with 512);
+// - with the pixels by tiles of a raster a slice shares TOD lines as no run of hits does, so
+//   pixel-major is left to the maps that are too small for slices (157 x 157 of 256, 3 float64
+//   rows: 70 pixel-major, 66 sliced; 256 x 256 of 256 72 and 68; 400 x 400 195 and 156).
+int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid, bool tiles) {
   const double avg = n_obs > 0 ? (double)n_valid / (double)n_obs : 1.0;
+  if (tiles && n_obs > (1 << 14)) return n_obs <= (1 << 18) ? 8 : avg >= 96 ? 4 : avg >= 48 ? 2 : 1;
   if (avg >= 1024) return 0;
   if (n_obs <= (1 << 18)) return avg >= 128 && n_t * (fp64 ? 8 : 4) * std::min(R, 4) <= kSegTodBytes ? 0 : 8;
   return avg >= 96 ? 4 : avg >= 48 ? 2 : 1;
@@ -851,7 +858,11 @@ int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid) 
 // two apart, meet in a few channels of its L2 (256 x 256 of 256 hits, 8 RHS 762 -> 1393;
 // 1024 x 1024 1267 -> 1927).  Past 2^18 pixels one float32 row gains nothing (1000 x 1000 of
 // 256: 1503 -> 1605).
-int scatter_run(int64_t n_keys, int64_t n_obs, bool fp64, int R) {
+// With the pixels by tiles of a raster (run 0 / 16): eighths up to 2^17 pixels, where runs of 16
+// blocks leave XCDs idle (157 x 157: 28 / 31), beyond them runs of 16 (500 x 500 of 256, 2 float64
+// rows 501 / 461; 1000 x 1000 of 256 939 / 860).
+int scatter_run(const Raster& raster, int64_t n_keys, int64_t n_obs, bool fp64, int R) {
+  if (raster.w) return n_obs <= (1 << 17) ? 0 : 16;
   if ((n_keys & ((1 << 14) - 1)) == 0) return 1;
   return n_obs <= (1 << 18) || R * (fp64 ? 8 : 4) >= 16 ? 0 : 1;
 }
@@ -861,11 +872,42 @@ int scatter_run(int64_t n_keys, int64_t n_obs, bool fp64, int R) {
 // pixel-major arrays for the scatter.  Bounds the workspace from the descriptor alone.
 int64_t sliced_allowance(int64_t n_valid) { return (2 * n_valid / 64 + 1) * 64; }
 
+// sort keys of n_pix pixels in raster order (whole 8 x 8 tiles)
+int64_t raster_keys(const Raster& r, int64_t n_pix) {
+  if (r.w == 0) return n_pix;
+  const int64_t rows = (n_pix + r.w - 1) / r.w;
+  return 64 * (int64_t)r.wt * ((rows + 7) / 8);
+}
+
+// Raster of the sky, read off the TOD: a map scanned along both axes steps by its row length w
+// as a detector crosses rows.  Taken where an eighth of the steps agree on one w of at least 16
+// with 16 rows or more, and whole tiles add at most a quarter to the keys; else the pixels
+// keep their own order.  By tiles / by rows, us per iteration: 1024 x 1024 pixels of 256 hits,
+// float32 polarisation 2283 / 2768 (its scatter 923 / 1371), 700 x 700 of 60, 3 float64
+// rows 832 / 1034, 512 x 512 of 60, 8 float32 rows 1096 / 1308, 256 x 256 of 60 87 / 96.
+Raster find_raster(mm_plan_s* P, const int32_t* d_pix, hipStream_t s) {
+  Raster r;
+  if (P->n_t < 4096 || P->n_pix < 1024) return r;
+  int32_t* step = P->temp<int32_t>(3);
+  hipchk(launch_raster_step(d_pix, P->n_t, step, s), "raster step");
+  int32_t* h = P->slot<int32_t>(kPinFlag);   // (slots of 8 bytes: the step's three words span two)
+  hipchk(hipMemcpyAsync(h, step, 12, hipMemcpyDeviceToHost, s), "copy");
+  hipchk(hipStreamSynchronize(s), "raster step");
+  P->release(step);
+  const int64_t w = h[0];
+  if (w < 16 || P->n_pix / w < 16 || h[1] < 8 || (int64_t)h[1] * 8 < h[2]) return r;
+  r.w = (uint32_t)w;
+  r.wt = (uint32_t)((w + 7) / 8);
+  if (raster_keys(r, P->n_pix) > std::min<int64_t>(P->n_pix + P->n_pix / 4, 0x7fffffff)) return Raster{};
+  return r;
+}
+
 // Pixel-major layout of a pointing with one non-zero per row: range check,
 // stable sort of the samples by key, observed compaction (Implementation
 // section, observed index scheme).  Keys lie in [-1, n_keys); -1 = no column.
 // The pixel-major sample ids and weights are temporaries when the scatter will
-// read a sliced copy of them (build_sell), else they are kept.
+// read a sliced copy of them (build_sell), else they are kept.  The observed ids follow
+// L.raster.
 void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, const float* d_w, Layout& L,
                   hipStream_t s, const char* range_msg) {
   const int64_t n = P->n_t;
@@ -886,13 +928,14 @@ void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, co
     char* scratch = P->temp<char>((int64_t)sort_scratch_bytes(n));
     uint32_t* keys = P->temp<uint32_t>(n);
     int32_t* vals = P->temp<int32_t>(n);
-    hipchk(launch_sort_by_pixel(d_key, n, n_keys, keys, vals, scratch, s), "sort by pixel");
+    const int64_t n_sort = raster_keys(L.raster, n_keys);
+    hipchk(launch_sort_by_pixel(d_key, n, n_sort, keys, vals, scratch, s, L.raster), "sort by pixel");
     P->release(scratch);
     uint32_t* seg = P->temp<uint32_t>(n);
     char* sscr = P->temp<char>((int64_t)scan_scratch_bytes(n));
     int64_t* nvalid_d = P->temp<int64_t>(1);
     hipchk(hipMemsetAsync(nvalid_d, 0, sizeof(int64_t), s), "memset");
-    hipchk(launch_segment_scan(keys, n, (uint32_t)n_keys, seg, nvalid_d, sscr, s), "observed ids");
+    hipchk(launch_segment_scan(keys, n, (uint32_t)n_sort, seg, nvalid_d, sscr, s), "observed ids");
     hipchk(hipMemcpyAsync(P->slot<int32_t>(kPinFlag), flag, 4, hipMemcpyDeviceToHost, s), "index check copy");
     hipchk(hipMemcpyAsync(P->slot<uint32_t>(kPinObs), seg + (n - 1), 4, hipMemcpyDeviceToHost, s), "copy");
     hipchk(hipMemcpyAsync(P->slot<int64_t>(kPinValid), nvalid_d, 8, hipMemcpyDeviceToHost, s), "copy");
@@ -900,8 +943,8 @@ void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, co
     if (*P->slot<int32_t>(kPinFlag)) fail(MM_EINVAL, range_msg);
     L.n_obs = *P->slot<uint32_t>(kPinObs);
     L.n_valid = *P->slot<int64_t>(kPinValid);
-    L.wps = layout_waves(n, P->main_fp64(), P->R, L.n_obs, L.n_valid);
-    L.sell.run = scatter_run(n_keys, L.n_obs, P->main_fp64(), P->R);
+    L.wps = layout_waves(n, P->main_fp64(), P->R, L.n_obs, L.n_valid, L.raster.w != 0);
+    L.sell.run = scatter_run(L.raster, n_keys, L.n_obs, P->main_fp64(), P->R);
     L.ptr = P->alloc<int64_t>(L.n_obs + 1);
     L.obs2glob = P->alloc<int32_t>(L.n_obs);
     if (L.wps > 0) {
@@ -911,7 +954,8 @@ void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, co
       L.perm = P->alloc<int32_t>(L.n_valid);
       if (ns == 3) L.w_pm = P->alloc<float>(2 * L.n_valid);
     }
-    hipchk(launch_build_layout(keys, vals, seg, n, (uint32_t)n_keys, d_w, ns, L.ptr, L.obs2glob, L.w_pm, L.perm, s),
+    hipchk(launch_build_layout(keys, vals, seg, n, (uint32_t)n_sort, d_w, ns, L.ptr, L.obs2glob, L.w_pm, L.perm, s,
+                               L.raster),
            "pointing layout");
     int32_t* glob2obs = P->temp<int32_t>(n_keys);
     hipchk(launch_obs_index(d_key, n, L.obs2glob, L.n_obs, glob2obs, n_keys, L.obs_idx, s), "observed index");
@@ -939,7 +983,7 @@ void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, co
 // Map bytes one gather pass looks up (all RHS) above which the gather visits its tiles
 // sorted by pixel rather than in time order: beyond one XCD's 4 MiB L2, the pixels a
 // scan revisits (other detectors, later passes) are gone from the caches by then in
-// time order, while sorted tiles that see the same pixels run together on one XCD.
+// time order, while sorted tiles that see the same pixels run together.
 constexpr int64_t kGatherOrderMapBytes = int64_t(4) << 20;
 
 // Gather order: the gather tiles sorted (stably) by the smallest observed id each sees.
@@ -1250,7 +1294,7 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
     const int64_t n_obs = std::min<int64_t>(n_keys, n);
     *n_obs_out = n_obs;
     B.pers += block_bytes(n, 4);
-    B.temps += block_bytes(1, 4);
+    B.temps += block_bytes(1, 4) + block_bytes(3, 4);
     if (n == 0) {
       B.pers += block_bytes(1, 8) + 2 * block_bytes(1, 4);
       return;
@@ -1417,6 +1461,7 @@ void build_plan(mm_plan_s* P, const mm_desc_t* d, const int32_t* d_pix, const fl
 
   const int64_t n = P->n_t;
   // ---- pointing: range check, sort by pixel, observed layout
+  P->px.raster = find_raster(P, d_pix, s);
   build_layout(P, d_pix, P->n_pix, P->ns, d_w, P->px, s, "pointing index outside [-1, n_pix)");
   P->n_obs = P->px.n_obs;
   P->n_valid = P->px.n_valid;
@@ -2280,7 +2325,7 @@ mm_status_t mm_hits(mm_plan_t P, int32_t* d_hits, void* stream) {
     if (!P || !d_hits) fail(MM_EINVAL, "NULL argument");
     hipStream_t s = as_stream(stream);
     wait_ready(P, s);
-    hipchk(launch_hits(P->px.ptr, P->px.obs2glob, d_hits, P->n_obs, P->n_pix, s), "hits");
+    hipchk(launch_hits(P->px.ptr, P->px.obs2glob, d_hits, P->n_obs, P->n_pix, s, P->px.raster), "hits");
   });
 }
 

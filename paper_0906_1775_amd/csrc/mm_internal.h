@@ -2,6 +2,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include "raster.hpp"
 #include <stdint.h>
 
 namespace mm {
@@ -134,7 +136,7 @@ hipError_t launch_ols_sky(int logn, bool fp64, bool map_f64, int ns, const void*
 hipError_t launch_gather(bool out_f64, int ns, const int32_t* pix_obs, const float* w,
                          const double* p, int64_t vs, void* y, int64_t n_t, int64_t n_obs, int n_rhs,
                          hipStream_t s, const CgState* st = nullptr, const float* p32 = nullptr,
-                         int64_t vs32 = 0, const int32_t* order = nullptr);
+                         int64_t vs32 = 0, const int32_t* order = nullptr, bool eighths = false);
 // runs of consecutive samples the gather assigns to one block
 int64_t gather_tiles(int64_t n_t);
 // key[i] = smallest observed id among the samples of gather tile i, -1 if none
@@ -183,21 +185,25 @@ hipError_t launch_to_observed(const double* glob, int64_t glob_stride, double* o
                               hipStream_t s);
 hipError_t launch_to_global(const double* obs, int64_t obs_stride, double* glob, int64_t glob_stride,
                             const int32_t* obs2glob, int64_t n_obs, int64_t n_pix, int ns, int n_rhs,
-                            hipStream_t s);
+                            hipStream_t s, const Raster& raster = {});
 hipError_t launch_hits(const int64_t* pix_ptr, const int32_t* obs2glob, int32_t* hits,
-                       int64_t n_obs, int64_t n_pix, hipStream_t s);
+                       int64_t n_obs, int64_t n_pix, hipStream_t s, const Raster& raster = {});
 hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
 // ---------------------------------------------------------------- plan (k_sort.hip)
 // flag[0] = 1 if any pix is < -1 or >= n_pix
+// step[0] = the most frequent distance beyond 1 between a sample's pixel and the next other one
+// (0: none), step[1] = how often it occurs, step[2] = how many distances, of samples spread over the TOD
+hipError_t launch_raster_step(const int32_t* pix, int64_t n, int32_t* step, hipStream_t s);
 hipError_t launch_check_pix(const int32_t* pix, int64_t n, int64_t n_pix, int32_t* flag,
                             hipStream_t s);
 size_t sort_scratch_bytes(int64_t n);
 // Stable sort of sample ids by pixel; excised samples (pix = -1) go last.
 // keys_out[i] = pixel of the i-th sample in pixel-major order, vals_out[i] = its sample id.
 hipError_t launch_sort_by_pixel(const int32_t* pix, int64_t n, int64_t n_pix, uint32_t* keys_out,
-                                int32_t* vals_out, void* scratch, hipStream_t s);
+                                int32_t* vals_out, void* scratch, hipStream_t s,
+                                const Raster& raster = {});
 size_t scan_scratch_bytes(int64_t n);
 // inclusive scan of uint32 values
 hipError_t launch_scan_inclusive(const uint32_t* in, uint32_t* out, int64_t n, void* scratch,
@@ -211,7 +217,8 @@ hipError_t launch_segment_scan(const uint32_t* keys, int64_t n, uint32_t n_pix, 
 // pix_ptr, obs2glob, w_pm, perm from the sorted order
 hipError_t launch_build_layout(const uint32_t* keys, const int32_t* vals, const uint32_t* seg_id,
                                int64_t n, uint32_t n_pix, const float* w, int ns, int64_t* pix_ptr,
-                               int32_t* obs2glob, float* w_pm, int32_t* perm, hipStream_t s);
+                               int32_t* obs2glob, float* w_pm, int32_t* perm, hipStream_t s,
+                               const Raster& raster);
 // time-major observed index pix_obs[t] (-1 for excised samples) through the inverse map
 // glob2obs [n_keys] (scratch) of obs2glob; the keys must be in [-1, n_keys)
 hipError_t launch_obs_index(const int32_t* key, int64_t n, const int32_t* obs2glob, int64_t n_obs,
