@@ -511,20 +511,24 @@ int compute_units() {
 // for 16,384 at 2^15)
 constexpr double kWave15Cost = 2.25;
 
-// Filter pass over c chunks with transforms of 2^logn points, in us: about
-// kOlsLatency + c * kOlsChunkNs / 1000, the time of one chunk alone and its share of a full
-// chip (measured per length: one-interval TODs of 65,536 samples, and 2^24 to 2^26 samples
-// at n_c = 64 and 8192; 2^6 .. 2^9 points are the workgroup transforms).  A TOD of a few
-// windows is done in one latency of the shortest ones, a long one at the rate that its halo
-// 2 n_c leaves.
-struct OlsCost {
-  double latency_us, chunk_ns;
-};
-constexpr OlsCost kOlsCost[2][10] = {
-    // float32: 2^6 .. 2^15 points
-    {{5.0, 0.5}, {5.0, 0.7}, {5.0, 0.95}, {5.0, 2.1}, {4.5, 3.3}, {4.5, 7.5}, {5.0, 15.6}, {5.5, 31.0}, {9.0, 65.0}, {20.0, 140.0}},
-    // float64: 2^6 .. 2^14 points
-    {{5.5, 0.8}, {5.5, 1.2}, {6.0, 1.9}, {6.5, 4.7}, {5.0, 6.0}, {6.0, 13.7}, {8.0, 30.0}, {12.5, 59.0}, {21.0, 130.0}, {0.0, 0.0}}};
+// Predicted time of a filter pass over c chunks with transforms of 2^logn points, in us, for the
+// comparison of lengths.  A wavefront-private transform fills the chip with 16 >> (logn - 10)
+// workgroups per compute unit (one at least): whole rounds take full_us each, a last one between
+// alone_us, one chunk by itself, and that.  The workgroup transforms of 2^6 .. 2^9 points take
+// chunk_ns per chunk.  Measured over n_c = 32 .. 3000 and 9,000 to 5 10^7 samples, where the
+// length it picks is at most a tenth slower than the best one.
+double ols_time_us(bool fp64, int logn, double c) {
+  constexpr double kLaunch = 5.0;
+  constexpr double chunk_ns[2][4] = {{0.5, 0.7, 0.95, 2.1}, {0.8, 1.2, 1.9, 4.7}};
+  constexpr double alone_us[2][6] = {{2.5, 2.5, 2.7, 4.4, 8.0, 20.0}, {2.6, 2.6, 5.0, 10.0, 20.0, 0.0}};
+  constexpr double full_us[2][6] = {{13.0, 14.2, 14.7, 16.0, 22.0, 43.0}, {22.5, 25.0, 25.0, 31.0, 42.0, 0.0}};
+  const int p = fp64 ? 1 : 0;
+  if (logn < 10) return kLaunch + 1e-3 * chunk_ns[p][logn - kMinLogN] * c;
+  const int i = logn - 10;
+  const double slots = (double)compute_units() * std::max(1, 16 >> i), rounds = std::floor(c / slots);
+  const double last = c / slots - rounds;
+  return kLaunch + rounds * full_us[p][i] + (last > 0 ? alone_us[p][i] + last * (full_us[p][i] - alone_us[p][i]) : 0.0);
+}
 
 // n_f of a filter set-up that is not autotuned (secondary: the float64 filter of a
 // mixed plan, which takes a forced n_f only when it has a float64 transform): the on-chip
@@ -552,9 +556,7 @@ int64_t choose_nf(int nf_req, int n_c, const std::vector<int64_t>& iv_start, int
   double best_us = 0.0;
   for (int64_t nf = lo; ilog2(nf) - 1 <= maxlog; nf <<= 1) {
     if (shape_req > 0 && !transform_exists(ilog2(nf) - 1, fp64, shape_req - 1)) continue;
-    const OlsCost& c = kOlsCost[fp64 ? 1 : 0][ilog2(nf) - 1 - kMinLogN];
-    const double us = c.latency_us + 1e-3 * c.chunk_ns * std::max(R, 1) *
-                                         (double)count_chunks(iv_start, nf - 2 * (int64_t)n_c);
+    const double us = ols_time_us(fp64, ilog2(nf) - 1, (double)count_chunks(iv_start, nf - 2 * (int64_t)n_c) * std::max(R, 1));
     if (best == 0 || us < best_us) {
       best = nf;
       best_us = us;
