@@ -719,17 +719,6 @@ hipError_t launch_convert(bool in_f64, bool out_f64, const void* in, void* out, 
   return hipGetLastError();
 }
 
-__global__ void k_to_observed(const double* __restrict__ glob, int64_t gs, double* __restrict__ obs, int64_t os,
-                              const int32_t* __restrict__ obs2glob, int64_t n_obs, int ns, int n_rhs) {
-  const int64_t per = n_obs * ns;
-  const int64_t n = per * n_rhs;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const int64_t r = i / per, rem = i % per, o = rem / ns, c = rem % ns;
-    obs[r * os + rem] = glob[r * gs + (int64_t)obs2glob[o] * ns + c];
-  }
-}
-
 // observed id of pixel p, -1 if it has none (obs2glob is in raster order)
 __device__ __forceinline__ int64_t observed_id(const int32_t* __restrict__ obs2glob, int64_t n_obs, uint32_t p,
                                                Raster raster) {
@@ -742,41 +731,129 @@ __device__ __forceinline__ int64_t observed_id(const int32_t* __restrict__ obs2g
   return lo < n_obs && (uint32_t)obs2glob[lo] == p ? lo : -1;
 }
 
-// global map = observed values at observed pixels, 0 elsewhere (one pass over the global map)
-__global__ void k_to_global(const double* __restrict__ obs, int64_t os, double* __restrict__ glob, int64_t gs,
-                            const int32_t* __restrict__ obs2glob, int64_t n_obs, int64_t n_pix,
-                            int ns, int n_rhs, Raster raster) {
-  const int64_t n = n_pix * n_rhs;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const int64_t r = i / n_pix, gp = i % n_pix;
-    const int64_t lo = observed_id(obs2glob, n_obs, (uint32_t)gp, raster);
-    const bool seen = lo >= 0;
-    for (int c = 0; c < ns; ++c)
-      glob[r * gs + gp * ns + c] = seen ? obs[r * os + lo * ns + c] : 0.0;
+// Copies between the rows of API buffers (global ids) and of iteration vectors (observed ids), all
+// parts of a row in one launch: blockIdx.x counts the blocks of part 0, then part 1, ..; row
+// blockIdx.y.  (Bound by their launches on small problems: six of them took 24 of the 167 us of an
+// operator with two template blocks on 2^22 samples.)  The parts travel as kernel arguments, no
+// more of them than there are: 17 (a kilobyte) cost a launch 0.7 us more than one.
+template <int N> struct PartsArg {
+  int n;
+  LayoutPart part[N];
+  __device__ __forceinline__ const LayoutPart& mine() const {
+    int k = 0;
+    if constexpr (N > 1)
+      while (k + 1 < n && (int)blockIdx.x >= part[k + 1].block0) ++k;
+    return part[k];
   }
+};
+template <int N> static PartsArg<N> parts_arg(const LayoutParts& P) {
+  PartsArg<N> a;
+  a.n = P.n;
+  for (int k = 0; k < N && k < P.n; ++k) a.part[k] = P.part[k];
+  return a;
 }
 
-hipError_t launch_to_observed(const double* glob, int64_t glob_stride, double* obs, int64_t obs_stride,
-                              const int32_t* obs2glob, int64_t n_obs, int64_t n_pix, int ns, int n_rhs,
+template <int N>
+__global__ __launch_bounds__(256) void k_to_observed(PartsArg<N> P, const double* __restrict__ glob, int64_t gs,
+                                                     double* __restrict__ obs, int64_t os) {
+  const LayoutPart L = P.mine();
+  const int64_t o = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  if (o >= L.n_obs) return;
+  const int64_t g = L.identity ? o : L.obs2glob[o];
+  const double* __restrict__ src = glob + (int64_t)blockIdx.y * gs + L.goff + g * L.ns;
+  double* __restrict__ dst = obs + (int64_t)blockIdx.y * os + L.ooff + o * L.ns;
+  for (int c = 0; c < L.ns; ++c) dst[c] = src[c];
+}
+
+// global row = observed values at observed ids, 0 elsewhere, by a search per global id
+template <int N>
+__global__ __launch_bounds__(256) void k_to_global(PartsArg<N> P, const double* __restrict__ obs, int64_t os,
+                                                   double* __restrict__ glob, int64_t gs) {
+  const LayoutPart L = P.mine();
+  const int64_t g = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  if (g >= L.n_glob) return;
+  const int64_t o = L.identity ? g : observed_id(L.obs2glob, L.n_obs, (uint32_t)g, L.raster);
+  const double* __restrict__ src = obs + (int64_t)blockIdx.y * os + L.ooff + o * L.ns;
+  double* __restrict__ dst = glob + (int64_t)blockIdx.y * gs + L.goff + g * L.ns;
+  for (int c = 0; c < L.ns; ++c) dst[c] = o >= 0 ? src[c] : 0.0;
+}
+
+// the observed values to their global ids, and nothing elsewhere
+template <int N>
+__global__ __launch_bounds__(256) void k_put_global(PartsArg<N> P, const double* __restrict__ obs, int64_t os,
+                                                    double* __restrict__ glob, int64_t gs) {
+  const LayoutPart L = P.mine();
+  const int64_t o = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  if (o >= L.n_obs) return;
+  const int64_t g = L.identity ? o : L.obs2glob[o];
+  const double* __restrict__ src = obs + (int64_t)blockIdx.y * os + L.ooff + o * L.ns;
+  double* __restrict__ dst = glob + (int64_t)blockIdx.y * gs + L.goff + g * L.ns;
+  for (int c = 0; c < L.ns; ++c) dst[c] = src[c];
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void k_zero_global(PartsArg<N> P, double* __restrict__ glob, int64_t gs) {
+  const LayoutPart L = P.mine();
+  const int64_t g = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  if (g >= L.n_glob) return;
+  double* __restrict__ dst = glob + (int64_t)blockIdx.y * gs + L.goff + g * L.ns;
+  for (int c = 0; c < L.ns; ++c) dst[c] = 0.0;
+}
+
+// blocks of 256 ids per part; the total
+static int64_t layout_blocks(LayoutParts& P, bool global) {
+  int64_t nb = 0;
+  for (int k = 0; k < P.n; ++k) {
+    P.part[k].block0 = (int)nb;
+    nb += ((global ? P.part[k].n_glob : P.part[k].n_obs) + 255) / 256;
+  }
+  return nb;
+}
+
+#define MM_PARTS(K, GRID, ...)                                                                           \
+  do {                                                                                                   \
+    if (P.n == 1) hipLaunchKernelGGL(K<1>, GRID, dim3(256), 0, s, parts_arg<1>(P), __VA_ARGS__);          \
+    else if (P.n <= 4) hipLaunchKernelGGL(K<4>, GRID, dim3(256), 0, s, parts_arg<4>(P), __VA_ARGS__);     \
+    else hipLaunchKernelGGL(K<kMaxLayoutParts>, GRID, dim3(256), 0, s, parts_arg<kMaxLayoutParts>(P), __VA_ARGS__); \
+  } while (0)
+
+hipError_t launch_to_observed(LayoutParts P, const double* glob, int64_t gs, double* obs, int64_t os, int n_rhs,
                               hipStream_t s) {
-  (void)n_pix;
-  const int64_t n = n_obs * ns * n_rhs;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_to_observed, grid_for(n), dim3(256), 0, s, glob, glob_stride, obs, obs_stride, obs2glob,
-                     n_obs, ns, n_rhs);
+  const int64_t nb = layout_blocks(P, false);
+  if (nb == 0 || n_rhs == 0) return hipSuccess;
+  if (nb > 0x7fffffff) return hipErrorInvalidValue;
+  MM_PARTS(k_to_observed, dim3((unsigned)nb, (unsigned)n_rhs), glob, gs, obs, os);
   return hipGetLastError();
 }
 
-hipError_t launch_to_global(const double* obs, int64_t obs_stride, double* glob, int64_t glob_stride,
-                            const int32_t* obs2glob, int64_t n_obs, int64_t n_pix, int ns, int n_rhs,
-                            hipStream_t s, const Raster& raster) {
-  const int64_t n = n_pix * n_rhs;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_to_global, grid_for(n), dim3(256), 0, s, obs, obs_stride, glob, glob_stride, obs2glob,
-                     n_obs, n_pix, ns, n_rhs, raster);
+// Every id observed: one pass over the observed ids.  Else zeros and that pass for large rows, the
+// search for small ones, whose launches count (its 20 dependent loads per id took 39 us for 2^20
+// polarised pixels, the two passes 15).
+hipError_t launch_to_global(LayoutParts P, const double* obs, int64_t os, double* glob, int64_t gs, int n_rhs,
+                            hipStream_t s) {
+  constexpr int64_t kSearchIds = 1 << 16;
+  bool all = true;
+  for (int k = 0; k < P.n; ++k) all = all && P.part[k].n_obs == P.part[k].n_glob;
+  int64_t nb = layout_blocks(P, true);
+  if (nb == 0 || n_rhs == 0) return hipSuccess;
+  if (nb > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 g((unsigned)nb, (unsigned)n_rhs);
+  if (!all && nb * 256 * n_rhs <= kSearchIds) {
+    MM_PARTS(k_to_global, g, obs, os, glob, gs);
+    return hipGetLastError();
+  }
+  if (!all) {
+    MM_PARTS(k_zero_global, g, glob, gs);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  nb = layout_blocks(P, false);
+  if (nb == 0) return hipSuccess;
+  MM_PARTS(k_put_global, dim3((unsigned)nb, (unsigned)n_rhs), obs, os, glob, gs);
   return hipGetLastError();
 }
+
+#undef MM_PARTS
 
 __global__ void k_hits(const int64_t* __restrict__ pix_ptr, const int32_t* __restrict__ obs2glob,
                        int32_t* __restrict__ hits, int64_t n_obs, int64_t n_pix, Raster raster) {

@@ -166,10 +166,10 @@ __global__ __launch_bounds__(256) void k_hwp_gather(const SampleTile* __restrict
         double v = 0.0, u = 0.0;
 #pragma unroll
         for (int k = 0; k < kHwpHarmonics; ++k) {
-          v += ar[k] * c[k] + ar[16 + k] * sn[k];
-          u += ar[8 + k] * c[k] + ar[24 + k] * sn[k];
+          v = fma(ar[k], c[k], fma(ar[16 + k], sn[k], v));
+          u = fma(ar[8 + k], c[k], fma(ar[24 + k], sn[k], u));
         }
-        y[i] = (Ty)((double)y0 + (v + tau * u));
+        y[i] = (Ty)((double)y0 + fma(tau, u, v));
       }
 #pragma unroll
       for (int i = 0; i + 1 < kHwpAhead; ++i) w[i] = w[i + 1], y1[i] = y1[i + 1];
@@ -401,24 +401,6 @@ __global__ void k_invert_diag(const double* __restrict__ d, double* __restrict__
 hipError_t launch_invert_diag(const double* d, double* out, int64_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_invert_diag, grid_for(n), dim3(256), 0, s, d, out, n);
-  return hipGetLastError();
-}
-
-// dst[r][i] = src[r][i], i < n, rows of stride dst_stride / src_stride
-__global__ void k_copy_rows(const double* __restrict__ src, int64_t src_stride, double* __restrict__ dst,
-                            int64_t dst_stride, int64_t n, int n_rhs) {
-  const int64_t total = n * n_rhs;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += stride) {
-    const int64_t r = k / n, i = k % n;
-    dst[r * dst_stride + i] = src[r * src_stride + i];
-  }
-}
-
-hipError_t launch_copy_rows(const double* src, int64_t src_stride, double* dst, int64_t dst_stride, int64_t n,
-                            int n_rhs, hipStream_t s) {
-  if (n == 0 || n_rhs == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_copy_rows, grid_for(n * n_rhs), dim3(256), 0, s, src, src_stride, dst, dst_stride, n, n_rhs);
   return hipGetLastError();
 }
 

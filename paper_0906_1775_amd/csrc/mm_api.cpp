@@ -776,30 +776,29 @@ void scatter_all(mm_plan_s* P, bool y_f64, const void* y, double* q, int R, hipS
 }
 
 // API map-shaped rows (stride ng, global ids) <-> iteration rows (stride nu, observed ids)
-void to_obs(mm_plan_s* P, const double* glob, double* obs, int R, hipStream_t s) {
-  hipchk(launch_to_observed(glob, P->ng(), obs, P->nu(), P->px.obs2glob, P->n_obs, P->n_pix, P->ns, R, s), "layout");
+LayoutParts layout_parts(const mm_plan_s* P) {
+  LayoutParts L;
+  auto add = [&](const Layout* lay, int64_t n_obs, int64_t n_glob, int ns, int64_t goff, int64_t ooff) {
+    LayoutPart& p = L.part[L.n++];
+    p.identity = lay == nullptr;
+    if (lay) p.obs2glob = lay->obs2glob, p.raster = lay->raster;
+    p.n_obs = n_obs, p.n_glob = n_glob, p.ns = ns, p.goff = goff, p.ooff = ooff;
+  };
+  add(&P->px, P->n_obs, P->n_pix, P->ns, 0, 0);
   for (const Template& T : P->tmpl) {
-    const double* g = glob + P->n_pix * P->ns + T.goff;
-    double* o = obs + P->nmap() + T.ooff;
-    if (T.kind == MM_TMPL_ONEHOT)
-      hipchk(launch_to_observed(g, P->ng(), o, P->nu(), T.lay.obs2glob, T.lay.n_obs, T.n_glob, 1, R, s), "layout");
-    else
-      hipchk(launch_copy_rows(g, P->ng(), o, P->nu(), T.n_unk, R, s), "layout");
+    const int64_t goff = P->n_pix * P->ns + T.goff, ooff = P->nmap() + T.ooff;
+    if (T.kind == MM_TMPL_ONEHOT) add(&T.lay, T.lay.n_obs, T.n_glob, 1, goff, ooff);
+    else add(nullptr, T.n_unk, T.n_unk, 1, goff, ooff);
   }
+  return L;
+}
+
+void to_obs(mm_plan_s* P, const double* glob, double* obs, int R, hipStream_t s) {
+  hipchk(launch_to_observed(layout_parts(P), glob, P->ng(), obs, P->nu(), R, s), "layout");
 }
 
 void to_glob(mm_plan_s* P, const double* obs, double* glob, int R, hipStream_t s) {
-  hipchk(launch_to_global(obs, P->nu(), glob, P->ng(), P->px.obs2glob, P->n_obs, P->n_pix, P->ns, R, s,
-                          P->px.raster),
-         "layout");
-  for (const Template& T : P->tmpl) {
-    double* g = glob + P->n_pix * P->ns + T.goff;
-    const double* o = obs + P->nmap() + T.ooff;
-    if (T.kind == MM_TMPL_ONEHOT)
-      hipchk(launch_to_global(o, P->nu(), g, P->ng(), T.lay.obs2glob, T.lay.n_obs, T.n_glob, 1, R, s), "layout");
-    else
-      hipchk(launch_copy_rows(o, P->nu(), g, P->ng(), T.n_unk, R, s), "layout");
-  }
+  hipchk(launch_to_global(layout_parts(P), obs, P->nu(), glob, P->ng(), R, s), "layout");
 }
 
 // out = [P B]^T N^-1 [P B] in (iteration layout), R right-hand sides, precision of fs

@@ -179,13 +179,24 @@ int scatter_blocks(int64_t n_obs, const SellLayout& L);
 int seg_lanes(int64_t n_obs, int64_t n_valid);   // lanes per pixel of the pixel-major scatter
 hipError_t launch_convert(bool in_f64, bool out_f64, const void* in, void* out, int64_t n,
                           hipStream_t s);
-// observed <-> global layout of n_rhs rows (strides obs_stride, glob_stride in doubles)
-hipError_t launch_to_observed(const double* glob, int64_t glob_stride, double* obs, int64_t obs_stride,
-                              const int32_t* obs2glob, int64_t n_obs, int64_t n_pix, int ns, int n_rhs,
+// observed <-> global layout of n_rhs rows (strides os, gs in doubles): the map and the template blocks
+struct LayoutPart {
+  const int32_t* obs2glob = nullptr;   // [n_obs] global id of each observed id, in raster order
+  int64_t n_obs = 0, n_glob = 0;
+  int64_t ooff = 0, goff = 0;          // offsets in a row
+  Raster raster;
+  int ns = 1, block0 = 0;
+  bool identity = false;               // every id is observed, in its own order
+};
+constexpr int kMaxLayoutParts = 17;    // the map and 16 template blocks
+struct LayoutParts {
+  int n = 0;
+  LayoutPart part[kMaxLayoutParts];
+};
+hipError_t launch_to_observed(LayoutParts P, const double* glob, int64_t gs, double* obs, int64_t os, int n_rhs,
                               hipStream_t s);
-hipError_t launch_to_global(const double* obs, int64_t obs_stride, double* glob, int64_t glob_stride,
-                            const int32_t* obs2glob, int64_t n_obs, int64_t n_pix, int ns, int n_rhs,
-                            hipStream_t s, const Raster& raster = {});
+hipError_t launch_to_global(LayoutParts P, const double* obs, int64_t os, double* glob, int64_t gs, int n_rhs,
+                            hipStream_t s);
 hipError_t launch_hits(const int64_t* pix_ptr, const int32_t* obs2glob, int32_t* hits,
                        int64_t n_obs, int64_t n_pix, hipStream_t s, const Raster& raster = {});
 hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
@@ -304,8 +315,6 @@ hipError_t launch_hwp_diag(int kind, const SampleTile* tiles, int n_tiles, const
                            const int32_t* iv_filter, const double* lags, int n_c, double* partial,
                            double* diag, hipStream_t s);
 hipError_t launch_invert_diag(const double* d, double* out, int64_t n, hipStream_t s);
-hipError_t launch_copy_rows(const double* src, int64_t src_stride, double* dst, int64_t dst_stride, int64_t n,
-                            int n_rhs, hipStream_t s);
 // y_out = f_b(0) y_in over tiles of the stationary intervals (white noise, n_c = 1)
 hipError_t launch_white(bool out_f64, bool in_f64, const SampleTile* tiles, int n_tiles, const int32_t* iv_filter,
                         const double* lags, int n_c, const void* y_in, void* y_out, int64_t n_t, int n_rhs,

@@ -88,3 +88,28 @@ def test_half_wave_plate_block(lens, scale, n_rhs, precision, tol):
         back[r] = x[r, 0] + (cols * x[r, 1:].reshape(-1, 32)[of]).sum(axis=1)
     assert max_rel(got, want) <= tol
     assert max_rel(mm.unpoint(torch.from_numpy(x).cuda()).cpu().numpy(), back) <= tol
+
+
+@pytest.mark.parametrize("n_blocks", [1, 3, 4, 16])
+def test_many_template_blocks(n_blocks):
+    rng = np.random.default_rng(n_blocks)
+    n, n_pix, R = 5000, 70, 2
+    pix = rng.integers(0, n_pix // 2, n).astype(np.int32)            # half of the map unobserved
+    sizes = [int(rng.integers(1, 300)) for _ in range(n_blocks)]
+    idx = [rng.integers(-1, max(1, m - m // 3), n).astype(np.int32) for m in sizes]   # and a third of the amplitudes
+    mm = _plan(pix, None, n_pix, 1, "fp64", R, [dict(kind="onehot", idx=torch.from_numpy(i).cuda(), n_amp=m)
+                                                for i, m in zip(idx, sizes)])
+    y = rng.standard_normal((R, n))
+    x = rng.standard_normal((R, n_pix + sum(sizes)))
+    got = mm.point(torch.from_numpy(y).cuda()).cpu().numpy()
+    back = mm.unpoint(torch.from_numpy(x).cuda()).cpu().numpy()
+    for r in range(R):
+        want, off = [np.bincount(pix, weights=y[r], minlength=n_pix)], n_pix
+        tod = x[r, :n_pix][pix]
+        for i, m in zip(idx, sizes):
+            ok = i >= 0
+            want.append(np.bincount(i[ok], weights=y[r][ok], minlength=m))
+            tod = tod + np.where(ok, x[r, off:off + m][np.where(ok, i, 0)], 0.0)
+            off += m
+        assert max_rel(got[r], np.concatenate(want)) <= 1e-12
+        assert max_rel(back[r], tod) <= 1e-12
