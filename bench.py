@@ -209,7 +209,7 @@ def paper_nf(n_c, iv_start):
 
 
 def time_filter(mm, tod, precision, s, n_launch=20):
-    """Mean launch time (ms) of the overlap-save N^-1 kernel: mm_weight launches only k_ols;
+    """Mean launch time (ms) of the overlap-save N^-1 kernel: mm_weight launches only the filter;
     HIP events on the stream it is launched on."""
     import ctypes
     import torch
@@ -236,11 +236,14 @@ def time_filter(mm, tod, precision, s, n_launch=20):
 
 
 def filter_kernel_name(precision, lib_nf, shape):
-    """The overlap-save kernel a plan launches: the wavefront-private four-step transforms for
-    shape 10 in float32 (2^14 and 2^15 points), the Stockham shapes otherwise."""
-    if precision == "mixed" and shape == 10 and lib_nf in (1 << 15, 1 << 16):
-        return "k_ols_wave32" if lib_nf == 1 << 16 else "k_ols_wave"
-    return "k_ols"
+    """The overlap-save kernel a plan launches: the wavefront-private transforms for shape 1 up to
+    2^13 points (float64: 2^14) and shape 10 beyond, the batched four-step one past 2^16 samples,
+    the Stockham shapes otherwise."""
+    logn, fp64 = lib_nf.bit_length() - 2, precision != "mixed"
+    if lib_nf > 1 << 16:
+        return "k_long_columns, k_long_rows, k_long_output"
+    wave = shape == 10 or (shape <= 1 and 10 <= logn <= (14 if fp64 else 13))
+    return "k_ols_wave" if wave else "k_ols"
 
 
 def filter_roofline(ols_ms, workload, precision, n_t, R, n_c, iv_start, lib_nf, shape=0):
@@ -365,7 +368,7 @@ def traffic_from(fetch_dir, write_dir, workload, precision, n_sample_rhs, alg_by
     cw, ow = read(write_dir, "WRITE_SIZE")
     copy_bytes = (1 << 28) * 4
     fs, ws = copy_bytes / (cf * 1024), copy_bytes / (cw * 1024)
-    rec = dict(kernel="k_ols (overlap-save N^-1)", workload=WORKLOADS[workload], precision=precision,
+    rec = dict(kernel="k_ols_wave (overlap-save N^-1)", workload=WORKLOADS[workload], precision=precision,
                n_sample_rhs=n_sample_rhs, kernel_source_hash=kernel_source_hash(),
                fetch_kib_per_dispatch=round(of, 2), write_kib_per_dispatch=round(ow, 2),
                dispatches_used="median over the filter dispatches of the run",
