@@ -713,14 +713,15 @@ void gather_all(mm_plan_s* P, bool y_f64, const double* x, void* y, int R, hipSt
 
 // Whether the filter looks its windows up in the map itself (launch_ols_sky) instead of reading
 // the TOD a gather wrote.  It saves the gather's launch and round trip and the TOD's way out and
-// back, and looks up the samples that windows share twice (halo times the lookups).  Per
-// iteration, separate / fused (us): up to 2^20 samples everywhere 1.05 to 1.24 (65,536 samples,
-// T 30.8 / 26.9, polarisation 35.2 / 32.6); temperature at every size (float64, 2^26 samples of
-// 2000 x 2000 pixels 1003 / 744, 3 x 1.8 M 124 / 104); polarisation in float64 with short
-// halos (2^24: 299 / 280; halo 2: 596 / 625) and in float32 while the TOD is small or, for
-// one row, past the last-level cache (2^22: 72 / 64; 2^24: 232 / 237; 2^26: 855 / 809); not
-// with many rows, each of which reads the pointing again (8 x 2^26: 4004 / 4694), and not from
-// a float64 map of float32 TODs (2^24: 201 / 219).
+// back, and looks up the samples that windows share twice (halo times the lookups).  Separate /
+// fused, us: up to 2^20 samples everywhere 1.05 to 1.24 times faster (an iteration of 65,536
+// samples: T 30.8 / 26.9, polarisation 35.2 / 32.6); temperature at every size (operator, 2^26
+// samples of 2000 x 2000 pixels, 4 float64 rows 3632 / 2971, 8 float32 rows of 4096 x 768 3280 /
+// 3287); polarisation in float64 up to halo 1.6 (2^24 samples: 244 / 206 at 1.32, 266 / 233 at
+// 1.58, 310 / 310 at 2); in float32 one row of the search direction with up to 2^13 points
+// (iteration, 2^26 samples: 696 / 653; 2^24: 195 / 182, at worst 206 / 209; with the two rows a
+// wavefront of 2^15 points 764 / 779), more rows while they are small, since each reads the
+// pointing again (2 x 2^25: 542 / 577), and a float64 map while it is (2^22: 58 / 50; 2^24: 188 / 195).
 bool sees_map(const mm_plan_s* P, const FilterSetup& fs, int R, bool map_f32) {
   if (P->n_c <= 1 || fs.long_path || !ols_variant_wave(fs.logn, fs.fp64, fs.variant) || !P->tmpl.empty() ||
       P->n_obs == 0 || (fs.fp64 && map_f32))
@@ -728,10 +729,11 @@ bool sees_map(const mm_plan_s* P, const FilterSetup& fs, int R, bool map_f32) {
   const int64_t total = R * P->n_t;
   if (total <= (1 << 20) || P->ns == 1) return true;
   const double halo = 2.0 * (double)fs.N / (double)fs.m;
-  if (fs.fp64) return halo <= 1.15 && (R <= 2 || total <= (1 << 24));
-  if (!map_f32) return halo <= 1.34 && total <= (1 << 21);
-  if (R > 1) return halo <= 1.15 && total <= (1 << 24);
-  return halo <= 1.34 && (total <= (1 << 22) || (halo <= 1.15 && total >= (1 << 26)));
+  if (halo > 1.6) return false;
+  if (fs.fp64) return R <= 4 || total <= (1 << 24);
+  if (fs.N > (1 << 13)) return false;
+  if (!map_f32) return total <= (1 << 22);
+  return R == 1 || (halo <= 1.15 && total <= (1 << 24));
 }
 
 // y_out = N^-1 P x (rows as gather_all), by way of the TOD y unless one kernel does both
