@@ -496,7 +496,7 @@ __global__ __launch_bounds__(Shape<LOGM>::NT) void k_symbol(
     }
   F::forward(v, lds, ptw, t);
   const double scale = 1.0 / (double)N;
-  T* __restrict__ out = spec + ((int64_t)blockIdx.y << logn);
+  T* __restrict__ out = spec + (int64_t)blockIdx.y * (N + 1);
   constexpr int LL = F::last_log_fwd(), RL = 1 << LL;
 #pragma unroll
   for (int i = 0; i < E / RL; ++i)
@@ -505,6 +505,39 @@ __global__ __launch_bounds__(Shape<LOGM>::NT) void k_symbol(
       const uint32_t k = (uint32_t)(b + B * (t + i * F::NT + r * (M >> LL)));
       out[((k & ((1 << rowlog) - 1)) << (logn - rowlog)) + (k >> rowlog)] = (T)(v[i * RL + r].re * scale);
     }
+}
+
+// A float64 sum with its roundings (Knuth's exact addition)
+struct Sum2 {
+  double hi, lo;
+  __device__ __forceinline__ void add(double x) {
+    const double s = hi + x, z = s - hi;
+    lo += (hi - (s - z)) + (x - z);
+    hi = s;
+  }
+};
+
+// f(0) + 2 sum_{tau = 1}^{n_c - 1} f(tau) behind each filter's N symbol values, one block per filter.
+// It is small beside f(0) (a 1/f filter passes no constant), hence the compensated sums.
+template <typename T>
+__global__ __launch_bounds__(1024) void k_lag_total(const double* __restrict__ lags, int n_c, int64_t N,
+                                                    T* __restrict__ spec) {
+  __shared__ double sh[2][1024];
+  const int tid = threadIdx.x;
+  const double* __restrict__ f = lags + (int64_t)blockIdx.x * n_c;
+  Sum2 s{0.0, 0.0};
+  for (int64_t tau = tid; tau < n_c; tau += 1024) s.add(tau ? f[tau] : 0.5 * f[0]);
+  for (int o = 512; o >= 1; o >>= 1) {
+    sh[0][tid] = s.hi;
+    sh[1][tid] = s.lo;
+    __syncthreads();
+    if (tid < o) {
+      s.add(sh[0][tid + o]);
+      s.lo += sh[1][tid + o];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) spec[(int64_t)blockIdx.x * (N + 1) + N] = (T)(2.0 * (s.hi + s.lo));
 }
 
 static int symbol_logm(int logn) { return logn < kSymbolLogN ? logn : kSymbolLogN; }
@@ -524,12 +557,16 @@ hipError_t launch_spectra(const double* lags, int n_filters, int n_c, int logn, 
     for (int f0 = 0; f0 < n_filters; f0 += 65535) {
       const dim3 g(1u << (logn - LOGM), (unsigned)(n_filters - f0 < 65535 ? n_filters - f0 : 65535));
       const double* lg = lags + (int64_t)f0 * n_c;
-      if (fp64)
-        hipLaunchKernelGGL((k_symbol<double, LOGM>), g, dim3(Shape<LOGM>::NT), 0, s, lg, n_c, logn, rowlog,
-                           (double*)spec + ((int64_t)f0 << logn), (const cx<double>*)scratch);
-      else
-        hipLaunchKernelGGL((k_symbol<float, LOGM>), g, dim3(Shape<LOGM>::NT), 0, s, lg, n_c, logn, rowlog,
-                           (float*)spec + ((int64_t)f0 << logn), (const cx<double>*)scratch);
+      auto go = [&](auto tc) {
+        using T = decltype(tc);
+        const int64_t N = int64_t(1) << logn;
+        T* out = (T*)spec + f0 * (N + 1);
+        hipLaunchKernelGGL((k_symbol<T, LOGM>), g, dim3(Shape<LOGM>::NT), 0, s, lg, n_c, logn, rowlog, out,
+                           (const cx<double>*)scratch);
+        hipLaunchKernelGGL(k_lag_total<T>, dim3(g.y), dim3(1024), 0, s, lg, n_c, N, out);
+      };
+      if (fp64) go(double{});
+      else go(float{});
       const hipError_t el = hipGetLastError();
       if (el != hipSuccess) return el;
     }
@@ -541,7 +578,8 @@ hipError_t launch_spectra(const double* lags, int n_filters, int n_c, int logn, 
 // One workgroup per (chunk, RHS).  The n_f = 2N real window x is z_n = x_n - i x_(n+N)
 // (negacyclic embedding, see k_ols_wave.hip): its shifted transform Z meets the real
 // symbol F pointwise, and exp(-2 pi i n / (4N)) times the plain transform of
-// conj(F Z) is y_n + i y_(n+N).  The table spec holds F / N.
+// conj(F Z) is y_n + i y_(n+N), all of it without the window's mean (window_mean).  The table spec
+// holds F / N, and behind it the response to a constant.
 
 template <typename T, typename Tin, int LOGN, int V>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, OlsShape<LOGN, V>::NT),
@@ -575,6 +613,13 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, OlsShape<LOGN, V>::NT),
   const int a = (int)(lo > s0 ? lo - s0 : 0);   // (lo <= out_start: a <= n_c)
   const int b = (int)(hi - s0 < 2 * N ? hi - s0 : 2 * N);
   const Rsrc src = buffer_of(yin + roff + s0 + a, (b - a) * (int)sizeof(Tin));
+  T c = (T)0;
+  if constexpr (NT > 64)
+    c = window_mean<T, 2 * N>(t, [&](int n) {
+      Tin x;
+      buffer_get(src, opaque((uint32_t)(n - a) * (uint32_t)sizeof(Tin)), x);
+      return (T)x;
+    });
 #pragma unroll
   for (int i = 0; i < E / R0; ++i)
 #pragma unroll
@@ -583,11 +628,23 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, OlsShape<LOGN, V>::NT),
       Tin x, y;
       buffer_get(src, off, x);
       buffer_get(src, opaque(off + N * (uint32_t)sizeof(Tin)), y);
-      v[i * R0 + r] = {(T)x, -(T)y};
+      v[i * R0 + r] = {(T)x - c, c - (T)y};
     }
+  if constexpr (NT <= 64) {   // one wavefront: from all samples
+    T sum = (T)0, sq = (T)0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      sum += v[e].re - v[e].im;
+      sq += v[e].re * v[e].re + v[e].im * v[e].im;
+    }
+    c = offset_of<NT>(sum, sq, 2 * N);
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = {v[e].re - c, v[e].im + c};
+  }
 
   F::template forward<true>(v, lds, ptw, t);
-  const T* __restrict__ S = spec + (int64_t)ch.filter * N;
+  const T* __restrict__ S = spec + (int64_t)ch.filter * (N + 1);
+  const T back = c * S[N];   // what the filter makes of the mean
   constexpr int LL = F::last_log_fwd(), RL = 1 << LL;
 #pragma unroll
   for (int i = 0; i < E / RL; ++i)
@@ -610,8 +667,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, OlsShape<LOGN, V>::NT),
       const int n = t + i * NT + r * (N >> LZ);
       const cx<T> z = cmul(v[i * RZ + r], qtw[n]);
       const uint32_t off = opaque((uint32_t)(n - n_c) * (uint32_t)sizeof(T));   // wraps below n_c
-      buffer_put(dst, off, z.re);
-      buffer_put(dst, opaque(off + N * (uint32_t)sizeof(T)), z.im);
+      buffer_put(dst, off, z.re + back);
+      buffer_put(dst, opaque(off + N * (uint32_t)sizeof(T)), z.im + back);
     }
 }
 

@@ -71,6 +71,12 @@ __device__ __forceinline__ uint32_t xcd_block() {
   return (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
+// The mean of a job's window (window_mean)
+template <typename T, typename Tin, int N>
+__device__ __forceinline__ T long_mean(const Tin* __restrict__ src, int64_t s0, int64_t lo, int64_t hi) {
+  return window_mean<T, 2 * N>(threadIdx.x, [&](int n) { return s0 + n >= lo && s0 + n < hi ? (T)src[s0 + n] : (T)0; });
+}
+
 // columns of the forward transform: work[j][k1][n2] = W_N^(n2 (k1 + 1/4)) sum_n1 z[N2 n1 + n2] W_N1^(n1 (k1 + 1/4))
 template <typename T, typename Tin, int L1, int L2>
 __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ yin, cx<T>* __restrict__ work,
@@ -92,6 +98,7 @@ __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ y
   const OlsChunk ch = chunks[job - (int64_t)rhs * n_chunks];
   const Tin* __restrict__ src = yin + (int64_t)rhs * n_t;
   const int64_t s0 = ch.out_start - n_c, lo = ch.iv_lo, hi = ch.iv_hi;
+  const T mean = long_mean<T, Tin, (int)N>(src, s0, lo, hi);
   cx<T>* tile = reinterpret_cast<cx<T>*>(lds);
   const int tid = threadIdx.x;
   // the workgroup's 16 columns, row by row: 16 consecutive points = two runs of 16 samples
@@ -102,7 +109,7 @@ __global__ __launch_bounds__(1024) void k_long_columns(const Tin* __restrict__ y
     const int64_t j = s0 + (int64_t)N2 * n1 + cg * kCW + c;
     const T a = (j >= lo && j < hi) ? (T)src[j] : (T)0;
     const T b = (j + N >= lo && j + N < hi) ? (T)src[j + N] : (T)0;
-    tile[c * TS + n1] = {a, -b};
+    tile[c * TS + n1] = {a - mean, mean - b};
   }
   __syncthreads();
   const int w = tid >> 6, t = tid & 63;   // wavefront w transforms column cg * 16 + w
@@ -155,7 +162,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_long_rows(cx<T>* __restrict_
   for (int r = 0; r < F2::E; ++r) v[r] = base[t + 64 * r];
   F2::forward_rev(v, lds + w * F2::LDS_BYTES, ptw2, t);
   // v[r] = Z[row + N1 k2], k2 = t + 64 r; the symbol in row order
-  const T* __restrict__ SR = spec_rows + (int64_t)ch.filter * N + (int64_t)row * N2;
+  const T* __restrict__ SR = spec_rows + (int64_t)ch.filter * (N + 1) + (int64_t)row * N2;
 #pragma unroll
   for (int r = 0; r < F2::E; ++r) {
     const T f = SR[t + 64 * r];
@@ -167,8 +174,9 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_long_rows(cx<T>* __restrict_
 }
 
 // columns of the inverse: N1-point transforms over k1, times W_N1^(n1 / 4), and the valid outputs
-template <typename T, int L1, int L2>
-__global__ __launch_bounds__(1024) void k_long_output(const cx<T>* __restrict__ work, T* __restrict__ yout,
+template <typename T, typename Tin, int L1, int L2>
+__global__ __launch_bounds__(1024) void k_long_output(const Tin* __restrict__ yin, const cx<T>* __restrict__ work,
+                                                      T* __restrict__ yout, const T* __restrict__ spec_rows,
                                                       const OlsChunk* __restrict__ chunks, int64_t job0,
                                                       int n_chunks, int64_t n_t, int n_c, int m,
                                                       const CgState* __restrict__ st,
@@ -186,6 +194,8 @@ __global__ __launch_bounds__(1024) void k_long_output(const cx<T>* __restrict__ 
   if (st && !st[rhs].active) return;   // this RHS has stopped iterating
   const OlsChunk ch = chunks[job - (int64_t)rhs * n_chunks];
   const int64_t s0 = ch.out_start - n_c, hi = ch.iv_hi;
+  const T back = long_mean<T, Tin, (int)N>(yin + (int64_t)rhs * n_t, s0, ch.iv_lo, hi) *
+                 spec_rows[(int64_t)ch.filter * (N + 1) + N];   // what the filter makes of the mean
   cx<T>* tile = reinterpret_cast<cx<T>*>(lds);
   const int tid = threadIdx.x;
   const cx<T>* __restrict__ srcw = work + jl * N;
@@ -214,8 +224,8 @@ __global__ __launch_bounds__(1024) void k_long_output(const cx<T>* __restrict__ 
     const int c = e % kCW, n1 = e / kCW;
     const int64_t pos = (int64_t)N2 * n1 + cg * kCW + c;
     const cx<T> z = tile[n1 * OS + c];
-    if (pos >= n_c && pos < n_c + m && s0 + pos < hi) dst[s0 + pos] = z.re;
-    if (pos + N >= n_c && pos + N < n_c + m && s0 + pos + N < hi) dst[s0 + pos + N] = z.im;
+    if (pos >= n_c && pos < n_c + m && s0 + pos < hi) dst[s0 + pos] = z.re + back;
+    if (pos + N >= n_c && pos + N < n_c + m && s0 + pos + N < hi) dst[s0 + pos + N] = z.im + back;
   }
 }
 
@@ -269,8 +279,8 @@ static hipError_t long_launch(const void* y_in, void* y_out, const OlsChunk* chu
                        (const cx<T>*)ltab);
     hipLaunchKernelGGL((k_long_rows<T, kL1, L2>), dim3((unsigned)(nb * NP)), dim3(64 * kRowWaves), 0, s, (cx<T>*)work,
                        chunks, j0, n_chunks, st, (const T*)spec, (const cx<T>*)ptw2, (const cx<T>*)ltab);
-    hipLaunchKernelGGL((k_long_output<T, kL1, L2>), dim3((unsigned)(nb * NG)), dim3(1024), 0, s,
-                       (const cx<T>*)work, (T*)y_out, chunks, j0, n_chunks, n_t, n_c, m, st, (const cx<T>*)ptw1,
+    hipLaunchKernelGGL((k_long_output<T, Tin, kL1, L2>), dim3((unsigned)(nb * NG)), dim3(1024), 0, s,
+                       (const Tin*)y_in, (const cx<T>*)work, (T*)y_out, (const T*)spec, chunks, j0, n_chunks, n_t, n_c, m, st, (const cx<T>*)ptw1,
                        (const cx<T>*)qtw);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

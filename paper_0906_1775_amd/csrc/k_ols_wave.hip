@@ -67,20 +67,17 @@ struct WaveShape {
 
 // Twiddle tables (complex entries).  A decimation-in-time stage of 2^s points with shift
 // sigma needs exp(-2 pi i (j + sigma) / len) for len = 2, 4, .., 2^s, j < max(1, len / 4) (the
-// other quarter is -i times these).  The tables hold j = 0, the s values
-// exp(-2 pi i sigma / len); the others follow by constants, one operation per point and one
-// rounding more, because table loads (from L2, a few dozen per thread) cost more than
-// arithmetic here: with all eight values of a 16-point stage in the tables 2^26 samples at
-// n_c = 8192 take 299 us instead of 227 (float32, NO = 32) and 571 instead of 528 (float64,
-// NO = 16).
+// other quarter is -i times these): eight values for a 16-point stage, at 0 for len = 2, else at
+// len / 4 + j.  All of them are rounded once, in the tables: as products of the j = 0 ones with
+// constants they cost 4 to 8 % of the filter's error.
 template <int NO>
 struct WaveTables {
   static constexpr int F1 = 0;                      // [NO][8]: sigma = s1, j < max(1, len / 4)
   static constexpr int F2 = F1 + NO * 8;            // [NO][16 k1][2]: sigma = s2
-  static constexpr int F3 = F2 + NO * 32;           // [NO][64 mu][4]: sigma = s3
-  static constexpr int I2 = F3 + NO * 256;          // [16 m][2]: sigma = m / 16
-  static constexpr int I3 = I2 + 32;                // [64 l][4]: sigma = l / 64
-  static constexpr int I4 = I3 + 256;               // [NO k_o][1024 g]: exp(-2 pi i g (k_o + 1/4) / N)
+  static constexpr int F3 = F2 + NO * 32;           // [NO][64 mu][8]: sigma = s3
+  static constexpr int I2 = F3 + NO * 512;          // [16 m][2]: sigma = m / 16
+  static constexpr int I3 = I2 + 32;                // [64 l][8]: sigma = l / 64
+  static constexpr int I4 = I3 + 512;               // [NO k_o][1024 g]: exp(-2 pi i g (k_o + 1/4) / N)
   static constexpr int TOTAL = I4 + NO * 1024;
 };
 
@@ -169,13 +166,6 @@ __device__ __forceinline__ void dit(cx<T>* v, Tw tw) {
   }
 #pragma unroll
   for (int k = 0; k < R; ++k) v[k] = x[k];
-}
-
-// the twiddle (len, j) from the len = 2, 4, 8, 16 ones of j = 0
-template <typename T>
-__device__ __forceinline__ cx<T> derived(const cx<T>* w, int len, int j) {
-  const cx<T> u = w[len == 2 ? 0 : len == 4 ? 1 : len == 8 ? 2 : 3];
-  return j == 0 ? u : cmul(u, unit128<T>(j * (128 / len)));
 }
 
 // The same for R <= 32, sigma = 1/4 and compile-time twiddles, in radix-4 levels after a
@@ -382,21 +372,34 @@ __device__ __forceinline__ void load_twiddles(cx<T>* w, const cx<T>* __restrict_
   for (int i = 0; i < n; ++i) w[i] = p[i];
 }
 
+template <typename T, int RPW>
+constexpr bool wave_early = sizeof(T) == 4 && RPW == 1;
+template <typename T, int NO, int RPW>
+constexpr bool wave_itab = RPW == 2 || (sizeof(T) == 8 && NO >= 8);
+
 // One row: 1024-point forward stage, symbol, 1024-point inverse stage and the twiddle
 // before the inverse's outer stage.  v[j] = column l + 64 j of row k_o on entry and exit.
 // EARLY: table loads go out a stage ahead, behind the exchange before it, and the symbol's
-// before the stage that needs it; else (float64, or two rows in registers, TWO) behind the
-// exchange only.
-template <typename T, int NO, bool EARLY, bool TWO>
+// before the stage that needs it; else (float64, or two rows in registers) where their values
+// are used, and the last inverse stage's from itab, a copy in LDS ([8][64]), where workgroups are
+// large enough for one (2^24 samples: float32 NO = 32 71.6 us against 83.1 from memory, float64 NO = 16 128
+// against 131; for NO < 8 the copies would cost occupancy, 90 against 85 at NO = 1).
+template <typename T, int NO, int RPW>
 __device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row, const cx<T>* __restrict__ tab,
-                                           const T* __restrict__ sym, int k_o, int l) {
+                                           const T* __restrict__ sym, const cx<T>* itab, int k_o, int l) {
   using W = WaveTables<NO>;
-  constexpr bool SUM6 = sizeof(T) == 8;
+  constexpr bool EARLY = wave_early<T, RPW>, TWO = RPW == 2;
+  // Six operations in float64 and, with two rows in registers, in the third stage; in the inverse of
+  // float32 but at NO = 1 and 2, where they would put the error above the plain transform's (1.05 of
+  // it, 0.99 so, for 3 % more time), and there not in the 4-point stages of float64 either.  Eight
+  // everywhere in float64 spill (NO = 1: 142 us against 82; an operator of 2 x 2^24 samples at
+  // NO = 16, the 4-point stages alone: 599 against 517).
+  constexpr bool SUM6 = sizeof(T) == 8, INV6 = sizeof(T) == 8 || NO > 2;
   const int m = l & 15, hq = l >> 4;
   const cx<T>* __restrict__ t2 = tab + W::F2 + (uint32_t)((k_o * 16 + 4 * hq) * 2);
-  const cx<T>* __restrict__ t3 = tab + W::F3 + (uint32_t)((k_o * 64 + l) * 4);
+  const cx<T>* __restrict__ t3 = tab + W::F3 + (uint32_t)((k_o * 64 + l) * 8);
   const T* __restrict__ fs = sym + (uint32_t)(k_o * 1024 + l);
-  cx<T> w2[8], w3[4];
+  cx<T> w2[8], w3[8];
   T f[16];
   if (EARLY) load_twiddles<8>(w2, t2);
   {   // forward: 16 points over j; the row's twiddles are uniform (scalar loads, all of them)
@@ -408,10 +411,10 @@ __device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row
   // (k1, l) -> lane (m, hq): k1 = 4 hq + e, h = 0 .. 3
   exchange_private<T>(v, row, [&](int i) { return i * 64 + l; },
                       [&](int i) { return (4 * hq + (i >> 2)) * 64 + m + 16 * (i & 3); });
-  if (EARLY) load_twiddles<4>(w3, t3);
+  if (EARLY) load_twiddles<8>(w3, t3);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) dit<T, 2, SUM6>(v + 4 * e, [&](int len, int) { return w2[2 * e + len / 4]; });   // 4 points over h
-  if (!EARLY) load_twiddles<4>(w3, t3);
+  for (int e = 0; e < 4; ++e) dit<T, 2, SUM6 && (NO > 2)>(v + 4 * e, [&](int len, int) { return w2[2 * e + len / 4]; });   // 4 points over h
+  if (!EARLY) load_twiddles<8>(w3, t3);
   // (k1, c1, m) -> lane mu = k1 + 16 c1, register m
   exchange_private<T>(v, row, [&](int i) { return ((i & 3) * 16 + 4 * hq + (i >> 2)) * 17 + m; },
                       [&](int i) { return l * 17 + i; });
@@ -419,7 +422,7 @@ __device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row
 #pragma unroll
     for (int c = 0; c < 16; ++c) f[c] = fs[64 * c];
   }
-  dit<T, 4, !EARLY>(v, [&](int len, int j) { return derived(w3, len, j); });   // 16 points over m
+  dit<T, 4, !EARLY>(v, [&](int len, int j) { return w3[len == 2 ? 0 : len / 4 + j]; });   // 16 points over m
 #pragma unroll
   for (int c = 0; c < 16; ++c) {   // conj(F Z)
     if (!EARLY) f[c] = fs[64 * c];
@@ -430,13 +433,19 @@ __device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row
   // (c1, k1, m) -> lane (m, hq): k1 = 4 hq + e, c1 = 0 .. 3
   exchange_private<T>(v, row, [&](int i) { return l * 17 + i; },
                       [&](int i) { return ((i & 3) * 16 + 4 * hq + (i >> 2)) * 17 + m; });
-  load_twiddles<4>(w3, tab + W::I3 + (uint32_t)(l * 4));
+  if (EARLY) load_twiddles<8>(w3, tab + W::I3 + (uint32_t)(l * 8));
 #pragma unroll
-  for (int e = 0; e < 4; ++e) dit<T, 2, true>(v + 4 * e, [&](int len, int) { return w2[len / 4]; });   // 4 points over c1
+  for (int e = 0; e < 4; ++e) dit<T, 2, INV6 && (NO > 2)>(v + 4 * e, [&](int len, int) { return w2[len / 4]; });   // 4 points over c1
   // (k1, l) -> lane l, register k1
   exchange_private<T>(v, row, [&](int i) { return (4 * hq + (i >> 2)) * 64 + m + 16 * (i & 3); },
                       [&](int i) { return i * 64 + l; });
-  dit<T, 4, true>(v, [&](int len, int j) { return derived(w3, len, j); });   // 16 points over k1
+  if constexpr (wave_itab<T, NO, RPW>) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w3[i] = itab[i * 64 + l];
+  } else if (!EARLY) {
+    load_twiddles<8>(w3, tab + W::I3 + (uint32_t)(l * 8));
+  }
+  dit<T, 4, INV6>(v, [&](int len, int j) { return w3[len == 2 ? 0 : len / 4 + j]; });   // 16 points over k1
   const cx<T>* __restrict__ w4 = tab + W::I4 + (uint32_t)(k_o * 1024 + l);
 #pragma unroll
   for (int j = 0; j < 16; ++j) v[j] = cmul(v[j], w4[64 * j]);
@@ -467,22 +476,36 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
   const int rhs = __builtin_amdgcn_readfirstlane((int)(job / gridDim.x));   // uniform: scalar row offsets
   if (st && !st[rhs].active) return;   // this RHS has stopped iterating
   __shared__ __align__(16) typename Slot<T>::type lds[S::LDS_SLOTS];
+  __shared__ __align__(16) cx<T> itab[wave_itab<T, NO, RPW> ? 512 : 1];
   const OlsChunk ch = chunks[job - (int64_t)rhs * gridDim.x];
   const int t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  if constexpr (wave_itab<T, NO, RPW>)   // (the exchange before its first use has a barrier)
+    for (int i = t; i < 512; i += NT) itab[(i & 7) * 64 + (i >> 3)] = tab[WaveTables<NO>::I3 + i];
 
   // the window: v[c NO + n_o] = x[n] - i x[n + N], n = t + NT c + 1024 n_o, x[i] = TOD sample
   // s0 + i inside the interval, else 0: window samples [a, b) are data, and a buffer over
   // them gives the zeros (every constant beside a column's offset is a multiple of 4096
   // bytes, which the instruction's offset field cannot hold)
   cx<T> v[S::E];
+  T mean = (T)0;   // the window's offset (fft.hpp)
+  const int64_t s0 = ch.out_start - n_c;
+  const int a = (int)(ch.iv_lo > s0 ? ch.iv_lo - s0 : 0);   // (iv_lo <= out_start: a <= n_c)
+  const int b = (int)(ch.iv_hi - s0 < 2 * N ? ch.iv_hi - s0 : 2 * N);
   if constexpr (SKY > 0) {
-    const int64_t s0 = ch.out_start - n_c;
-    const int a = (int)(ch.iv_lo > s0 ? ch.iv_lo - s0 : 0);
-    const int b = (int)(ch.iv_hi - s0 < 2 * N ? ch.iv_hi - s0 : 2 * N);
     const Rsrc ids = buffer_of(sky.idx + s0 + a, (b - a) * 4);
     const Rsrc ang = buffer_of(SKY == 3 ? sky.w + (s0 + a) : nullptr, SKY == 3 ? (b - a) * 8 : 0);
     const Tin* __restrict__ map = yin + (int64_t)rhs * sky.vs;
+    if constexpr (S::NW > 1) mean = window_mean<T, 2 * N>(t, [&](int n) {
+      const uint32_t k = (uint32_t)(n - a);
+      int32_t p;
+      float2 sc = make_float2(0.f, 0.f);
+      buffer_get(ids, opaque(4 * k), p);
+      if constexpr (SKY == 3) buffer_get(ang, opaque(8 * k), sc);
+      p = k < (uint32_t)(b - a) ? p : -1;
+      const double val = sky_value<SKY, Tin>(map, p >= 0 ? p : 0, sc.x, sc.y);
+      return p >= 0 ? (T)val : (T)0;
+    });
     constexpr int K = 2 * NO < 32 ? 2 * NO : 32;   // samples whose pixels are in registers at once
 #pragma unroll
     for (int c = 0; c < S::C; ++c) {
@@ -508,11 +531,12 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
       }
     }
   } else {
-    const int64_t s0 = ch.out_start - n_c;
-    const int64_t lo = ch.iv_lo, hi = ch.iv_hi;
-    const int a = (int)(lo > s0 ? lo - s0 : 0);   // (lo <= out_start: a <= n_c)
-    const int b = (int)(hi - s0 < 2 * N ? hi - s0 : 2 * N);
     const Rsrc src = buffer_of(yin + (int64_t)rhs * n_t + s0 + a, (b - a) * (int)sizeof(Tin));
+    if constexpr (S::NW > 1) mean = window_mean<T, 2 * N>(t, [&](int n) {
+      Tin x;
+      buffer_get(src, opaque((uint32_t)(n - a) * (uint32_t)sizeof(Tin)), x);
+      return (T)x;
+    });
 #pragma unroll
     for (int c = 0; c < S::C; ++c) {
       const uint32_t off = opaque((uint32_t)(t + NT * c - a) * (uint32_t)sizeof(Tin));
@@ -525,6 +549,19 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
       }
     }
   }
+  if constexpr (S::NW == 1) {   // one wavefront: from eight runs of 64 samples
+    T sum = (T)0, sq = (T)0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const cx<T> z = v[4 * i];
+      sum += z.re - z.im;
+      sq += z.re * z.re + z.im * z.im;
+    }
+    mean = offset_of<64>(sum, sq, 512);
+  }
+#pragma unroll
+  for (int e = 0; e < S::E; ++e) v[e] = {v[e].re - mean, v[e].im + mean};
+  const T* __restrict__ sym = spec + (int64_t)ch.filter * (N + 1);
   // forward, outer stage over n_o
   if constexpr (NO > 1) {
 #pragma unroll
@@ -534,12 +571,13 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
   // the rows of this wavefront
 #pragma unroll
   for (int i = 0; i < S::RPW; ++i)
-    filter_row<T, NO, sizeof(T) == 4 && RPW == 1, RPW == 2>(v + 16 * i, lds + w * kWRow, tab, spec + (int64_t)ch.filter * N, w + S::NW * i, t & 63);
+    filter_row<T, NO, RPW>(v + 16 * i, lds + w * kWRow, tab, sym, itab, w + S::NW * i, t & 63);
   exchange_rows<T, NO, RPW, false>(v, lds, t);
   // inverse, outer stage over k_o; the outputs n and n + N of the window, positions
   // [n_c, n_c + m) of it from out_start on, cut at the interval's end
   const int len = (int)(ch.iv_hi - ch.out_start < m ? ch.iv_hi - ch.out_start : m);
   const Rsrc dst = buffer_of(yout + (int64_t)rhs * n_t + ch.out_start, len * (int)sizeof(T));
+  const T back = mean * sym[N];   // what the filter makes of the mean
 #pragma unroll
   for (int c = 0; c < S::C; ++c) {
     if constexpr (NO > 1) dif_quarter<T, LOGNO>(v + c * NO);
@@ -547,8 +585,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
 #pragma unroll
     for (int n_b = 0; n_b < NO; ++n_b) {
       const cx<T> z = v[c * NO + n_b];
-      buffer_put(dst, off + 1024 * n_b * (uint32_t)sizeof(T), z.re);
-      buffer_put(dst, off + (1024 * n_b + N) * (uint32_t)sizeof(T), z.im);
+      buffer_put(dst, off + 1024 * n_b * (uint32_t)sizeof(T), z.re + back);
+      buffer_put(dst, off + (1024 * n_b + N) * (uint32_t)sizeof(T), z.im + back);
     }
   }
 }
@@ -561,22 +599,26 @@ __global__ void k_wave_tables(cx<T>* __restrict__ tab) {
   if (e >= W::TOTAL) return;
   // entry i of a stage with shift num / den, as a fraction of a turn: num / (den 2^(i + 1))
   auto stage = [](int i, double num, double den) -> double { return num / (den * (double)(2 << i)); };
+  // entry i of a 16-point stage
+  auto stage16 = [](int i, double num, double den) -> double {
+    const int len = i == 0 ? 2 : i == 1 ? 4 : i < 4 ? 8 : 16, j = i == 0 ? 0 : i - len / 4;
+    return (j * den + num) / ((double)len * den);
+  };
   double frac;
   if (e < W::F2) {
-    const int i = e % 8, len = i == 0 ? 2 : i == 1 ? 4 : i < 4 ? 8 : 16, j = i == 0 ? 0 : i - len / 4;
-    frac = (j * (double)NO + e / 8 + 0.25) / ((double)len * NO);
+    frac = stage16(e % 8, e / 8 + 0.25, NO);
   } else if (e < W::F3) {
     const int i = e - W::F2, k_o = i / 32, k1 = (i / 2) % 16;
     frac = stage(i % 2, k_o + 0.25 + (double)NO * k1, 16.0 * NO);
   } else if (e < W::I2) {
-    const int i = e - W::F3, k_o = i / 256, mu = (i / 4) % 64;
-    frac = stage(i % 4, k_o + 0.25 + (double)NO * mu, 64.0 * NO);
+    const int i = e - W::F3, k_o = i / 512, mu = (i / 8) % 64;
+    frac = stage16(i % 8, k_o + 0.25 + (double)NO * mu, 64.0 * NO);
   } else if (e < W::I3) {
     const int i = e - W::I2;
     frac = stage(i % 2, i / 2, 16.0);
   } else if (e < W::I4) {
     const int i = e - W::I3;
-    frac = stage(i % 4, i / 4, 64.0);
+    frac = stage16(i % 8, i / 8, 64.0);
   } else {
     const int i = e - W::I4, k_o = i / 1024, g = i % 1024;
     frac = (double)(g * (4 * k_o + 1)) / (4096.0 * NO);

@@ -649,7 +649,7 @@ void build_filter_nf(mm_plan_s* P, FilterSetup& fs, bool fp64, int64_t nf, hipSt
     fs.ptw = get((int64_t)std::max(ntw, 1) * 2 * esz);
     hipchk(launch_pass_twiddles(fs.ptw, logn, fp64, s, variant), "pass twiddle tables");
   }
-  fs.spec = get((int64_t)P->n_filt * fs.N * esz);
+  fs.spec = get((int64_t)P->n_filt * (fs.N + 1) * esz);
   char* sscr = P->temp<char>((int64_t)spectra_scratch_bytes(logn));
   build_symbols(fs, P->lags, P->n_filt, P->n_c, fs.spec, sscr, s);
   P->release(sscr);   // later work on this stream may reuse it
@@ -1269,7 +1269,7 @@ size_t filter_bytes(const std::vector<int64_t>& iv_start, int n_filt, int n_c, i
   }
   const int nq = quarter_count(logn, fp64, variant);
   return block_bytes(n_chunks * (int64_t)sizeof(OlsChunk), 1) + (nq ? block_bytes((int64_t)nq * 2 * esz, 1) : 0) + tw +
-         block_bytes((int64_t)n_filt * N * esz, 1);
+         block_bytes((int64_t)n_filt * (N + 1) * esz, 1);
 }
 
 // Upper bounds of a plan's device memory from its descriptor alone: persistent data,
@@ -1400,7 +1400,7 @@ PlanBounds plan_bounds(const mm_desc_t* d) {
     const int64_t N64 = int64_t(1) << logn64;
     const int64_t n_dots = (int64_t)std::max(d->n_intervals, 1) * interval_dot_parts(d->n_intervals, longest);
     B.call_temps = block_bytes(std::max<int64_t>(n, 1), 8) + block_bytes(3 * (int64_t)nf_filt * n_c, 8) +
-                   block_bytes(3 * (int64_t)nf_filt * N64, 8) + block_bytes(3 * n_dots, 8) +
+                   block_bytes(3 * (int64_t)nf_filt * (N64 + 1), 8) + block_bytes(3 * n_dots, 8) +
                    block_bytes((int64_t)std::max(lags_scratch_bytes(n_c, lag_len, batch),
                                                  spectra_scratch_bytes(logn64)), 1);
   }
@@ -2447,7 +2447,7 @@ mm_status_t mm_noise_gradient(mm_plan_t P, const void* d_tod, int32_t tod_dtype,
     const bool in64 = tod_dtype == MM_F64;
     const int esz = in64 ? 8 : 4;
     const int nfl = P->n_filt, n_iv = std::max(P->n_iv, 1);
-    const int64_t spec_n = (int64_t)nfl * f64.N;
+    const int64_t spec_n = (int64_t)nfl * (f64.N + 1);
     const int batch = std::max(1, std::min(nfl, 16));
     const size_t lsb = lags_scratch_bytes(P->n_c, P->lag_len, batch);
     // temporaries above the work vectors, released in reverse order on every exit

@@ -83,10 +83,11 @@ hipError_t launch_lags(const double* params /*dev [nf][3]*/, int n_filters, doub
                        size_t scratch_bytes, hipStream_t s, int mode = 0, int n_modes = 1);
 size_t lags_scratch_bytes(int n_c, int64_t lag_len, int filters_per_batch);
 // the symbol of filter f at the shifted frequencies k + 1/4 of N = 2^logn points, times 1/N:
-// F_k at spec[f][(k mod 2^rowlog) 2^(logn - rowlog) + (k >> rowlog)]
+// F_k at spec[f][(k mod 2^rowlog) 2^(logn - rowlog) + (k >> rowlog)], and at spec[f][N] the filter's
+// response to a constant, the sum of f(|tau|)
 size_t spectra_scratch_bytes(int logn);
 hipError_t launch_spectra(const double* lags, int n_filters, int n_c, int logn, int rowlog, bool fp64,
-                          void* spec /*[nf][N]*/, void* scratch, hipStream_t s);
+                          void* spec /*[nf][N + 1]*/, void* scratch, hipStream_t s);
 // y_out[r][t] = (N^-1 y_in)[r][t]; compute type T (fp64 flag); input type in_f64; output type T
 // st (optional): per-RHS CG states; rows of RHS no longer active are skipped
 hipError_t launch_ols(bool fp64, bool in_f64, int logn, const void* y_in, void* y_out,
