@@ -532,8 +532,10 @@ double ols_time_us(bool fp64, int logn, double c) {
 
 // n_f of a filter set-up that is not autotuned (secondary: the float64 filter of a
 // mixed plan, which takes a forced n_f only when it has a float64 transform): the on-chip
-// length above 2 n_c of the least predicted time, of those a forced shape has.  Where 2^15 is the smallest one (the
-// workloads' n_c = 8192) and the wavefront-private shapes may be taken, the choice between
+// length above 2 n_c of the least predicted time, whatever the forced shape (choose_variant takes
+// shape 1 where the length has no such shape; most shapes exist at one or two lengths, in
+// float64 at one or none, and the only one left above 2 n_c may be all halo).  Where 2^15 is the smallest
+// one (the workloads' n_c = 8192) and the wavefront-private shapes may be taken, the choice between
 // 2^15 and 2^16 goes by full rounds over the chip, one workgroup per CU in both: fewer
 // chunks, no more than 2.25 times the work each.
 int64_t choose_nf(int nf_req, int n_c, const std::vector<int64_t>& iv_start, int R, int shape_req, bool fp64,
@@ -555,14 +557,13 @@ int64_t choose_nf(int nf_req, int n_c, const std::vector<int64_t>& iv_start, int
   int64_t best = 0;
   double best_us = 0.0;
   for (int64_t nf = lo; ilog2(nf) - 1 <= maxlog; nf <<= 1) {
-    if (shape_req > 0 && !transform_exists(ilog2(nf) - 1, fp64, shape_req - 1)) continue;
     const double us = ols_time_us(fp64, ilog2(nf) - 1, (double)count_chunks(iv_start, nf - 2 * (int64_t)n_c) * std::max(R, 1));
     if (best == 0 || us < best_us) {
       best = nf;
       best_us = us;
     }
   }
-  return best ? best : lo;
+  return best;
 }
 
 int choose_variant(int shape_req, int64_t nf, bool fp64) {
