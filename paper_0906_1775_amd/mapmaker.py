@@ -42,6 +42,9 @@ def fft_length_rule(n_c: int, longest: int) -> int:
     return int(L.load().mm_fft_length_rule(int(n_c), int(longest)))
 
 
+_LAG_WORKSPACE = 68 << 20   # bytes up to which noise_lags takes more workspace than a call needs
+
+
 def noise_lags(params: torch.Tensor, f_samp: float, n_c: int, lag_dft_len: int = 1 << 20,
                deriv: int = 0) -> torch.Tensor:
     """Lags f(tau) [n_filters, n_c] (or their derivative, deriv = 1 .. 3 for sigma, f_knee,
@@ -53,8 +56,11 @@ def noise_lags(params: torch.Tensor, f_samp: float, n_c: int, lag_dft_len: int =
         raise ValueError("params must be a contiguous float64 CUDA tensor [n_filters, 3]")
     n = ctypes.c_size_t(0)
     L.check(lib.mm_noise_lags_workspace_size(int(n_c), int(lag_dft_len), ctypes.byref(n)), lib)
-    # room for a few filters: the library then takes more of them per launch
-    ws = torch.empty(int(n.value) * max(1, min(4, int(params.shape[0]))), dtype=torch.uint8, device=params.device)
+    # where that is small, room for up to four filters at once (64 at n_c = 8192: 0.66 ms with 4 x 16 MiB): the
+    # library takes more of them per launch; a large one already holds many
+    size = int(n.value)
+    ws = torch.empty(size * max(1, min(4, int(params.shape[0]), _LAG_WORKSPACE // size)), dtype=torch.uint8,
+                     device=params.device)
     out = torch.empty((params.shape[0], int(n_c)), dtype=torch.float64, device=params.device)
     L.check(lib.mm_noise_lags(_ptr(params), int(params.shape[0]), float(f_samp), int(n_c), int(lag_dft_len),
                               int(deriv), _ptr(out), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()), lib)
