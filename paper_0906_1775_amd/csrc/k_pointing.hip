@@ -739,16 +739,19 @@ __device__ __forceinline__ int64_t observed_id(const int32_t* __restrict__ obs2g
 template <int N> struct PartsArg {
   int n;
   LayoutPart part[N];
+  int first;   // blocks of earlier launches
+  __device__ __forceinline__ int block() const { return first + (int)blockIdx.x; }
   __device__ __forceinline__ const LayoutPart& mine() const {
     int k = 0;
     if constexpr (N > 1)
-      while (k + 1 < n && (int)blockIdx.x >= part[k + 1].block0) ++k;
+      while (k + 1 < n && block() >= part[k + 1].block0) ++k;
     return part[k];
   }
 };
-template <int N> static PartsArg<N> parts_arg(const LayoutParts& P) {
+template <int N> static PartsArg<N> parts_arg(const LayoutParts& P, int64_t first) {
   PartsArg<N> a;
   a.n = P.n;
+  a.first = (int)first;
   for (int k = 0; k < N && k < P.n; ++k) a.part[k] = P.part[k];
   return a;
 }
@@ -757,7 +760,7 @@ template <int N>
 __global__ __launch_bounds__(256) void k_to_observed(PartsArg<N> P, const double* __restrict__ glob, int64_t gs,
                                                      double* __restrict__ obs, int64_t os) {
   const LayoutPart L = P.mine();
-  const int64_t o = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  const int64_t o = (int64_t)(P.block() - L.block0) * 256 + threadIdx.x;
   if (o >= L.n_obs) return;
   const int64_t g = L.identity ? o : L.obs2glob[o];
   const double* __restrict__ src = glob + (int64_t)blockIdx.y * gs + L.goff + g * L.ns;
@@ -770,7 +773,7 @@ template <int N>
 __global__ __launch_bounds__(256) void k_to_global(PartsArg<N> P, const double* __restrict__ obs, int64_t os,
                                                    double* __restrict__ glob, int64_t gs) {
   const LayoutPart L = P.mine();
-  const int64_t g = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  const int64_t g = (int64_t)(P.block() - L.block0) * 256 + threadIdx.x;
   if (g >= L.n_glob) return;
   const int64_t o = L.identity ? g : observed_id(L.obs2glob, L.n_obs, (uint32_t)g, L.raster);
   const double* __restrict__ src = obs + (int64_t)blockIdx.y * os + L.ooff + o * L.ns;
@@ -783,7 +786,7 @@ template <int N>
 __global__ __launch_bounds__(256) void k_put_global(PartsArg<N> P, const double* __restrict__ obs, int64_t os,
                                                     double* __restrict__ glob, int64_t gs) {
   const LayoutPart L = P.mine();
-  const int64_t o = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  const int64_t o = (int64_t)(P.block() - L.block0) * 256 + threadIdx.x;
   if (o >= L.n_obs) return;
   const int64_t g = L.identity ? o : L.obs2glob[o];
   const double* __restrict__ src = obs + (int64_t)blockIdx.y * os + L.ooff + o * L.ns;
@@ -794,7 +797,7 @@ __global__ __launch_bounds__(256) void k_put_global(PartsArg<N> P, const double*
 template <int N>
 __global__ __launch_bounds__(256) void k_zero_global(PartsArg<N> P, double* __restrict__ glob, int64_t gs) {
   const LayoutPart L = P.mine();
-  const int64_t g = (int64_t)(blockIdx.x - L.block0) * 256 + threadIdx.x;
+  const int64_t g = (int64_t)(P.block() - L.block0) * 256 + threadIdx.x;
   if (g >= L.n_glob) return;
   double* __restrict__ dst = glob + (int64_t)blockIdx.y * gs + L.goff + g * L.ns;
   for (int c = 0; c < L.ns; ++c) dst[c] = 0.0;
@@ -810,11 +813,17 @@ static int64_t layout_blocks(LayoutParts& P, bool global) {
   return nb;
 }
 
-#define MM_PARTS(K, GRID, ...)                                                                           \
-  do {                                                                                                   \
-    if (P.n == 1) hipLaunchKernelGGL(K<1>, GRID, dim3(256), 0, s, parts_arg<1>(P), __VA_ARGS__);          \
-    else if (P.n <= 4) hipLaunchKernelGGL(K<4>, GRID, dim3(256), 0, s, parts_arg<4>(P), __VA_ARGS__);     \
-    else hipLaunchKernelGGL(K<kMaxLayoutParts>, GRID, dim3(256), 0, s, parts_arg<kMaxLayoutParts>(P), __VA_ARGS__); \
+// nb blocks a row, at most 2^23 (2^31 threads; 2^32 are refused) of them a launch
+#define MM_PARTS(K, NB, ...)                                                                                  \
+  do {                                                                                                        \
+    for (int64_t first = 0; first < (NB); first += 1 << 23) {                                                 \
+      const dim3 g((unsigned)std::min<int64_t>((NB) - first, 1 << 23), (unsigned)n_rhs);                       \
+      if (P.n == 1) hipLaunchKernelGGL(K<1>, g, dim3(256), 0, s, parts_arg<1>(P, first), __VA_ARGS__);         \
+      else if (P.n <= 4) hipLaunchKernelGGL(K<4>, g, dim3(256), 0, s, parts_arg<4>(P, first), __VA_ARGS__);    \
+      else hipLaunchKernelGGL(K<kMaxLayoutParts>, g, dim3(256), 0, s, parts_arg<kMaxLayoutParts>(P, first), __VA_ARGS__); \
+      const hipError_t e = hipGetLastError();                                                                 \
+      if (e != hipSuccess) return e;                                                                          \
+    }                                                                                                         \
   } while (0)
 
 hipError_t launch_to_observed(LayoutParts P, const double* glob, int64_t gs, double* obs, int64_t os, int n_rhs,
@@ -822,8 +831,8 @@ hipError_t launch_to_observed(LayoutParts P, const double* glob, int64_t gs, dou
   const int64_t nb = layout_blocks(P, false);
   if (nb == 0 || n_rhs == 0) return hipSuccess;
   if (nb > 0x7fffffff) return hipErrorInvalidValue;
-  MM_PARTS(k_to_observed, dim3((unsigned)nb, (unsigned)n_rhs), glob, gs, obs, os);
-  return hipGetLastError();
+  MM_PARTS(k_to_observed, nb, glob, gs, obs, os);
+  return hipSuccess;
 }
 
 // Every id observed: one pass over the observed ids.  Else zeros and that pass for large rows, the
@@ -837,20 +846,14 @@ hipError_t launch_to_global(LayoutParts P, const double* obs, int64_t os, double
   int64_t nb = layout_blocks(P, true);
   if (nb == 0 || n_rhs == 0) return hipSuccess;
   if (nb > 0x7fffffff) return hipErrorInvalidValue;
-  const dim3 g((unsigned)nb, (unsigned)n_rhs);
   if (!all && nb * 256 * n_rhs <= kSearchIds) {
-    MM_PARTS(k_to_global, g, obs, os, glob, gs);
-    return hipGetLastError();
+    MM_PARTS(k_to_global, nb, obs, os, glob, gs);
+    return hipSuccess;
   }
-  if (!all) {
-    MM_PARTS(k_zero_global, g, glob, gs);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  if (!all) MM_PARTS(k_zero_global, nb, glob, gs);
   nb = layout_blocks(P, false);
-  if (nb == 0) return hipSuccess;
-  MM_PARTS(k_put_global, dim3((unsigned)nb, (unsigned)n_rhs), obs, os, glob, gs);
-  return hipGetLastError();
+  MM_PARTS(k_put_global, nb, obs, os, glob, gs);
+  return hipSuccess;
 }
 
 #undef MM_PARTS
