@@ -187,7 +187,9 @@ typedef struct {
   int64_t device_bytes;         /* bytes of the workspace in use (at most the bound) */
   int64_t n_sliced;             /* entries of the scatter's pixel-major pointing: n_valid when
                                    it is read as is (128 or more hits per observed pixel on
-                                   average and at most 256 MiB of TOD per scatter pass), else
+                                   average and either at most 256 MiB of TOD per scatter pass, up to
+                                   2^18 pixels and, from 2^14 on, no raster to be seen, or 1024 or
+                                   more hits on at most 10,240 pixels), else
                                    the sliced copy's (a multiple of 64, >= n_valid; the excess
                                    is padding to the widest pixel of each slice) */
   int64_t n_tmpl;               /* template amplitudes per RHS in map-shaped buffers (0 = none) */

@@ -620,14 +620,18 @@ int scatter_blocks(int64_t n_obs, const SellLayout& L) {
 }
 
 // Lanes per pixel of the pixel-major scatter (128 hits and more on average, or a sliced copy that
-// would not fit).  16 fill the chip from 2^15 pixels on; fewer pixels with more hits need more
-// lanes each (us, float32, one RHS, with 16, 64 and 512 lanes: 144 pixels of 1500 hits 45, 15,
-// 11; 1024 of 4096 neighbouring hits 68, 27, 11; 1024 of 400 17, 11, 11.5; 25,600 of 200 41, 30,
-// -; 16,384 of 160 16, 21, 79).
-int seg_lanes(int64_t n_obs, int64_t n_valid) {
+// would not fit); row: one float32 row, columns: template columns.  16 lanes fill the chip from 2^13 pixels on;
+// fewer pixels with more hits need more lanes each (us with 16, 64 and 512 lanes; float32, one row: 144 pixels
+// of 1500 hits 45, 15, 11; 1600 of 10,500 319, 91, 75; 3840 of 4400 130, 71, 66; 1024 columns of 4096
+// neighbouring hits 68, 27, 11; 3840 of 1100 hits, 4 rows of Q, U 91, 64, -).  Beyond 4096 pixels 64 lanes pay
+// for one float32 row only (6400 of 655 hits, Q, U 31, 21, -; 10,000 of 840 75, 53, -; but 2 float64 rows, T, of
+// 8064 pixels of 2000 hits 69, 125, -, and 15,360 pixels of 1100, one float32 row, 53, 64, 93), and for a
+// single row of up to 2^14 columns (16,384 of 4096 hits 127, 104, 99 as neighbours and 131, 103, 212 in runs of 8).
+int seg_lanes(int64_t n_obs, int64_t n_valid, bool row, bool columns) {
   const double avg = n_obs > 0 ? (double)n_valid / (double)n_obs : 1.0;
-  if ((avg >= 2048 && n_obs <= (1 << 15)) || (avg >= 512 && n_obs <= 256)) return 512;
-  return avg >= 1024 || (avg >= 200 && n_obs <= (1 << 15)) || (avg >= 128 && n_obs <= (1 << 12)) ? 64 : 16;
+  if ((avg >= 2048 && n_obs <= (1 << 12)) || (avg >= 512 && n_obs <= 256)) return 512;
+  if (avg >= 128 && n_obs <= (1 << 12)) return 64;
+  return row && ((avg >= 200 && n_obs <= 10240) || (columns && avg >= 1024 && n_obs <= (1 << 14))) ? 64 : 16;
 }
 
 template <typename Ty, typename Tq, typename Tp>

@@ -840,15 +840,19 @@ constexpr int64_t kSegTodBytes = int64_t(256) << 20;
 //   is the faster one while the TOD allows it (4096 of 400: 31 and 13, 65,536 of 400: 142 and 119);
 // - beyond, the slices fill the chip by themselves and more wavefronts only pay for long rows
 //   (3 M x 20: 305 with 1, 338 with 4; 2^20 x 200: 1163, 1003 and 1042 with 1, 4 and 8);
-// - with 1024 hits pixel-major whatever the TOD, 64 lanes or more on a pixel's hits (1024 columns
-//   of 4096 neighbouring samples: 170 sliced, 27 with 64 lanes, 11 with 512);
+// - with 1024 hits pixel-major whatever the TOD for template columns, whose hits are neighbours or
+//   few runs (1024 columns of 4096 samples: 170 sliced, 27 with 64 lanes, 11 with 512; 16,384 of
+//   16,384: 814 and 427), and for maps of up to 2^13 pixels (10,240 with one float32 row), whose
+//   slices leave the chip idle (1600 pixels of 167,000 hits: 13,500 and 1410; 8064 of 8300, 2 float64
+//   rows: 604 and 351; 10,000 of 27,000: 1974 and 1405).  Larger maps are sliced as with fewer hits:
+//   15,360 of 17,000 846 and 1020, 65,000 of 4200 628 and 876, 150,000 of 1800 512 and 801;
 // - with the pixels by tiles of a raster a slice shares TOD lines as no run of hits does, so
 //   pixel-major is left to the maps that are too small for slices (157 x 157 of 256, 3 float64
 //   rows: 70 pixel-major, 66 sliced; 256 x 256 of 256 72 and 68; 400 x 400 195 and 156).
-int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid, bool tiles) {
+int layout_waves(int64_t n_t, bool fp64, int R, int64_t n_obs, int64_t n_valid, bool tiles, bool columns) {
   const double avg = n_obs > 0 ? (double)n_valid / (double)n_obs : 1.0;
   if (tiles && n_obs > (1 << 14)) return n_obs <= (1 << 18) ? 8 : avg >= 96 ? 4 : avg >= 48 ? 2 : 1;
-  if (avg >= 1024) return 0;
+  if (avg >= 1024 && (columns || n_obs <= (!fp64 && R == 1 ? 10240 : 8192))) return 0;
   if (n_obs <= (1 << 18)) return avg >= 128 && n_t * (fp64 ? 8 : 4) * std::min(R, 4) <= kSegTodBytes ? 0 : 8;
   return avg >= 96 ? 4 : avg >= 48 ? 2 : 1;
 }
@@ -947,7 +951,7 @@ void build_layout(mm_plan_s* P, const int32_t* d_key, int64_t n_keys, int ns, co
     if (*P->slot<int32_t>(kPinFlag)) fail(MM_EINVAL, range_msg);
     L.n_obs = *P->slot<uint32_t>(kPinObs);
     L.n_valid = *P->slot<int64_t>(kPinValid);
-    L.wps = layout_waves(n, P->main_fp64(), P->R, L.n_obs, L.n_valid, L.raster.w != 0);
+    L.wps = layout_waves(n, P->main_fp64(), P->R, L.n_obs, L.n_valid, L.raster.w != 0, &L != &P->px);
     L.sell.run = scatter_run(L.raster, n_keys, L.n_obs, P->main_fp64(), P->R);
     L.ptr = P->alloc<int64_t>(L.n_obs + 1);
     L.obs2glob = P->alloc<int32_t>(L.n_obs);
@@ -1013,7 +1017,7 @@ void build_sell(mm_plan_s* P, Layout& L, int ns, hipStream_t s) {
   auto keep_pixel_major = [&]() {
     L.sell_entries = L.n_valid;
     L.sell.wps = 0;
-    L.sell.lanes = seg_lanes(L.n_obs, L.n_valid);
+    L.sell.lanes = seg_lanes(L.n_obs, L.n_valid, !P->main_fp64() && P->R == 1, &L != &P->px);
     L.sell.ptr = L.ptr;
     L.sell.perm = L.perm;
     L.sell.w_pm = L.w_pm;

@@ -177,7 +177,8 @@ hipError_t launch_scatter_q32(int ns, const SellLayout& L, const float* y, float
                               double* pq_part, int pq_stride, int pq_slot, const CgState* st);
 // blocks (= p.q partial sums) of a scatter over the n_obs pixels of a layout
 int scatter_blocks(int64_t n_obs, const SellLayout& L);
-int seg_lanes(int64_t n_obs, int64_t n_valid);   // lanes per pixel of the pixel-major scatter
+// lanes per pixel of the pixel-major scatter (row: one float32 row; columns: template columns)
+int seg_lanes(int64_t n_obs, int64_t n_valid, bool row, bool columns);
 hipError_t launch_convert(bool in_f64, bool out_f64, const void* in, void* out, int64_t n,
                           hipStream_t s);
 // observed <-> global layout of n_rhs rows (strides os, gs in doubles): the map and the template blocks
