@@ -207,6 +207,50 @@ template <> struct Acc<float> {
   __device__ double value() const { return (double)s + (double)c; }
 };
 
+// A batch of NB samples of one pixel (t < 0: none) added to its sums.  float64: the batch's values meet
+// pairwise before they go to the running sum, which a long row would otherwise round once per hit
+// (2^24 samples of 256 x 256 pixels in 8 wavefronts a slice: error 2.2e-16 of the sums, 1.8e-16 with 16
+// lanes a pixel, 1.65e-16 so).
+template <int NS, int NB, typename Ty>
+__device__ __forceinline__ void add_batch(Acc<Ty>* a, const Ty* v, const int32_t* t, const float2* w) {
+  if constexpr (sizeof(Ty) == 8) {
+    static_assert((NB & (NB - 1)) == 0, "pairs");
+    Ty x[NS][NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if constexpr (NS == 1) {
+        x[0][b] = v[b];
+      } else {   // (w of an empty slot may be anything)
+        const Ty h = (Ty)0.5 * v[b];
+        x[0][b] = h;
+        x[1][b] = t[b] >= 0 ? h * (Ty)w[b].x : (Ty)0;
+        x[2][b] = t[b] >= 0 ? h * (Ty)w[b].y : (Ty)0;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NS; ++c) {
+#pragma unroll
+      for (int d = NB / 2; d >= 1; d >>= 1)
+#pragma unroll
+        for (int b = 0; b < d; ++b) x[c][b] += x[c][b + d];
+      a[c].add(x[c][0]);
+    }
+  } else {
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (t[b] < 0) continue;
+      if constexpr (NS == 1) {
+        a[0].add(v[b]);
+      } else {
+        const Ty h = (Ty)0.5 * v[b];
+        a[0].add(h);
+        a[1].add(h * (Ty)w[b].x);
+        a[2].add(h * (Ty)w[b].y);
+      }
+    }
+  }
+}
+
 // Sliced layout of the pixel-major pointing: slice s holds the 64 observed
 // pixels 64s .. 64s+63; entry (j, L) at sell_off[s] + 64 j + L is the j-th
 // sample (in time order) of pixel 64s + L, or -1 past that pixel's hits.  A
@@ -397,18 +441,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter(
             const Ty yv = yr[tt[b] >= 0 ? tt[b] : 0];
             vv[b] = tt[b] >= 0 ? yv : (Ty)0;
           }
-#pragma unroll
-          for (int b = 0; b < kBatch; ++b) {
-            if (tt[b] < 0) continue;
-            if (NS == 1) {
-              a[g][0].add(vv[b]);
-            } else {
-              const Ty h = (Ty)0.5 * vv[b];
-              a[g][0].add(h);
-              a[g][1].add(h * (Ty)ww[b].x);
-              a[g][2].add(h * (Ty)ww[b].y);
-            }
-          }
+          add_batch<NS, kBatch, Ty>(a[g], vv, tt, ww);
         }
       }
       const int64_t o = s * 64 + lane;
@@ -533,18 +566,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void k_scatter_seg(
             const Ty yv = yr[tt[b] >= 0 ? tt[b] : 0];
             vv[b] = tt[b] >= 0 ? yv : (Ty)0;
           }
-#pragma unroll
-          for (int b = 0; b < kSegBatch; ++b) {
-            if (tt[b] < 0) continue;
-            if (NS == 1) {
-              a[g][0].add(vv[b]);
-            } else {
-              const Ty h = (Ty)0.5 * vv[b];
-              a[g][0].add(h);
-              a[g][1].add(h * (Ty)ww[b].x);
-              a[g][2].add(h * (Ty)ww[b].y);
-            }
-          }
+          add_batch<NS, kSegBatch, Ty>(a[g], vv, tt, ww);
         }
       }
       if constexpr (kWide) {   // wavefront sums, then one thread per value adds them in wavefront order
