@@ -80,11 +80,11 @@ __device__ __forceinline__ void gather_tile(const int32_t* __restrict__ pix_obs,
 // the tiles in time order; with it block b takes one tile, the tiles sorted by
 // the pixels they see, so that tiles that run at once look up the same part of the
 // map: dealt to the 8 XCDs in turn, or (eighths) each XCD a contiguous eighth of them,
-// b -> (b mod 8) * ceil(n_tiles / 8) + b / 8.  Eighths suit several rows of a map that is
-// swept along one axis (8 rows of 4096 x 768 pixels, a whole solve: 226 ms against
-// 233); else the lookups of one part of the map crowd one L2, and tiles are dealt
-// (2^27 samples of 1024 x 1024 pixels 499 us against 627, 2^26 of 1000 x 1000 251
-// against 313, where the streams alone take 365 and 180).
+// b -> (b mod 8) * ceil(n_tiles / 8) + b / 8.  Maps swept along one axis take eighths (8 float32 rows of
+// 4096 x 768 pixels, a whole solve 226 ms against 233; one row of 12,288 x 4096, T, 459 us against 492, 2^28
+// samples of 4096 x 768, Q, U, 872 against 921); with the pixels by tiles of a raster the lookups of one
+// part of the map crowd one L2, and tiles are dealt (2^27 samples of 1024 x 1024 pixels 499 us against 627,
+// 2^26 of 1000 x 1000 251 against 313, where the streams alone take 365 and 180).
 template <typename Ty, int NS, typename Tp>
 __global__ __launch_bounds__(256) void k_gather(const int32_t* __restrict__ pix_obs,
                                                 const float2* __restrict__ w,

@@ -700,7 +700,7 @@ void gather_all(mm_plan_s* P, bool y_f64, const double* x, void* y, int R, hipSt
                 const CgState* st = nullptr, const float* x32 = nullptr) {
   const int64_t vs = P->nu();
   hipchk(launch_gather(y_f64, P->ns, P->px.obs_idx, P->w, x, vs, y, P->n_t, P->n_obs, R, s, st, x32, P->vs32(),
-                       P->gather_order, R > 1 && P->px.raster.w == 0),
+                       P->gather_order, P->px.raster.w == 0),
          "gather");
   for (const Template& T : P->tmpl) {
     const int64_t off = P->nmap() + T.ooff;
