@@ -50,10 +50,6 @@ template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
-template <typename T>
-__device__ __forceinline__ cx<T> cconj(cx<T> a) { return {a.re, -a.im}; }
-template <typename T>
-__device__ __forceinline__ cx<T> cscale(cx<T> a, T s) { return {a.re * s, a.im * s}; }
 
 // cos(2 pi k / 32), k in [0, 32) (correctly rounded decimal expansions for k <= 8)
 __host__ __device__ constexpr double cos32_first_octant(int k) {
@@ -352,7 +348,6 @@ struct BlockFFT {
 
   static constexpr int first_log_fwd() { return flog(0); }
   static constexpr int last_log_fwd() { return flog(NP - 1); }
-  static constexpr int first_log_rev() { return ilog(0); }
   static constexpr int last_log_rev() { return ilog(NP - 1); }
 };
 

@@ -205,10 +205,10 @@ hipError_t launch_fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
 // ---------------------------------------------------------------- plan (k_sort.hip)
-// flag[0] = 1 if any pix is < -1 or >= n_pix
 // step[0] = the most frequent distance beyond 1 between a sample's pixel and the next other one
 // (0: none), step[1] = how often it occurs, step[2] = how many distances, of samples spread over the TOD
 hipError_t launch_raster_step(const int32_t* pix, int64_t n, int32_t* step, hipStream_t s);
+// flag[0] = 1 if any pix is < -1 or >= n_pix
 hipError_t launch_check_pix(const int32_t* pix, int64_t n, int64_t n_pix, int32_t* flag,
                             hipStream_t s);
 size_t sort_scratch_bytes(int64_t n);
