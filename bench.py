@@ -65,7 +65,7 @@ WORKLOADS = {
           "8 noise realisations as RHS, n_c 8192",
 }
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_0906_1775_amd", "csrc", f)
-                  for f in ("k_filter.hip", "k_ols_wave.hip", "fft.hpp")]
+                  for f in ("k_filter.hip", "k_ols_wave.hip", "fft.hpp", "sky.hpp")]
 
 
 def traffic_file(workload: str) -> str:
