@@ -199,7 +199,8 @@ typedef struct {
 /*
  * Device bytes a plan of this descriptor needs in its workspace (an upper bound
  * computed from the descriptor alone: it holds for any pointing the descriptor
- * admits).  The plan holds the time-major observed index and the pixel-major
+ * admits, on the device that is current in this call and in mm_plan: the default
+ * n_f depends on its number of compute units).  The plan holds the time-major observed index and the pixel-major
  * (or sliced) pointing of the pixel-indexing scheme (Implementation section),
  * the lags and overlap-save spectra of N^-1 (Weighting section), the block
  * preconditioner (Implementation section), and the TOD and CG work vectors of

@@ -506,22 +506,25 @@ int compute_units() {
   return cached_cu;
 }
 
-// Workgroup time of one 2^15-point wavefront-private transform over one 2^14-point one
-// (2^28 float32 samples at n_c = 8192: 834 us for 5,632 jobs at n_f = 2^16 against 1,064 us
-// for 16,384 at 2^15)
+// Workgroup time of one 2^15-point wavefront-private transform over one 2^14-point one, as the
+// documented default length takes it.  Measured on 2^28 float32 samples at n_c = 8192: 914 us for
+// 5,462 jobs at n_f = 2^16, 22 rounds of 256, against 1,066 us for 16,384 at 2^15, 64 rounds (2.5
+// a round; 2.25 where the window's mean is not looked for).  The two lie close together between
+// these factors, so that either length costs a tenth at most.
 constexpr double kWave15Cost = 2.25;
 
 // Predicted time of a filter pass over c chunks with transforms of 2^logn points, in us, for the
 // comparison of lengths.  A wavefront-private transform fills the chip with 16 >> (logn - 10)
 // workgroups per compute unit (one at least): whole rounds take full_us each, a last one between
 // alone_us, one chunk by itself, and that.  The workgroup transforms of 2^6 .. 2^9 points take
-// chunk_ns per chunk.  Measured over n_c = 32 .. 3000 and 9,000 to 5 10^7 samples, where the
-// length it picks is at most a tenth slower than the best one.
+// chunk_ns per chunk.  Fitted to 126 combinations of n_c = 32 .. 3000, 9,000 to 5 10^7 samples and
+// 1 or 3 rows, where the length it picks is 0.2 % slower than the best one on average and 3.9 % at
+// most (1.0 % and 13 % with the times of transforms that do not take the window's mean off).
 double ols_time_us(bool fp64, int logn, double c) {
   constexpr double kLaunch = 5.0;
-  constexpr double chunk_ns[2][4] = {{0.5, 0.7, 0.95, 2.1}, {0.8, 1.2, 1.9, 4.7}};
-  constexpr double alone_us[2][6] = {{2.5, 2.5, 2.7, 4.4, 8.0, 20.0}, {2.6, 2.6, 5.0, 10.0, 20.0, 0.0}};
-  constexpr double full_us[2][6] = {{13.0, 14.2, 14.7, 16.0, 22.0, 43.0}, {22.5, 25.0, 25.0, 31.0, 42.0, 0.0}};
+  constexpr double chunk_ns[2][4] = {{0.53, 0.71, 0.95, 2.0}, {1.02, 1.27, 1.92, 4.99}};
+  constexpr double alone_us[2][6] = {{2.6, 2.5, 2.7, 4.2, 8.3, 24.0}, {2.6, 2.8, 5.0, 10.3, 20.1, 0.0}};
+  constexpr double full_us[2][6] = {{14.1, 14.9, 15.7, 17.6, 23.3, 47.9}, {23.6, 29.1, 27.3, 30.9, 37.8, 0.0}};
   const int p = fp64 ? 1 : 0;
   if (logn < 10) return kLaunch + 1e-3 * chunk_ns[p][logn - kMinLogN] * c;
   const int i = logn - 10;
@@ -537,7 +540,7 @@ double ols_time_us(bool fp64, int logn, double c) {
 // float64 at one or none, and the only one left above 2 n_c may be all halo).  Where 2^15 is the smallest
 // one (the workloads' n_c = 8192) and the wavefront-private shapes may be taken, the choice between
 // 2^15 and 2^16 goes by full rounds over the chip, one workgroup per CU in both: fewer
-// chunks, no more than 2.25 times the work each.
+// chunks, about 2.25 times the work each.
 int64_t choose_nf(int nf_req, int n_c, const std::vector<int64_t>& iv_start, int R, int shape_req, bool fp64,
                   bool secondary) {
   const int maxlog = ols_max_logn(fp64);
@@ -1279,7 +1282,8 @@ size_t filter_bytes(const std::vector<int64_t>& iv_start, int n_filt, int n_c, i
 
 // Upper bounds of a plan's device memory from its descriptor alone: persistent data,
 // work vectors, the build's temporaries (stacked over the work region) and the
-// temporaries of later calls (stacked above the TOD work buffers).  Every count the
+// temporaries of later calls (stacked above the TOD work buffers), and the compute units of
+// the current device, at which choose_nf looks.  Every count the
 // data decide is bounded: observed pixels by min(n_pix, n_samples) (one-hot
 // amplitudes by min(n_amp, n_samples)), pointed samples by n_samples, a sliced
 // scatter layout by sliced_allowance, the p.q partial sums by kScatterBlocks per
