@@ -319,6 +319,14 @@ __device__ __forceinline__ void exchange_rows(cx<T>* v, typename Slot<T>::type* 
   } else {
     constexpr int PARTS = sizeof(T) == 4 ? 1 : 2, H = S::NW;   // H rows in LDS at a time
     const int l = t & 63, w = t >> 6;
+    // Two rows in registers: the rows beyond an LDS instruction's offset from a base of their own,
+    // which the compiler does not see through (else it holds eight addresses instead of one over both
+    // rows, beside 64 registers of points, and spills: 2^24 samples 71.1 us against 68.3 with this and
+    // the rows' own addresses, 2^33 27.1 ms and 91.7 GB of traffic against 25.9 and 78.1)
+    const int far = RPW == 2 ? (int)opaque((uint32_t)(t + 8 * kWRow)) : t;
+    auto column = [&](int k, int c) {
+      return RPW == 2 && k >= 8 ? far + (k - 8) * kWRow + S::NT * c : k * kWRow + t + S::NT * c;
+    };
     cx<T> out[S::E];
 #pragma unroll
     for (int i = 0; i < S::RPW; ++i)
@@ -341,7 +349,7 @@ __device__ __forceinline__ void exchange_rows(cx<T>* v, typename Slot<T>::type* 
 #pragma unroll
           for (int c = 0; c < S::C; ++c)
 #pragma unroll
-            for (int k = 0; k < H; ++k) put(k * kWRow + t + S::NT * c, v[c * NO + H * i + k]);
+            for (int k = 0; k < H; ++k) put(column(k, c), v[c * NO + H * i + k]);
         } else {
 #pragma unroll
           for (int j = 0; j < 16; ++j) put(w * kWRow + l + 64 * j, v[16 * i + j]);
@@ -354,7 +362,7 @@ __device__ __forceinline__ void exchange_rows(cx<T>* v, typename Slot<T>::type* 
 #pragma unroll
           for (int c = 0; c < S::C; ++c)
 #pragma unroll
-            for (int k = 0; k < H; ++k) get(k * kWRow + t + S::NT * c, out[c * NO + H * i + k]);
+            for (int k = 0; k < H; ++k) get(column(k, c), out[c * NO + H * i + k]);
         }
       }
 #pragma unroll
@@ -395,6 +403,7 @@ __device__ __forceinline__ void filter_row(cx<T>* v, typename Slot<T>::type* row
   // everywhere in float64 spill (NO = 1: 142 us against 82; an operator of 2 x 2^24 samples at
   // NO = 16, the 4-point stages alone: 599 against 517).
   constexpr bool SUM6 = sizeof(T) == 8, INV6 = sizeof(T) == 8 || NO > 2;
+  if (TWO) l = (int)opaque((uint32_t)l);   // (each row forms its addresses anew)
   const int m = l & 15, hq = l >> 4;
   const cx<T>* __restrict__ t2 = tab + W::F2 + (uint32_t)((k_o * 16 + 4 * hq) * 2);
   const cx<T>* __restrict__ t3 = tab + W::F3 + (uint32_t)((k_o * 64 + l) * 8);
@@ -559,6 +568,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(WaveShape<NO, RPW>::NT, Wa
     }
     mean = offset_of<64>(sum, sq, 512);
   }
+  if constexpr (RPW == 2) mean = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mean)));   // (the same in every lane)
 #pragma unroll
   for (int e = 0; e < S::E; ++e) v[e] = {v[e].re - mean, v[e].im + mean};
   const T* __restrict__ sym = spec + (int64_t)ch.filter * (N + 1);

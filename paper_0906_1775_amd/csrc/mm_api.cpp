@@ -507,10 +507,10 @@ int compute_units() {
 }
 
 // Workgroup time of one 2^15-point wavefront-private transform over one 2^14-point one, as the
-// documented default length takes it.  Measured on 2^28 float32 samples at n_c = 8192: 914 us for
-// 5,462 jobs at n_f = 2^16, 22 rounds of 256, against 1,066 us for 16,384 at 2^15, 64 rounds (2.5
+// documented default length takes it.  Measured on 2^28 float32 samples at n_c = 8192: 877 us for
+// 5,462 jobs at n_f = 2^16, 22 rounds of 256, against 1,080 us for 16,384 at 2^15, 64 rounds (2.36
 // a round; 2.25 where the window's mean is not looked for).  The two lie close together between
-// these factors, so that either length costs a tenth at most.
+// these factors, so that either length costs a twentieth at most.
 constexpr double kWave15Cost = 2.25;
 
 // Predicted time of a filter pass over c chunks with transforms of 2^logn points, in us, for the
