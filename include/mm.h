@@ -415,8 +415,8 @@ mm_status_t mm_noise_lags(const double* d_params, int32_t n_filters, double f_sa
  * lags, with no workspace argument and no allocation.  Its scratch is a static
  * device array of 64 MiB that each device the library runs on holds until the
  * process ends; arguments whose scratch need (mm_noise_lags_workspace_size)
- * exceeds 64 MiB are rejected with MM_EINVAL (for n_c = 8192 the 2^20-point
- * construction needs 16 MiB per filter).  Every call on a device uses that
+ * exceeds 64 MiB are rejected with MM_EINVAL (16 MiB for n_c = 8192 and the
+ * 2^20-point construction, whose filters go through the array in groups).  Every call on a device uses that
  * device's one array: calls that overlap in time on one device race, so the
  * caller serialises them (one stream, or its own synchronisation).  Nothing in
  * the array needs to start at zero.  Arguments and errors as mm_noise_lags.

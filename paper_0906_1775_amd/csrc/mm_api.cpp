@@ -720,8 +720,9 @@ void gather_all(mm_plan_s* P, bool y_f64, const double* x, void* y, int R, hipSt
 // back, and looks up the samples that windows share twice (halo times the lookups).  Separate /
 // fused, us: up to 2^20 samples everywhere 1.05 to 1.24 times faster (an iteration of 65,536
 // samples: T 30.8 / 26.9, polarisation 35.2 / 32.6); temperature at every size (operator, 2^26
-// samples of 2000 x 2000 pixels, 4 float64 rows 3632 / 2971, 8 float32 rows of 4096 x 768 3280 /
-// 3287); polarisation in float64 up to halo 1.6 (2^24 samples: 244 / 206 at 1.32, 266 / 233 at
+// samples of 2000 x 2000 pixels, 4 float64 rows 3632 / 2971, 8 float32 rows of 4096 x 768 3520 /
+// 3477; also where the map exceeds the caches: 12,288 x 4096 pixels, one float32 row 1626 / 1564, 8
+// 7562 / 7299, 4 float64 rows 5364 / 4756); polarisation in float64 up to halo 1.6 (2^24 samples: 244 / 206 at 1.32, 266 / 233 at
 // 1.58, 310 / 310 at 2); in float32 one row of the search direction with up to 2^13 points
 // (iteration, 2^26 samples: 696 / 653; 2^24: 195 / 182, at worst 206 / 209; with the two rows a
 // wavefront of 2^15 points 764 / 779), more rows while they are small, since each reads the
