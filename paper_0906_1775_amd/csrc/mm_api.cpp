@@ -518,7 +518,7 @@ constexpr double kWave15Cost = 2.25;
 // workgroups per compute unit (one at least): whole rounds take full_us each, a last one between
 // alone_us, one chunk by itself, and that.  The workgroup transforms of 2^6 .. 2^9 points take
 // chunk_ns per chunk.  Fitted to 126 combinations of n_c = 32 .. 3000, 9,000 to 5 10^7 samples and
-// 1 or 3 rows, where the length it picks is 0.2 % slower than the best one on average and 3.9 % at
+// 1 or 3 rows, where the length it picks is 0.2 % slower than the best one on average and 5 % at
 // most (1.0 % and 13 % with the times of transforms that do not take the window's mean off).
 double ols_time_us(bool fp64, int logn, double c) {
   constexpr double kLaunch = 5.0;
